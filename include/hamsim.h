@@ -132,22 +132,21 @@ hs_status hs_build_factors(int n_qubits, int n_terms, const char *const *pauli_t
  * FP64.  Results do not depend on the batch size or on fusion (with
  * HS_RENORM the FP64 norm sums per tile, and tiles differ between batch
  * sizes, so renormalised complex128 results agree to FP64 rounding).
- * Launch shapes follow four environment variables, read at every call (a
- * handle keeps one launch plan per setting): HAMSIM_WMIN_BYTES (shortest
- * row run of a strided tile, default 256), HAMSIM_MAX_FUSE (factors per
- * launch, 1..8, default 8), HAMSIM_XCD_SWIZZLE (which launches deal
- * contiguous eighths of their tiles to the 8 XCDs: 0 none, 1 all, 2 strided,
- * 3 contiguous, default 3) and HAMSIM_PAIR_LDS (which closed complex64
- * launches whose row pairs read adjacent LDS partners use the pair kernel:
- * 0 none, 1 all except one-state strided launches with row runs under
- * 1 KiB whose factors are stored in natural order, 2 all; odd offsets of
- * contiguous tiles included; default 1).  Results are
- * the same bits for every setting, and for every storage order
- * (hs_factor_storage).
- * A factor whose coupling range fits no tile held in LDS (e.g. X_0 X_{n-1}
- * at large n) is applied out of place into a scratch state (allocated on
- * first use, counted by hs_footprint) and copied back.  Calls that share a
- * handle share its workspace, so they must be ordered on one stream.
+ * How: a factor couples a row only with the rows its group's X-masks reach, a
+ * coset of 2^rho rows, and acts on every coset as one small dense matrix of
+ * entries of the factor's local unitary (times D for the factor that carries
+ * it).  hs_evolve applies these matrices to tiles of the state held in LDS
+ * and reads neither the stored diagonals nor their structural zeros; entries
+ * are rounded as the stored ones are and summed in ascending-offset order, so
+ * the results are those of one DIA SpMV per factor bit for bit.
+ * Launch shapes follow two environment variables, read at every call (a
+ * handle keeps one launch plan per setting): HAMSIM_WMIN_BYTES (shortest row
+ * run of a strided tile, default 256) and HAMSIM_MAX_FUSE (factors per
+ * launch, 1..8; 8, the default, sets no limit).  HAMSIM_XCD_SWIZZLE and
+ * HAMSIM_PAIR_LDS are accepted and change nothing.  Results are the same bits
+ * for every setting, and for every storage order (hs_factor_storage).
+ * Calls that share a handle share its workspace, so they must be ordered on
+ * one stream.
  * The state is checked (device memory, batch * N elements inside one
  * allocation) before anything else, also when steps is 0.
  * Small states (N <= 2048 complex64 or 1024 complex128 rows by default; the
@@ -217,20 +216,23 @@ hs_status hs_footprint(hs_factors f, int batch, size_t *bytes);
  * the rows, so a factor closed in complex64 can need the open launch and its
  * scratch state in complex128).  For admission before building. */
 hs_status hs_footprint_dtype(hs_factors f, int batch, hs_dtype dtype, size_t *bytes);
-/* The launches one Trotter step makes for `batch` states with evolve `flags`:
- * *n_launches receives their count; launch i applies the factors at
- * positions [first_factor[i], first_factor[i] + n_factors[i]) of the part's
- * factor sequence (arrays of `cap` entries, may be NULL to query the count).
+/* The fusion list of one Trotter step for `batch` states with evolve `flags`:
+ * *n_launches receives its length; entry i holds the factors at positions
+ * [first_factor[i], first_factor[i] + n_factors[i]) of the part's factor
+ * sequence (arrays of `cap` entries, may be NULL to query the count) that one
+ * tile of the batch's rows is closed under.  It is what a launch per closed
+ * tile of stored diagonals would be; hs_evolve takes the states of a batch
+ * tile by tile and may need fewer launches.
  * `part` selects the step: 0 a lone step (the sequence of hs_step_sequence),
  * and of an evolution of several steps 1 the first (s_0 .. s_{L-2} J),
  * 2 a middle one (s_1 .. s_{L-2} J), 3 the last (s_1 .. s_{L-1}), with J the
  * joint factor (hs_step_joint); without a joint all four are the plain step.
- * A launch of several factors is one fused kernel; batches above
- * HS_MAX_BATCH repeat the list per chunk. */
+ * Batches above HS_MAX_BATCH repeat the list per chunk. */
 hs_status hs_step_launches(hs_factors f, int batch, unsigned flags, int part, int *n_launches,
                            int *first_factor, int *n_factors, int cap);
-/* Sets *violated to 1 if any in-place launch met a nonzero coefficient that
- * couples rows of different tiles (never for factors built here); syncs. */
+/* Sets *violated to 1 if an evolution met a nonzero coefficient that couples
+ * rows of different tiles.  Tiles are formed from the masks the coefficients
+ * come from, so it stays 0; syncs. */
 hs_status hs_check(hs_factors f, void *stream, int *violated);
 /* Release a handle.  Device memory is returned stream-ordered on the build
  * stream; work that uses the factors on other streams must have completed. */

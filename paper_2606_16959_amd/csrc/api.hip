@@ -10,12 +10,14 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
 #include <tuple>
 #include <vector>
 
+#include "gate_plan.h"
 #include "hs_internal.h"
 #include "tile_plan.h"
 
@@ -89,22 +91,14 @@ hs_status hip_fail(hipError_t e, const char *what) {
         if (e_ != hipSuccess) return hip_fail(e_, what);    \
     } while (0)
 
+// One entry of the fusion list (hs_step_launches): consecutive factors whose
+// coupling hulls one closed tile of the batch's rows holds.
 struct Run {
     int first = 0;              // position of the first factor in the step sequence
     std::vector<int> factors;   // factor indices at consecutive sequence positions
     Geo geo;
-    int launch_batch = 1;       // states per launch (1 when the chunk does not fit)
     bool elementwise = false;   // a single main-diagonal factor
-    bool open = false;          // no closed tile holds the factor's coupling range: open
-                                // launch into the scratch state, then copied back
-    bool pairs = false;         // closed complex64 launch whose every diagonal pairs: the
-                                // partners of a thread's two rows are adjacent LDS entries
-                                // (regular offset; even-aligned unless the offset is odd)
-    bool pairs_odd = false;     // ... and some offset is odd (contiguous tile, one-row windows):
-                                // the pair kernel's odd-offset path
-    bool perm = false;          // some diagonal is stored out of natural order (perm_pos)
-    int desc_start = 0;
-    std::vector<int> dstart;    // per factor, relative to desc_start (size nf + 1)
+    bool open = false;          // no closed tile holds the factor's coupling range
 };
 
 // The factor sequence of each part of an evolution of several steps.  With a
@@ -125,12 +119,15 @@ std::vector<int> part_sequence(const Plan &P, int part) {
     return out;
 }
 
-struct EvolvePlan {
-    int swizzle = 0;
-    bool needs_scratch = false;  // some run is open
-    std::vector<Run> runs[kParts];
-    std::vector<DiagDesc> host_desc;
-    DiagDesc *dev_desc = nullptr;
+// The coset program of every step part on the device, with its launches
+// (gate_plan.h).
+struct GatePlan {
+    hs::GateProgram prog;
+    int launch0[kParts + 1] = {0, 0, 0, 0, 0};   // part q makes launches [launch0[q], launch0[q + 1])
+    std::vector<hs::GateBlock> blocks;           // prog.blocks with their diagonals' addresses
+    std::vector<float> coef32;
+    void *dev = nullptr;
+    hs::GateTables tab;
 };
 
 }  // namespace
@@ -144,17 +141,16 @@ struct hs_factors_s {
     double *work_dev = nullptr;      // [8][G][4] partials, then [8][4] records
     double *norm_dev = nullptr;      // per-tile norm partials of the step's last launch, on demand
     size_t norm_bytes = 0;
-    void *scratch_dev = nullptr;     // output of open launches (HS_MAX_BATCH states), on demand
-    size_t scratch_bytes = 0;
     hipStream_t alloc_stream = nullptr;   // device memory is stream-ordered on this stream
-    std::map<PlanKey, EvolvePlan> plans;
+    std::map<PlanKey, std::unique_ptr<GatePlan>> plans;
+    std::unique_ptr<GatePlan> whole;      // whole evolutions of small states
     std::mutex mu;
-    // whole-evolution tables (small states), built on first use
-    bool whole_ready = false;
-    std::vector<hs::WholeEntry> whole_walk;
-    int32_t whole_part_off[5] = {0, 0, 0, 0, 0};
-    hs::WholeEntry *whole_walk_dev = nullptr;
-    bool any_perm = false;           // a factor is stored out of natural order (perm_pos)
+    // D = exp(-i h E) of every factor that carries it: N entries of the
+    // handle's dtype in natural order when the factor is nothing else (its
+    // own diagonal, or one of diag_own), else FP64 entries in the order the
+    // factor's coset product reads them
+    std::vector<const void *> diag_of;
+    std::vector<void *> diag_own;
 
     double *partials() { return work_dev; }
     double *records() { return work_dev + (size_t)HS_MAX_BATCH * hs::kReduceBlocks * 4; }
@@ -164,35 +160,35 @@ struct hs_factors_s {
     ~hs_factors_s() {
         for (auto &f : plan.factors)
             if (f.dev) (void)hipFreeAsync(f.dev, alloc_stream);
+        for (void *p : diag_own) (void)hipFreeAsync(p, alloc_stream);
         for (auto &kv : plans)
-            if (kv.second.dev_desc) (void)hipFreeAsync(kv.second.dev_desc, alloc_stream);
+            if (kv.second->dev) (void)hipFreeAsync(kv.second->dev, alloc_stream);
+        if (whole && whole->dev) (void)hipFreeAsync(whole->dev, alloc_stream);
         if (viol_dev) (void)hipFreeAsync(viol_dev, alloc_stream);
-        if (scratch_dev) (void)hipFreeAsync(scratch_dev, alloc_stream);
         if (norm_dev) (void)hipFreeAsync(norm_dev, alloc_stream);
         if (work_dev) (void)hipFreeAsync(work_dev, alloc_stream);
-        if (whole_walk_dev) (void)hipFreeAsync(whole_walk_dev, alloc_stream);
     }
 };
 
 namespace {
 
-// The launches of every step part (host only): greedy fusion extends a run
-// while the union of coupling hulls still fits one closed tile with rows runs
-// of at least w_min elements; each run gets its tile geometry and kernel form.
-void form_runs(const Plan &P, int dtype, const PlanKey &key, EvolvePlan &ep) {
+// The fusion list of every step part (host only): greedy fusion extends a run
+// while the union of coupling hulls still fits one closed tile of the batch's
+// rows with row runs of at least w_min elements.  hs_step_launches reports it
+// and choose_storage_order reads it; hs_evolve launches gate programs, which
+// need no more launches than this list has entries.
+void form_runs(const Plan &P, int dtype, const PlanKey &key, std::vector<Run> (&all)[kParts]) {
     const int n = P.n;
     const int batch = key.chunk;
     const bool fuse = key.fuse != 0;
     const int Tmax = tile_rows_max(dtype, batch, P.N);
     const int Wmin = w_min(dtype, key);
-    const size_t sc = elem_bytes(dtype);
-    ep = EvolvePlan();
-    ep.swizzle = key.swizzle;
     const int max_fuse = key.max_fuse;
     for (int part = 0; part < (P.joint < 0 ? 1 : kParts); ++part) {
         // runs are consecutive positions of the part's factor sequence
         const std::vector<int> seq = part_sequence(P, part);
-        std::vector<Run> &runs = ep.runs[part];
+        std::vector<Run> &runs = all[part];
+        runs.clear();
         const int F = (int)seq.size();
         int f = 0;
         while (f < F) {
@@ -224,45 +220,14 @@ void form_runs(const Plan &P, int dtype, const PlanKey &key, EvolvePlan &ep) {
                 if (G.xmask_union) empty = false;
                 ++g;
             }
-            run.launch_batch = batch;
             run.geo = geometry(empty ? 0 : lb, empty ? 0 : hb, n, Tmax);
-            if (!run.geo.ok) {            // orbit wider than the batched tile: one state per launch
-                run.launch_batch = 1;
-                run.geo = geometry(lb, hb, n, tile_rows_max(dtype, 1, P.N));
-            }
-            if (!run.geo.ok) {            // no closed tile at all (a single factor): open launch
-                const Factor &Fo = P.factors[run.factors[0]];
-                std::vector<long long> o(Fo.offs.begin(), Fo.offs.end());
-                run.launch_batch = batch;
-                run.geo = generic_geometry(o.data(), (int)o.size(), P.N, dtype, batch);
-                run.open = true;
-                ep.needs_scratch = true;
-            }
-            run.pairs = key.pairs && dtype == HS_C64 && !run.open && !run.elementwise;
-            bool permuted = false;
-            for (int k : run.factors) permuted = permuted || P.factors[k].perm_s > 0;
-            if (key.pairs == 1 && run.geo.qb > 0 && run.launch_batch == 1 && ((size_t)1 << run.geo.logW) * sc < 1024 &&
-                !permuted)
-                run.pairs = false;
-            const int64_t lowmask = (int64_t(1) << run.geo.qb) - 1;
-            // odd offsets pair in contiguous tiles (the pair kernel's odd-offset path)
-            const bool odd_ok = key.pairs >= 1 && run.geo.qb == 0 && run.geo.logW == 0 && !permuted;
-            for (int k : run.factors)
-                for (int64_t d : P.factors[k].offs) {
-                    if ((d & lowmask) != 0) run.pairs = false;
-                    if (run.geo.logW == 0 && (d & 1)) {
-                        if (odd_ok && P.N - (d < 0 ? -d : d) >= 2)
-                            run.pairs_odd = true;
-                        else
-                            run.pairs = false;
-                    }
-                }
-            if (!run.pairs) run.pairs_odd = false;
+            if (!run.geo.ok) run.geo = geometry(lb, hb, n, tile_rows_max(dtype, 1, P.N));
+            run.open = !run.geo.ok;
             runs.push_back(run);
             f = g;
         }
     }
-    for (int part = 1; P.joint < 0 && part < kParts; ++part) ep.runs[part] = ep.runs[0];
+    for (int part = 1; P.joint < 0 && part < kParts; ++part) all[part] = all[0];
 }
 
 // Storage order of every factor (perm_pos): a factor that the one-state plan
@@ -287,11 +252,11 @@ void choose_storage_order(Plan &P, int dtype) {
     const size_t sc = elem_bytes(dtype);
     const int chunk_bytes = env_int("HAMSIM_PERM_CHUNK_BYTES", 0, 0, 1 << 24);
     const int chunk_windows = env_int("HAMSIM_PERM_CHUNK_WINDOWS", 4, 1, 1 << 12);
-    EvolvePlan ep;
-    form_runs(P, dtype, plan_key(1, true), ep);
+    std::vector<Run> runs[kParts];
+    form_runs(P, dtype, plan_key(1, true), runs);
     std::vector<int> smin(P.factors.size(), -1), wlog(P.factors.size(), 0);
     for (int part = 0; part < kParts; ++part)
-        for (const Run &run : ep.runs[part]) {
+        for (const Run &run : runs[part]) {
             const bool strided = !run.open && !run.elementwise && run.geo.qb > 0;
             for (int k : run.factors) {
                 const int q = strided ? run.geo.qb : 0;
@@ -317,151 +282,78 @@ void choose_storage_order(Plan &P, int dtype) {
     }
 }
 
-// The runs of one plan key with their descriptors on the device.
-hs_status make_evolve_plan(hs_factors_s *h, const PlanKey &key, EvolvePlan &ep, void *stream) {
-    const Plan &P = h->plan;
-    const size_t sc = elem_bytes(h->dtype);
-    form_runs(P, h->dtype, key, ep);
-    for (int part = 0; part < kParts; ++part) {
-        if (part > 0 && P.joint < 0) {
-            ep.runs[part] = ep.runs[0];
-            continue;
-        }
-        for (Run &run : ep.runs[part]) {
-            run.desc_start = (int)ep.host_desc.size();
-            run.dstart.assign(1, 0);
-            run.perm = false;
-            for (int k : run.factors) {
-                const Factor &Fk = P.factors[k];
-                for (size_t j = 0; j < Fk.offs.size(); ++j) {
-                    const int64_t d = Fk.offs[j];
-                    DiagDesc dd{};
-                    dd.ptr = static_cast<const char *>(Fk.dev) + Fk.elem_off[j] * sc;
-                    dd.off = (int32_t)d;
-                    const int64_t lowmask = (int64_t(1) << run.geo.qb) - 1;
-                    dd.regular = (d & lowmask) == 0;
-                    dd.m = dd.regular ? (int32_t)(d >> run.geo.qb) : 0;
-                    dd.lo = (int32_t)std::max<int64_t>(0, -d);
-                    dd.hi = (int32_t)std::min<int64_t>(P.N, P.N - d);
-                    dd.ps = Fk.perm_s;
-                    dd.pc = Fk.perm_c;
-                    dd.plr = (int32_t)(((P.N - (d < 0 ? -d : d)) >> Fk.perm_s) << Fk.perm_c);
-                    if (Fk.perm_s > 0) run.perm = true;
-                    ep.host_desc.push_back(dd);
-                }
-                run.dstart.push_back((int)(ep.host_desc.size() - run.desc_start));
-            }
-            // out-of-order storage is read by closed tile launches only
-            if (run.perm && (run.open || run.elementwise))
-                return fail(HS_EDEVICE, "a factor stored out of natural order in an open or elementwise launch");
-        }
+// log2 rows of an evolution's tiles: 64 KiB of LDS, so that two workgroups
+// share a CU, halved (down to 1024 rows) while the launch would have fewer
+// than 256 of them, one per compute unit.
+int gate_tile_bits(int dtype, int64_t N, int batch) {
+    int kt = dtype == HS_C128 ? 12 : 13;
+    while (kt > 10 && ((N * batch) >> kt) < 256) --kt;
+    return kt;
+}
+
+// Uploads a program's tables; the host copies live as long as the plan, so
+// the ordered copies are safe.
+hs_status upload_gates(hs_factors_s *h, GatePlan &gp, hipStream_t st) {
+    const hs::GateProgram &p = gp.prog;
+    gp.blocks = p.blocks;
+    for (size_t k = 0; k < gp.blocks.size(); ++k)
+        gp.blocks[k].diag = p.dfactor[k] >= 0 ? h->diag_of[p.dfactor[k]] : nullptr;
+    const bool c128 = h->dtype == HS_C128;
+    if (!c128) gp.coef32.assign(p.coef.begin(), p.coef.end());
+    constexpr int kTabs = 4;
+    const struct {
+        const void *src;
+        size_t bytes;
+    } part[kTabs] = {{gp.blocks.data(), gp.blocks.size() * sizeof(hs::GateBlock)},
+                     {p.words.data(), p.words.size() * sizeof(uint32_t)},
+                     {c128 ? (const void *)p.coef.data() : (const void *)gp.coef32.data(),
+                      p.coef.size() * (c128 ? 8 : 4)},
+                     {p.coef64.data(), p.coef64.size() * 8}};
+    size_t off[kTabs], total = 0;
+    for (int k = 0; k < kTabs; ++k) {
+        off[k] = total;
+        total += (part[k].bytes + 255) / 256 * 256;
     }
-    const size_t bytes = ep.host_desc.size() * sizeof(DiagDesc);
-    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    HS_HIP(hipMallocAsync(reinterpret_cast<void **>(&ep.dev_desc), std::max<size_t>(bytes, 64), st),
-           "hipMallocAsync(descriptors)");
-    // the host table lives as long as the plan, so an ordered async copy is safe
-    hipError_t e = hipMemcpyAsync(ep.dev_desc, ep.host_desc.data(), bytes, hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) {
-        (void)hipFreeAsync(ep.dev_desc, st);
-        ep.dev_desc = nullptr;
-        return hip_fail(e, "hipMemcpy(descriptors)");
-    }
+    HS_HIP(hipMallocAsync(&gp.dev, std::max<size_t>(total, 256), st), "hipMallocAsync(coset tables)");
+    char *base = static_cast<char *>(gp.dev);
+    for (int k = 0; k < kTabs; ++k)
+        if (part[k].bytes)
+            HS_HIP(hipMemcpyAsync(base + off[k], part[k].src, part[k].bytes, hipMemcpyHostToDevice, st),
+                   "coset tables");
+    gp.tab.blocks = reinterpret_cast<const hs::GateBlock *>(base + off[0]);
+    gp.tab.words = reinterpret_cast<const uint32_t *>(base + off[1]);
+    gp.tab.coef = base + off[2];
+    gp.tab.coef64 = reinterpret_cast<const double *>(base + off[3]);
     return HS_OK;
 }
 
-// Whether the step's last launch can also produce the FP64 norm partials
-// (a closed tile launch whose LDS holds the per-wave sums).
-bool run_makes_norm(const Run &run) { return !run.elementwise && !run.open && run.geo.T >= 64; }
-
-hs_status launch_run(hs_factors_s *h, const EvolvePlan &ep, const Run &run, void *psi, int chunk,
-                     const double *nrm2_records, void *stream, double *norm_partials = nullptr) {
+// The coset programs of every step part for one plan key, or (loop) of a
+// whole small state.
+hs_status make_gate_plan(hs_factors_s *h, const PlanKey &key, bool loop, std::unique_ptr<GatePlan> &out, void *stream) {
     const Plan &P = h->plan;
-    const bool c128 = h->dtype == HS_C128;
-    const size_t sc = elem_bytes(h->dtype);
-    if (run.elementwise) {
-        const Factor &Fk = P.factors[run.factors[0]];
-        int e = hs::launch_diag_steps(psi, psi, Fk.dev, P.N, chunk, 1, nrm2_records, c128,
-                                      stream_out(chunk, P.N, h->dtype), stream);
-        if (e) return hip_fail((hipError_t)e, "diag kernel launch");
-        return HS_OK;
+    std::unique_ptr<GatePlan> gp(new GatePlan());
+    const int wlog = ilog2(std::max<int64_t>(2, w_min(h->dtype, key)));
+    const int max_factors = !key.fuse ? 1 : key.max_fuse < hs::kMaxRun ? key.max_fuse : 0;
+    const int kt = gate_tile_bits(h->dtype, P.N, key.chunk);
+    for (int q = 0; q < kParts; ++q) {
+        gp->launch0[q] = (int)gp->prog.launches.size();
+        hs::gate_launches(P, hs::gate_steps(P, part_sequence(P, q)), kt, wlog, max_factors, loop, gp->prog);
     }
-    const int lbatch = run.launch_batch;
-    for (int b0 = 0; b0 < chunk; b0 += lbatch) {
-        TileArgs a{};
-        char *p = static_cast<char *>(psi) + (size_t)b0 * P.N * sc;
-        a.y = run.open ? h->scratch_dev : p;
-        a.x = p;
-        a.stride = P.N;
-        a.N = (int32_t)P.N;
-        a.nf = (int32_t)run.factors.size();
-        for (int k = 0; k <= a.nf; ++k) a.dstart[k] = run.dstart[k];
-        a.desc = ep.dev_desc + run.desc_start;
-        a.qb = run.geo.qb;
-        a.kb = run.geo.kb;
-        a.logW = run.geo.logW;
-        a.nlw_log = run.geo.nlw_log;
-        a.T = run.geo.T;
-        a.nrm2 = nrm2_records ? nrm2_records + 4 * b0 : nullptr;
-        a.viol = run.open ? nullptr : h->viol_dev;
-        a.swizzle = swizzled(ep.swizzle, run.geo) ? 1 : 0;
-        a.stream_out = stream_out(chunk, P.N, h->dtype);
-        a.pairs = run.pairs ? (run.pairs_odd ? 2 : 1) : 0;
-        a.perm = run.perm ? 1 : 0;
-        // partials of state b0 + b at [((b0 + b) * tiles + tile) * 4]
-        a.norm_out = norm_partials ? norm_partials + (size_t)b0 * (P.N / run.geo.T) * 4 : nullptr;
-        const int nb = std::min(lbatch, chunk - b0);
-        int e = hs::launch_tile(a, nb, c128, !run.open, stream);
-        if (e) return hip_fail((hipError_t)e, "tile kernel launch");
-        if (run.open)
-            HS_HIP(hipMemcpyAsync(p, h->scratch_dev, (size_t)nb * P.N * sc, hipMemcpyDeviceToDevice,
-                                  reinterpret_cast<hipStream_t>(stream)), "copy back");
+    gp->launch0[kParts] = (int)gp->prog.launches.size();
+    if (hs_status s = upload_gates(h, *gp, reinterpret_cast<hipStream_t>(stream))) {
+        if (gp->dev) (void)hipFreeAsync(gp->dev, reinterpret_cast<hipStream_t>(stream));
+        return s;
     }
+    out = std::move(gp);
     return HS_OK;
 }
 
 // Rows up to which hs_evolve runs a whole evolution in one launch
-// (HAMSIM_WHOLE_MAX_ROWS, capped by the kernel's limit; 0 never).  The
-// default is where one workgroup per state stops beating the launch per run
-// and step on MI355X: 2048 complex64 rows (n <= 11: 1.3-3x faster, n = 12
-// and 13 up to 2.7x slower) and 1024 complex128 rows.
+// (HAMSIM_WHOLE_MAX_ROWS, capped by the tile one workgroup holds; 0 never).
 int64_t whole_max_rows(int dtype) {
     const int lim = dtype == HS_C128 ? hs::kWholeRowsC128 : hs::kWholeRowsC64;
     const int dflt = dtype == HS_C128 ? 1024 : 2048;
     return env_int("HAMSIM_WHOLE_MAX_ROWS", dflt, 0, lim);
-}
-
-// The whole-evolution kernel's walk: for each step part, one entry per
-// diagonal it applies, in order (factor by factor, ascending offsets).
-hs_status make_whole_tables(hs_factors_s *h, void *stream) {
-    const Plan &P = h->plan;
-    const size_t sc = elem_bytes(h->dtype);
-    h->whole_walk.clear();
-    for (int q = 0; q < kParts; ++q) {
-        h->whole_part_off[q] = (int32_t)h->whole_walk.size();
-        for (int fi : part_sequence(P, q)) {
-            const Factor &F = P.factors[fi];
-            for (size_t j = 0; j < F.offs.size(); ++j) {
-                const int64_t d = F.offs[j];
-                hs::WholeEntry e{};
-                e.ptr = static_cast<const char *>(F.dev) + F.elem_off[j] * sc;
-                e.off = (int32_t)d;
-                e.lo = (int32_t)std::max<int64_t>(0, -d);
-                e.hi = (int32_t)std::min<int64_t>(P.N, P.N - d);
-                e.last = j + 1 == F.offs.size() ? 1u : 0u;
-                h->whole_walk.push_back(e);
-            }
-        }
-    }
-    h->whole_part_off[kParts] = (int32_t)h->whole_walk.size();
-    if (h->whole_walk.empty()) return fail(HS_EINVAL, "no diagonals to apply");
-    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const size_t nw = h->whole_walk.size() * sizeof(hs::WholeEntry);
-    HS_HIP(hipMallocAsync(reinterpret_cast<void **>(&h->whole_walk_dev), nw, st), "hipMallocAsync(whole walk)");
-    // the host vector lives as long as the handle, so an ordered async copy is safe
-    HS_HIP(hipMemcpyAsync(h->whole_walk_dev, h->whole_walk.data(), nw, hipMemcpyHostToDevice, st), "whole walk");
-    h->whole_ready = true;
-    return HS_OK;
 }
 
 hs_status check_handle(hs_factors f) {
@@ -503,7 +395,6 @@ static hs_status build_device(hs_factors_s *h, void *stream) {
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     h->alloc_stream = st;
     choose_storage_order(P, h->dtype);
-    for (auto &f : P.factors) h->any_perm = h->any_perm || f.perm_s > 0;
     for (auto &f : P.factors) {
         hs::layout_factor(f, P.N, sc);
         HS_HIP(hipMallocAsync(&f.dev, f.elems_total * sc, st), "hipMallocAsync(factor diagonals)");
@@ -596,6 +487,34 @@ static hs_status build_device(hs_factors_s *h, void *stream) {
         a.perm_c = f.perm_c;
         int le = hs::launch_construct(a, (int)f.offs.size(), P.N, c128, stream);
         if (le) { cleanup(); return hip_fail((hipError_t)le, "construct kernel"); }
+        const void *dtab = nullptr;
+        if (f.has_diag && f.terms.empty() && f.perm_s == 0) {
+            dtab = f.dev;
+        } else if (f.has_diag) {
+            void *own = nullptr;
+            if ((e = hipMallocAsync(&own, (size_t)P.N * (f.terms.empty() ? sc : 16), st)) != hipSuccess) {
+                cleanup();
+                return hip_fail(e, "hipMallocAsync(diagonal)");
+            }
+            h->diag_own.push_back(own);
+            if (f.terms.empty()) {          // stored out of natural order: once more in order
+                static const int64_t zero_off[1] = {0};
+                void *d0 = nullptr;
+                if ((e = upload(zero_off, 8, &d0)) != hipSuccess) { cleanup(); return hip_fail(e, "diagonal table"); }
+                hs::ConstructArgs d = a;
+                d.base = own;
+                d.offs = static_cast<int64_t *>(d0);
+                d.elem_off = static_cast<uint64_t *>(d0);
+                d.perm_s = d.perm_c = 0;
+                le = hs::launch_construct(d, 1, P.N, c128, stream);
+            } else {
+                le = hs::launch_phase_order(a.phase, static_cast<double *>(own), P.N,
+                                            hs::gate_step(P, (int)h->diag_of.size(), 0).basis, stream);
+            }
+            if (le) { cleanup(); return hip_fail((hipError_t)le, "diagonal kernel"); }
+            dtab = own;
+        }
+        h->diag_of.push_back(dtab);
     }
     e = hipStreamSynchronize(reinterpret_cast<hipStream_t>(stream));
     cleanup();
@@ -647,49 +566,55 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
     int cur_dev = 0;
     HS_HIP(hipGetDevice(&cur_dev), "hipGetDevice");
     if (cur_dev != f->device) return fail(HS_EINVAL, "current device differs from the build device");
-    if (!(flags & (HS_RENORM | HS_NO_FUSE)) && P.N <= whole_max_rows(f->dtype) && !f->any_perm) {
+    const bool c128 = f->dtype == HS_C128;
+    const bool fuse = !(flags & HS_NO_FUSE);
+    const bool renorm = (flags & HS_RENORM) != 0;
+    if (P.joint < 0 && !renorm && P.seq.size() == 1 && P.factors[P.seq[0]].terms.empty()) {
+        // a step that is one diagonal factor: all steps in one pass (the
+        // same multiplications, one step after the other, per entry)
+        for (int c0 = 0; c0 < batch; c0 += HS_MAX_BATCH) {
+            const int chunk = std::min(HS_MAX_BATCH, batch - c0);
+            void *p = static_cast<char *>(psi) + (size_t)c0 * P.N * sc;
+            int e = hs::launch_diag_steps(p, p, f->diag_of[P.seq[0]], P.N, chunk, steps, nullptr, c128,
+                                          stream_out(chunk, P.N, f->dtype), stream);
+            if (e) return hip_fail((hipError_t)e, "diag kernel launch");
+        }
+        return HS_OK;
+    }
+    if (!renorm && fuse && P.N <= whole_max_rows(f->dtype)) {
         // a small state: the whole evolution of every state in one launch
-        if (!f->whole_ready)
-            if (hs_status s = make_whole_tables(f, stream)) return s;
-        hs::WholeArgs w{};
-        w.psi = psi;
-        w.stride = P.N;
-        w.N = (int32_t)P.N;
-        w.steps = steps;
-        w.walk = f->whole_walk_dev;
-        for (int q = 0; q <= kParts; ++q) w.part_off[q] = f->whole_part_off[q];
-        int e = hs::launch_whole(w, batch, f->dtype == HS_C128, stream);
+        if (!f->whole)
+            if (hs_status s = make_gate_plan(f, plan_key(1, true), true, f->whole, stream)) return s;
+        const GatePlan &gp = *f->whole;
+        hs::GateRun r;
+        r.psi = psi;
+        r.N = P.N;
+        r.batch = batch;
+        r.by_rows = gp.prog.by_rows;
+        r.steps = steps;
+        for (int q = 0; q < kParts; ++q) r.part[q] = gp.prog.launches[q].block0;
+        r.part[kParts] = gp.prog.launches[kParts - 1].block1;
+        int e = hs::launch_gates(gp.prog.launches[0], gp.tab, r, c128, false, stream);
         if (e) return hip_fail((hipError_t)e, "whole-evolution kernel launch");
         return HS_OK;
     }
-    const bool fuse = !(flags & HS_NO_FUSE);
-    const bool renorm = (flags & HS_RENORM) != 0;
     for (int c0 = 0; c0 < batch; c0 += HS_MAX_BATCH) {
         const int chunk = std::min(HS_MAX_BATCH, batch - c0);
         const PlanKey key = plan_key(chunk, fuse);
         auto it = f->plans.find(key);
         if (it == f->plans.end()) {
-            EvolvePlan ep;
-            if (hs_status s = make_evolve_plan(f, key, ep, stream)) return s;
-            it = f->plans.emplace(key, std::move(ep)).first;
+            std::unique_ptr<GatePlan> gp;
+            if (hs_status s = make_gate_plan(f, key, false, gp, stream)) return s;
+            it = f->plans.emplace(key, std::move(gp)).first;
         }
-        const EvolvePlan &ep = it->second;
-        if (ep.needs_scratch && f->scratch_bytes < (size_t)chunk * P.N * sc) {
-            // stream-ordered: the old buffer's last use precedes this point on `stream`
-            hipStream_t hst = reinterpret_cast<hipStream_t>(stream);
-            if (f->scratch_dev) HS_HIP(hipFreeAsync(f->scratch_dev, hst), "hipFreeAsync(scratch)");
-            f->scratch_dev = nullptr;
-            f->scratch_bytes = 0;
-            const size_t bytes = (size_t)chunk * P.N * sc;
-            HS_HIP(hipMallocAsync(&f->scratch_dev, bytes, hst), "hipMallocAsync(scratch)");
-            f->scratch_bytes = bytes;
-        }
+        const GatePlan &gp = *it->second;
         if (renorm) {
             // the step's last launch sums |y|^2 per tile: room for its partials
             size_t need = 0;
-            for (int q = 0; q < kParts; ++q)
-                if (!ep.runs[q].empty() && run_makes_norm(ep.runs[q].back()))
-                    need = std::max(need, (size_t)chunk * (P.N / ep.runs[q].back().geo.T) * 4 * sizeof(double));
+            for (int q = 0; q < kParts; ++q) {
+                const hs::GateLaunch &L = gp.prog.launches[gp.launch0[q + 1] - 1];
+                need = std::max(need, (size_t)chunk * (P.N / L.rows) * 4 * sizeof(double));
+            }
             if (need > f->norm_bytes) {
                 hipStream_t hst = reinterpret_cast<hipStream_t>(stream);
                 if (f->norm_dev) HS_HIP(hipFreeAsync(f->norm_dev, hst), "hipFreeAsync(norm partials)");
@@ -701,39 +626,35 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
             }
         }
         void *p = static_cast<char *>(psi) + (size_t)c0 * P.N * sc;
-        const std::vector<Run> &lone = ep.runs[kPartLone];
-        if (!renorm && P.joint < 0 && lone.size() == 1 && lone[0].elementwise) {
-            // a step that is one diagonal factor: all steps in one pass (the
-            // same multiplications, one step after the other, per entry)
-            const Factor &Fk = P.factors[lone[0].factors[0]];
-            int e = hs::launch_diag_steps(p, p, Fk.dev, P.N, chunk, steps, nullptr, f->dtype == HS_C128,
-                                          stream_out(chunk, P.N, f->dtype), stream);
-            if (e) return hip_fail((hipError_t)e, "diag kernel launch");
-            continue;
-        }
+        const bool streamed = stream_out(chunk, P.N, f->dtype) != 0;
         const double *rec = f->records() + 2;    // squared norm of state b at rec[4 b]
         for (int s = 0; s < steps; ++s) {
             const int part = steps == 1 ? kPartLone
                              : s == 0 ? kPartFirst : s == steps - 1 ? kPartLast : kPartMiddle;
-            const std::vector<Run> &runs = ep.runs[part];
-            const bool fused_norm = renorm && run_makes_norm(runs.back());
-            for (size_t ri = 0; ri < runs.size(); ++ri) {
-                const double *nrm = (renorm && s > 0 && ri == 0) ? rec : nullptr;
-                double *np = (fused_norm && ri + 1 == runs.size()) ? f->norm_dev : nullptr;
-                if (hs_status st = launch_run(f, ep, runs[ri], p, chunk, nrm, stream, np)) return st;
+            const int l0 = gp.launch0[part], l1 = gp.launch0[part + 1];
+            for (int l = l0; l < l1; ++l) {
+                const hs::GateLaunch &L = gp.prog.launches[l];
+                hs::GateRun r;
+                r.psi = p;
+                r.N = P.N;
+                r.batch = chunk;
+                r.by_rows = gp.prog.by_rows;
+                r.stage_diag = L.stage_diag >= 0 ? f->diag_of[L.stage_diag] : nullptr;
+                r.nrm2 = (renorm && s > 0 && l == l0) ? rec : nullptr;
+                r.norm_out = (renorm && l + 1 == l1) ? f->norm_dev : nullptr;
+                r.part[0] = L.block0;
+                r.part[1] = L.block1;
+                int e = hs::launch_gates(L, gp.tab, r, c128, streamed, stream);
+                if (e) return hip_fail((hipError_t)e, "coset kernel launch");
             }
-            if (fused_norm) {
-                const int tiles = (int)(P.N / runs.back().geo.T);
+            if (renorm) {
+                const int tiles = (int)(P.N / gp.prog.launches[l1 - 1].rows);
                 int e = hs::launch_reduce_partials(f->norm_dev, tiles, chunk, f->records(), stream);
-                if (e) return hip_fail((hipError_t)e, "norm reduction");
-            } else if (renorm) {
-                int e = hs::launch_reduce(p, f->dtype, p, f->dtype, chunk, P.N, f->partials(),
-                                          hs::kReduceBlocks, f->records(), false, stream);
                 if (e) return hip_fail((hipError_t)e, "norm reduction");
             }
         }
         if (renorm) {
-            int e = hs::launch_scale(p, P.N, chunk, rec, f->dtype == HS_C128, stream);
+            int e = hs::launch_scale(p, P.N, chunk, rec, c128, stream);
             if (e) return hip_fail((hipError_t)e, "scale kernel");
         }
     }
@@ -881,18 +802,10 @@ hs_status hs_step_launches(hs_factors f, int batch, unsigned flags, int part, in
     if (batch < 1 || !n_launches) return fail(HS_EINVAL, "batch >= 1 and an output are required");
     if (part < 0 || part >= kParts) return fail(HS_EINVAL, "part must be 0..3");
     if (flags & ~(unsigned)(HS_RENORM | HS_NO_FUSE)) return fail(HS_EINVAL, "unknown evolve flag");
-    std::lock_guard<std::mutex> lock(f->mu);
     const int chunk = std::min(HS_MAX_BATCH, batch);
-    const bool fuse = !(flags & HS_NO_FUSE);
-    const PlanKey key = plan_key(chunk, fuse);
-    auto it = f->plans.find(key);
-    if (it == f->plans.end()) {
-        EvolvePlan ep;
-        if (hs_status s = make_evolve_plan(f, key, ep, f->alloc_stream)) return s;
-        it = f->plans.emplace(key, std::move(ep)).first;
-        HS_HIP(hipStreamSynchronize(f->alloc_stream), "hipStreamSynchronize");
-    }
-    const auto &runs = it->second.runs[part];
+    std::vector<Run> all[kParts];
+    form_runs(f->plan, f->dtype, plan_key(chunk, !(flags & HS_NO_FUSE)), all);
+    const auto &runs = all[part];
     *n_launches = (int)runs.size();
     if (first_factor && n_factors) {
         if (cap < (int)runs.size()) return fail(HS_EINVAL, "output too small");
@@ -915,6 +828,9 @@ static size_t footprint_bytes(const Plan &P, int dtype, int batch) {
         }
     }
     total += (size_t)batch * P.N * sc;                                // the states
+    for (const auto &F : P.factors)
+        if (F.has_diag) total += (size_t)P.N * 2 * sc;                // D in FP64 beside the factor's diagonals
+                                                                      // (complex128: and the table it comes from)
     bool open = false;                                                // a factor no closed tile holds
     for (const auto &F : P.factors)
         if (F.xmask_union && !geometry(F.xlb, F.xhb, P.n, tile_rows_max(dtype, 1, P.N)).ok) open = true;
@@ -997,7 +913,7 @@ hs_status hs_dia_spmv(int n_diags, const long long *offsets, const void *const *
         hipError_t e = hipMemcpyAsync(ddev, hd.data(), sizeof(DiagDesc) * n_diags, hipMemcpyHostToDevice, st);
         TileArgs a = open_args(geo, ddev, n_diags, xb + (size_t)c0 * N * sc, yb + (size_t)c0 * N * sc, N);
         a.stream_out = stream_out(chunk, N, dtype);
-        if (e == hipSuccess) e = (hipError_t)hs::launch_tile(a, chunk, dtype == HS_C128, false, stream);
+        if (e == hipSuccess) e = (hipError_t)hs::launch_tile(a, chunk, dtype == HS_C128, stream);
         hipError_t e2 = hipStreamSynchronize(st);
         (void)hipFreeAsync(ddev, st);
         if (e != hipSuccess) return hip_fail(e, "dia_spmv launch");

@@ -716,7 +716,7 @@ hs_status hs_dia_evolve(hs_dia U, void *psi, int batch, int steps, void *stream)
         for (int s = 0; s < steps; ++s) {
             TileArgs a = open_args(geo, dd, nd, cur, other, N);
             a.stream_out = stream_out(chunk, N, U->dtype);
-            int le = hs::launch_tile(a, chunk, U->dtype == HS_C128, false, st);
+            int le = hs::launch_tile(a, chunk, U->dtype == HS_C128, st);
             if (le) return dhip((hipError_t)le, "tile kernel launch");
             std::swap(cur, other);
         }

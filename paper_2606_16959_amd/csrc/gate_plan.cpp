@@ -1,0 +1,246 @@
+// Host planning of the coset programs (gate_plan.h): plain C++, no device.
+
+#include "gate_plan.h"
+
+#include <algorithm>
+#include <cmath>
+
+namespace hs {
+namespace {
+
+int popc64(uint64_t v) { return __builtin_popcountll(v); }
+uint64_t top_bit(uint64_t v) { return 1ull << (63 - __builtin_clzll(v)); }
+
+// bits of v at the positions of `mask`, packed
+uint64_t pack_bits(uint64_t v, uint64_t mask) {
+    uint64_t o = 0;
+    int j = 0;
+    for (uint64_t m = mask; m; m &= m - 1, ++j) o |= ((v >> __builtin_ctzll(m)) & 1ull) << j;
+    return o;
+}
+// the packed bits of v spread to the positions of `mask`
+uint64_t spread_bits(uint64_t v, uint64_t mask) {
+    uint64_t o = 0;
+    for (uint64_t m = mask; m; m &= m - 1, v >>= 1)
+        if (v & 1) o |= m & -m;
+    return o;
+}
+
+// Fully reduced masks of the span of `masks`, by ascending highest bit.
+std::vector<uint64_t> reduced_span(const std::vector<uint64_t> &masks) {
+    std::vector<uint64_t> red;
+    for (uint64_t v : masks) {
+        for (uint64_t r : red)
+            if (v & top_bit(r)) v ^= r;
+        if (!v) continue;
+        for (uint64_t &r : red)
+            if (r & top_bit(v)) r ^= v;
+        red.push_back(v);
+    }
+    std::sort(red.begin(), red.end());
+    return red;
+}
+
+uint64_t combine(const std::vector<uint64_t> &basis, uint64_t j) {
+    uint64_t v = 0;
+    for (size_t c = 0; c < basis.size(); ++c)
+        if ((j >> c) & 1) v ^= basis[c];
+    return v;
+}
+
+}  // namespace
+
+std::vector<GateSeg> gate_segments(uint64_t mask) {
+    std::vector<GateSeg> out;
+    int sh = 0;
+    for (int q = 0; q < 64;) {
+        if (!((mask >> q) & 1)) {
+            ++q;
+            continue;
+        }
+        int e = q;
+        while (e < 64 && ((mask >> e) & 1)) ++e;
+        const int len = e - q;
+        out.push_back({sh, (uint32_t)((1ull << len) - 1), q});
+        sh += len;
+        q = e;
+    }
+    return out;
+}
+
+GateStep gate_step(const Plan &P, int factor, int pos) {
+    const Factor &F = P.factors[factor];
+    GateStep g;
+    g.factor = factor;
+    g.pos = pos;
+    g.carries_d = F.has_diag;
+    g.diag_only = F.terms.empty();
+    if (g.diag_only) return g;
+    std::vector<uint64_t> masks;
+    for (int k : F.terms) masks.push_back(P.terms[k].x);
+    g.basis = reduced_span(masks);
+    for (uint64_t m : masks) g.flips |= m;
+    const int rho = (int)g.basis.size(), R = 1 << rho, K = 1 << F.bits.size();
+    uint64_t support = 0;
+    for (int q : F.bits) support |= 1ull << q;
+    const uint64_t free_bits = support & ~g.pivots();
+    for (int q : F.bits)
+        if ((free_bits >> q) & 1) g.type_bits.push_back(q);
+    // the products, one per setting of the free support bits
+    const int types = 1 << g.type_bits.size();
+    std::vector<std::complex<double>> M((size_t)types * R * R);
+    for (int t = 0; t < types; ++t) {
+        const uint64_t a0 = spread_bits((uint64_t)t, free_bits);
+        for (int i = 0; i < R; ++i)
+            for (int j = 0; j < R; ++j)
+                M[((size_t)t * R + i) * R + j] =
+                    F.L[pack_bits(a0 ^ combine(g.basis, i), support) * K + pack_bits(a0 ^ combine(g.basis, j), support)];
+    }
+    // one parity of the flip that decides between real and imaginary entries
+    // (unit flips first; every entry must agree)
+    auto kinds = [&](int m) {        // 1 real, 2 imaginary entries among the flips by m
+        int k = 0;
+        for (int t = 0; t < types; ++t)
+            for (int i = 0; i < R; ++i) {
+                const std::complex<double> v = M[((size_t)t * R + i) * R + (i ^ m)];
+                if (v.real() != 0.0) k |= 1;
+                if (v.imag() != 0.0) k |= 2;
+            }
+        return k;
+    };
+    std::vector<int> kd(R);
+    for (int m = 0; m < R; ++m) kd[m] = kinds(m);
+    bool typed = false;
+    for (int km = R - 1; km >= 0 && !typed; --km) {      // R <= 1024; R - 1 (every flip imaginary) fits most
+        bool ok = true;
+        for (int m = 0; m < R && ok; ++m) ok = (kd[m] & ~((popc64(m & km) & 1) ? 2 : 1)) == 0;
+        if (ok) {
+            typed = true;
+            g.kmask = km;
+        }
+    }
+    g.form = typed ? (g.carries_d ? kGateRealD : kGateReal) : (g.carries_d ? kGateComplexD : kGateComplex);
+    for (int t = 0; t < types; ++t)
+        for (int p = 0; p < R * R; ++p) {
+                const int i = g.carries_d ? p % R : p / R, j = g.carries_d ? p / R : p % R;
+                const std::complex<double> v = M[((size_t)t * R + i) * R + j];
+                if (!typed) {
+                    g.entries.push_back(v.real());
+                    g.entries.push_back(v.imag());
+                    continue;
+                }
+                const int ki = popc64(i & g.kmask) & 1, kj = popc64(j & g.kmask) & 1;
+                if (ki == kj) g.entries.push_back(v.real());
+                else g.entries.push_back(!g.carries_d && ki ? -v.imag() : v.imag());
+            }
+    return g;
+}
+
+std::vector<GateStep> gate_steps(const Plan &P, const std::vector<int> &seq) {
+    std::vector<GateStep> out;
+    for (size_t pos = 0; pos < seq.size(); ++pos) out.push_back(gate_step(P, seq[pos], (int)pos));
+    return out;
+}
+
+void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, int wlog, int max_factors, bool loop,
+                   GateProgram &out) {
+    const uint64_t all = (1ull << P.n) - 1;
+    kt = loop ? P.n : std::min(kt, P.n);
+    wlog = std::min(wlog, kt);
+    size_t i = 0;
+    while (i < steps.size()) {
+        // the run of steps one tile holds
+        uint64_t need = 0;
+        size_t j = i;
+        int w = wlog;
+        while (j < steps.size()) {
+            const uint64_t nx = need | steps[j].flips;
+            if (max_factors > 0 && (int)(j - i) >= max_factors) break;
+            if (popc64(nx | ((1ull << w) - 1)) > kt) {
+                if (j > i) break;
+                // a single wide factor: shorten the runs, down to row pairs
+                while (w > 1 && popc64(nx | ((1ull << w) - 1)) > kt) --w;
+            }
+            need = nx;
+            ++j;
+        }
+        GateLaunch L;
+        uint64_t tile = (need | ((1ull << w) - 1)) & all;
+        for (int q = 0; q < P.n && popc64(tile) < kt; ++q) tile |= 1ull << q;
+        L.tile = tile;
+        L.kt = popc64(tile);
+        L.rows = int64_t(1) << L.kt;
+        L.in = gate_segments(tile);
+        L.out = gate_segments(all & ~tile);
+        L.block0 = (int)out.blocks.size();
+        for (size_t q = i; q < j; ++q) {
+            const GateStep &g = steps[q];
+            if (g.diag_only && q == i && !loop) {
+                L.stage_diag = g.factor;
+                continue;
+            }
+            GateBlock b{};
+            out.dfactor.push_back(g.carries_d ? g.factor : -1);
+            if (g.diag_only) {
+                b.kind = kGateDiag;
+                out.blocks.push_back(b);
+                continue;
+            }
+            std::vector<uint64_t> loc;
+            uint64_t piv = 0, types = 0;
+            for (uint64_t v : g.basis) {
+                loc.push_back(pack_bits(v, tile));
+                piv |= top_bit(loc.back());
+            }
+            b.rho = (int)loc.size();
+            b.form = g.form;
+            b.kmask = g.kmask;
+            b.nz = (int)g.type_bits.size();
+            b.ztab = (int)out.words.size();
+            for (int zb : g.type_bits) {
+                const uint64_t z = 1ull << zb, zl = pack_bits(z & tile, tile);
+                types |= zl;
+                out.words.push_back((uint32_t)zl);
+                out.words.push_back((uint32_t)(z & ~tile));
+            }
+            std::vector<double> &dst = g.carries_d ? out.coef64 : out.coef;
+            const bool pairs = g.form == kGateComplex || g.form == kGateComplexD;
+            while (dst.size() % 4) dst.push_back(0.0);
+            b.coef = (int)(dst.size() / (pairs ? 2 : 1));
+            dst.insert(dst.end(), g.entries.begin(), g.entries.end());
+            if (b.rho > kGateMaxCoset || pairs) {
+                b.kind = kGateRows;
+                out.by_rows = true;
+                b.wtab = (int)out.words.size();
+                for (uint64_t v : loc) out.words.push_back((uint32_t)(63 - __builtin_clzll(v)));
+                for (uint64_t v : loc) out.words.push_back((uint32_t)v);
+                for (uint64_t v : g.basis) out.words.push_back((uint32_t)(63 - __builtin_clzll(v)));
+                out.blocks.push_back(b);
+                continue;
+            }
+            const int nt = popc64(types);
+            uint64_t holes = piv;
+            b.tshift = L.kt - b.rho;
+            b.lane = nt != 0;             // (type bits outside the tile are uniform)
+            if (nt && nt <= kGateMaxType && L.kt - b.rho - nt >= 6) {
+                b.lane = 0;
+                holes |= types;
+                b.ntype = nt;
+                b.tshift -= nt;
+                int k = 0;
+                for (uint64_t p = types; p; p &= p - 1) b.tpos |= (uint32_t)__builtin_ctzll(p) << (8 * k++);
+            }
+            for (uint64_t p = holes; p; p &= p - 1) b.holes |= (uint64_t)__builtin_ctzll(p) << (8 * b.nhole++);
+            for (int c = 0; c < b.rho; ++c) {
+                b.basis[c] = (uint32_t)loc[c];
+                b.rpiv[c] = 63 - __builtin_clzll(g.basis[c]);
+            }
+            out.blocks.push_back(b);
+        }
+        L.block1 = (int)out.blocks.size();
+        out.launches.push_back(L);
+        i = j;
+    }
+}
+
+}  // namespace hs

@@ -1,0 +1,163 @@
+// The factors as programs of small dense products (host planning and the
+// records the kernels read).
+//
+// A factor's exponential couples a row only with the rows its group's X-masks
+// reach: the masks span 2^rho flips, and the factor is one 2^rho x 2^rho
+// product on every coset r ^ span, with entries of the factor's local unitary
+// (L[loc(r), loc(r')], times D[r'] for the factor that carries the diagonal
+// terms).  The stored diagonals (Eq. 6) hold the same entries once per row and
+// diagonal, about half of them structural zeros.  A launch that applies the
+// products needs no coefficient stream: it moves the state, and D where the
+// factor carries it.  Entries are rounded to the state's dtype exactly as the
+// stored ones are, and every row sums its products in the order of ascending
+// offsets, so the results are those of the stored diagonals bit for bit.
+#pragma once
+
+#include <cstdint>
+#include <vector>
+
+#include "hs_internal.h"
+
+namespace hs {
+
+constexpr int kGateMaxCoset = 3;     // rank of the largest coset a thread holds in registers
+constexpr int kGateMaxType = 4;      // type bits that a block's coset numbering keeps apart
+constexpr int kGateSegs = 16;        // bit segments of a tile or of its complement
+
+// LDS position of tile-local row i: XOR of the low bits with higher ones, so
+// that the rows a wave reads for one coset element fall on distinct banks
+// whichever bits the coset spans.  It is linear over XOR: the position of
+// row i ^ m is that of i XOR that of m.
+constexpr int gate_lds_pos(int i, bool c128) {
+    const int lb = c128 ? 4 : 5;       // rows of one 256-byte bank line
+    return i ^ (((i >> lb) & ((1 << (lb - 1)) - 1)) << 1) ^ ((i >> (2 * lb - 2)) & 1);
+}
+
+// How a factor's entries are kept (R: the state's real type).
+//   kGateReal     entries real or imaginary by one parity of the flip; stored
+//                 as R values of the product between rows turned by i^kappa
+//                 (kappa_j = parity(j & kmask)): M'[i][j] = i^(kappa_i -
+//                 kappa_j) M[i][j], all real, so an entry is two FMAs
+//   kGateComplex  general entries, (re, im) pairs of R
+//   kGateRealD    the factor carries D: FP64 moduli v, M = v or i v by
+//                 parity((i ^ j) & kmask); the coefficient is the rounded v D[j]
+//   kGateComplexD general FP64 entries with D
+enum GateForm { kGateReal = 0, kGateComplex = 1, kGateRealD = 2, kGateComplexD = 3 };
+
+// kGateCosets: a thread holds whole cosets (rank up to kGateMaxCoset, forms
+// Real and RealD).  kGateRows: every thread sums its rows one by one, for
+// larger cosets and general entries.  kGateDiag: the product with a diagonal.
+enum GateKind { kGateCosets = 0, kGateDiag = 1, kGateRows = 2 };
+
+// One factor on the tile.
+//
+// A coset's number is spread over the tile-local index bits that are no
+// holes (the pivots, 0 in a coset's first row, and the type bits).  The top
+// ntype bits of the number are the type bits' values: with at least 64 cosets
+// per type they are the same for all lanes of a wave, whose matrix then comes
+// through scalar loads.  With fewer cosets ntype is 0, type bits are no
+// holes, and each lane loads its own matrix.
+struct GateBlock {
+    const void *diag;              // kGateDiag: N entries; forms with D: FP64 [2^rho][N >> rho],
+                                   // element j of coset c (launch_phase_order)
+    uint64_t holes;                // ascending local positions, one byte each
+    int32_t kind, rho, form, kmask;
+    int32_t nz, ztab;              // type bits: nz pairs (local bit, row bit outside the tile) in `words`
+    int32_t coef;                  // first entry: table[type][i][j], or [type][j][i] with D
+    int32_t wtab;                  // kGateRows: in `words`, rho local pivots, masks, row pivots
+    int32_t nhole, ntype;
+    int32_t lane, pad;             // lane: each lane loads its own matrix
+    int32_t tshift;                // log2(cosets) - ntype
+    uint32_t tpos;                 // local position of type bit t: byte t
+    uint32_t basis[kGateMaxCoset]; // reduced masks of the coset, in tile-local index space
+    int32_t rpiv[kGateMaxCoset];   // row bits of the pivots, ascending
+};
+
+// dst bits of a segment: ((i >> sh) & mask) << dst
+struct GateSeg {
+    int32_t sh;
+    uint32_t mask;
+    int32_t dst;
+};
+
+// ------------------------------------------------------------ host planning
+
+// One factor of a step as a coset product (or a diagonal alone).
+struct GateStep {
+    int factor = 0;                // stored factor
+    int pos = 0;                   // its position in the part's sequence
+    bool diag_only = false;        // D and nothing else
+    bool carries_d = false;
+    uint64_t flips = 0;            // union of the masks
+    std::vector<uint64_t> basis;   // reduced masks by ascending highest bit (the pivots): ascending
+                                   // coset coordinates are ascending rows
+    std::vector<int> type_bits;    // support bits that are no pivots: they select the product
+    int form = kGateReal;
+    int kmask = 0;
+    std::vector<double> entries;   // [type][i][j] ([type][j][i] with D) as `form` keeps them, in FP64
+    uint64_t pivots() const {
+        uint64_t p = 0;
+        for (uint64_t v : basis) p |= 1ull << (63 - __builtin_clzll(v));
+        return p;
+    }
+};
+
+struct GateLaunch {
+    uint64_t tile = 0;             // row bits of the tile
+    int kt = 0;                    // log2 of its rows
+    int64_t rows = 0;
+    int block0 = 0, block1 = 0;
+    int stage_diag = -1;           // factor whose diagonal multiplies the tile as it is loaded
+    std::vector<GateSeg> in, out;  // tile-local bits -> row bits; tile number -> row bits
+};
+
+struct GateProgram {
+    bool by_rows = false;               // some block is of kind kGateRows
+    std::vector<GateLaunch> launches;
+    std::vector<GateBlock> blocks;      // diag filled at upload from dfactor
+    std::vector<int> dfactor;           // factor whose D the block reads, or -1
+    std::vector<uint32_t> words;
+    std::vector<double> coef;           // forms Real and Complex (rounded to the dtype at upload)
+    std::vector<double> coef64;         // forms RealD and ComplexD
+};
+
+GateStep gate_step(const Plan &P, int factor, int pos);
+std::vector<GateStep> gate_steps(const Plan &P, const std::vector<int> &seq);
+
+// Launches for `steps`: consecutive steps share a launch while a tile of
+// 2^kt rows that holds the low wlog bits (rows in one run) holds every bit
+// they flip; at most max_factors factors per launch (0: any number).
+// `loop`: one launch of the whole state whose blocks are applied again and
+// again (no diagonal folded into the load).  Appends to `out`.
+void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, int wlog, int max_factors, bool loop,
+                   GateProgram &out);
+
+// Device tables of a program and one launch's run-time arguments (gates.hip).
+struct GateTables {
+    const GateBlock *blocks = nullptr;
+    const uint32_t *words = nullptr;
+    const void *coef = nullptr;
+    const double *coef64 = nullptr;
+};
+struct GateRun {
+    void *psi = nullptr;
+    int64_t N = 0;
+    int batch = 1;
+    bool by_rows = false;          // the program has kGateRows blocks
+    const void *stage_diag = nullptr;
+    const double *nrm2 = nullptr;
+    double *norm_out = nullptr;    // partials of state b, tile t at [(b * tiles + t) * 4]
+    int steps = 1;
+    int32_t part[5] = {0, 0, 0, 0, 0};
+};
+int launch_gates(const GateLaunch &L, const GateTables &t, const GateRun &r, bool c128, bool stream_out, void *stream);
+
+// FP64 phase table in the order GateBlock::diag holds it: entry j * (N >> rho) + c
+// belongs to element j of the coset (reduced masks `basis`) whose first row,
+// its pivot bits taken out, is c.
+int launch_phase_order(const double *phase, double *out, int64_t N, const std::vector<uint64_t> &basis, void *stream);
+
+// Segments that deposit consecutive index bits into the set bits of `mask`.
+std::vector<GateSeg> gate_segments(uint64_t mask);
+
+}  // namespace hs

@@ -1,0 +1,575 @@
+// The coset kernel: a launch's tile program (gate_plan.h) applied to the
+// state, one tile of one state per workgroup.
+//
+// A tile is every setting of the row bits in the launch's tile mask; all of a
+// launch's factors couple rows inside one tile.  The workgroup loads the tile
+// once (16 bytes per lane, runs of at least 256 bytes), keeps it in LDS and
+// applies block after block: a thread holds a coset of 2^LC rows in registers
+// and multiplies it by the factor's small dense matrix, so a factor costs one
+// LDS read and one write of the tile and one barrier.  The matrix entries are
+// read through scalar loads, or from cache where they depend on further row
+// bits.
+//
+// What bounds it: HBM for large states (state read and written once per
+// launch, and 16 bytes of D per row where a factor carries it).  A factor
+// that flips three bits costs 16 FMAs per row, the one that carries D about
+// 80 operations, which take less time than the bytes.  Two 64 KiB tiles fit a
+// CU's LDS, so one tile's loads and stores overlap the other's arithmetic.
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+#include <mutex>
+
+#include "dev_common.h"
+#include "gate_plan.h"
+
+namespace hs {
+
+struct GateArgs {
+    void *psi;
+    int64_t N;                     // rows of a state, and elements between states
+    int32_t batch;
+    int32_t kt;                    // log2 of the tile's rows
+    int32_t tiles, total;          // tiles of a state, and of all states
+    int32_t nin, nout;
+    GateSeg in[kGateSegs], out[kGateSegs];
+    const GateBlock *blocks;
+    const uint32_t *words;
+    const void *coef;
+    const double *coef64;
+    const void *stage_diag;        // or null: multiplies the tile as it is loaded
+    const double *nrm2;            // per-state squared norms to divide out, or null
+    double *norm_out;              // or null: partials of state b, tile t at [(b * tiles + t) * 4]
+    int32_t by_rows;               // a block is of kind kGateRows (twice the LDS)
+    int32_t steps;                 // > 1 only when the tile is the whole state
+    int32_t part[5];               // step part q applies blocks [part[q], part[q + 1])
+};
+
+template <typename R>
+__device__ __forceinline__ constexpr int lds_pos(int i) {
+    return gate_lds_pos(i, sizeof(R) == 8);
+}
+
+// A value of a program table at a uniform address: constant memory as far as
+// the kernel goes, so the load is a scalar one.
+template <typename V>
+__device__ __forceinline__ V uload(const V &p) {
+    return *(const __attribute__((address_space(4))) V *)&p;
+}
+__device__ __forceinline__ uint32_t seg_deposit(const GateSeg *s, int n, uint32_t i) {
+    uint32_t r = 0;
+    for (int k = 0; k < n; ++k) r |= ((i >> s[k].sh) & s[k].mask) << s[k].dst;
+    return r;
+}
+
+// i x and -i y: the turned rows of kGateReal
+template <typename R>
+__device__ __forceinline__ C2<R> turn(C2<R> x) { return C2<R>{-x.im, x.re}; }
+template <typename R>
+__device__ __forceinline__ C2<R> unturn(C2<R> y) { return C2<R>{y.im, -y.re}; }
+
+// A coset times the factor's matrix, kGateReal: x the coset's rows, out(i, y)
+// takes row i of the result.  ODD: kmask has every bit, so the turns are
+// register names and signs.  LANE: the matrix depends on the lane.
+template <typename R, int RHO, bool ODD, bool LANE, typename FO>
+__device__ __forceinline__ void apply_real(C2<R> (&x)[1 << RHO], const R *m, int kmask, FO out) {
+    constexpr int D = 1 << RHO;
+#pragma unroll
+    for (int j = 1; j < D; ++j)
+        if (ODD ? (__builtin_popcount(j) & 1) : (__builtin_popcount(j & kmask) & 1)) x[j] = turn(x[j]);
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+        R row[D];
+#pragma unroll
+        for (int j = 0; j < D; ++j) row[j] = LANE ? m[i * D + j] : uload(m[i * D + j]);
+        C2<R> y{(R)0, (R)0};
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            y.re = rfma(row[j], x[j].re, y.re);
+            y.im = rfma(row[j], x[j].im, y.im);
+        }
+        if (ODD ? (__builtin_popcount(i) & 1) : (__builtin_popcount(i & kmask) & 1)) y = unturn(y);
+        out(i, y);
+    }
+}
+
+// The coefficient v D of one entry, rounded to the state's dtype as the
+// stored diagonals are.
+template <typename R>
+__device__ __forceinline__ C2<R> d_entry(double vr, double vi, d2v D) {
+    const double tr = vr * D.x - vi * D.y;
+    const double ti = vr * D.y + vi * D.x;
+    return C2<R>{(R)tr, (R)ti};
+}
+// v real, or imaginary (imag): i v D
+template <typename R>
+__device__ __forceinline__ C2<R> d_entry_typed(double v, bool imag, d2v D) {
+    const C2<R> g{(R)(v * D.x), (R)(v * D.y)};
+    return imag ? C2<R>{-g.im, g.re} : g;
+}
+
+// The same for kGateRealD, partners j outermost (each D[j] is used by every
+// row of the coset): entries table[j][i], d(j) is D of element j.
+template <typename R, int RHO, bool ODD, bool LANE, typename FD, typename FO>
+__device__ __forceinline__ void apply_real_d(const C2<R> (&x)[1 << RHO], const double *m, int kmask, FD d, FO out) {
+    constexpr int D = 1 << RHO;
+    C2<R> y[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) y[i] = C2<R>{(R)0, (R)0};
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+        const d2v dj = d(j);
+        double e[D];
+#pragma unroll
+        for (int i = 0; i < D; ++i) e[i] = LANE ? m[j * D + i] : uload(m[j * D + i]);
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            const bool imag = ODD ? (__builtin_popcount(i ^ j) & 1) : (__builtin_popcount((i ^ j) & kmask) & 1);
+            cfma(y[i], d_entry_typed<R>(e[i], imag, dj), x[j]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < D; ++i) out(i, y[i]);
+}
+
+constexpr int kGateThreads = 512;
+
+// One kGateCosets block of rank RHO on the tile in LDS.
+template <typename R, int RHO>
+__device__ __forceinline__ void apply_cosets(const GateArgs &a, const GateBlock &B, C2<R> *lds, uint32_t base, int first,
+                                             int nt) {
+    constexpr int D = 1 << RHO;
+    const int cosets = (1 << a.kt) >> RHO;
+    int step[RHO];
+#pragma unroll
+    for (int q = 0; q < RHO; ++q) step[q] = lds_pos<R>((int)B.basis[q]);
+#pragma unroll 1
+    for (int cs = first; cs < cosets; cs += nt) {
+        // the coset's first row: its number's bits around the holes
+        int rep = B.ntype ? cs & ((1 << B.tshift) - 1) : cs;
+        for (int h = 0; h < B.nhole; ++h) {
+            const int low = (1 << ((int)(B.holes >> (8 * h)) & 63)) - 1;
+            rep = ((rep & ~low) << 1) | (rep & low);
+        }
+        for (int t = 0; t < B.ntype; ++t)
+            rep |= ((cs >> (B.tshift + t)) & 1) << ((B.tpos >> (8 * t)) & 31);
+        int type = 0;
+        for (int t = 0; t < B.nz; ++t)
+            type |= (int)(((rep & uload(a.words[B.ztab + 2 * t])) | (base & uload(a.words[B.ztab + 2 * t + 1]))) != 0)
+                    << t;
+        const bool lane = B.lane != 0;
+        if (!lane) type = __builtin_amdgcn_readfirstlane(type);
+        const int64_t k0 = B.coef + ((int64_t)type << (2 * RHO));
+        const int pos0 = lds_pos<R>(rep);
+        auto at = [&](int j) -> C2<R> & {
+            int m = 0;
+#pragma unroll
+            for (int q = 0; q < RHO; ++q)
+                if ((j >> q) & 1) m ^= step[q];
+            return lds[pos0 ^ m];
+        };
+        C2<R> x[D];
+        auto out = [&](int i, C2<R> y) { at(i) = y; };
+        if (B.form == kGateReal) {
+            const R *m = reinterpret_cast<const R *>(a.coef) + k0;
+#pragma unroll
+            for (int j = 0; j < D; ++j) x[j] = at(j);
+            if (B.kmask == D - 1) {
+                if (lane) apply_real<R, RHO, true, true>(x, m, B.kmask, out);
+                else apply_real<R, RHO, true, false>(x, m, B.kmask, out);
+            } else {
+                if (lane) apply_real<R, RHO, false, true>(x, m, B.kmask, out);
+                else apply_real<R, RHO, false, false>(x, m, B.kmask, out);
+            }
+        } else {
+            const double *m = a.coef64 + k0;
+            uint32_t r = base | seg_deposit(a.in, a.nin, (uint32_t)rep);
+#pragma unroll
+            for (int c = RHO - 1; c >= 0; --c) {
+                const int rp = B.rpiv[c];
+                r = ((r >> rp >> 1) << rp) | (r & ((1u << rp) - 1));
+            }
+            g_d2 *dp = (g_d2 *)B.diag + r;
+            const int64_t len = a.N >> RHO;
+            // complex64 holds every D of the coset, loaded before the rows;
+            // complex128 has no registers for that
+            constexpr bool ALL = sizeof(R) == 4;
+            d2v dj[ALL ? D : 1];
+            if constexpr (ALL)
+#pragma unroll
+                for (int j = 0; j < D; ++j) dj[j] = dp[j * len];
+            auto d = [&](int j) -> d2v {
+                if constexpr (ALL) return dj[j];
+                else return dp[j * len];
+            };
+#pragma unroll
+            for (int j = 0; j < D; ++j) x[j] = at(j);
+            if (B.kmask == D - 1) {
+                if (lane) apply_real_d<R, RHO, true, true>(x, m, B.kmask, d, out);
+                else apply_real_d<R, RHO, true, false>(x, m, B.kmask, d, out);
+            } else {
+                if (lane) apply_real_d<R, RHO, false, true>(x, m, B.kmask, d, out);
+                else apply_real_d<R, RHO, false, false>(x, m, B.kmask, d, out);
+            }
+        }
+    }
+}
+
+// A kGateRows block: every row's sum over its coset goes to the second half
+// of LDS, then replaces the row.
+template <typename R>
+__device__ __forceinline__ void apply_rows(const GateArgs &a, const GateBlock &B, C2<R> *lds, uint32_t base, int tid,
+                                           int nt) {
+    const int T = 1 << a.kt;
+    const uint32_t *w = a.words + B.wtab;
+    const int rho = B.rho, dim = 1 << rho;
+    g_d2 *dtab = (g_d2 *)B.diag;
+    const C2<R> *mc = reinterpret_cast<const C2<R> *>(a.coef);
+    const R *mr = reinterpret_cast<const R *>(a.coef);
+#pragma unroll 1
+    for (int i = tid; i < T; i += nt) {
+        int own = 0, e = i;             // own coordinate, the coset's element 0
+        for (int c = 0; c < rho; ++c)
+            if ((i >> (int)uload(w[c])) & 1) {
+                own |= 1 << c;
+                e ^= (int)uload(w[rho + c]);
+            }
+        int64_t tab = 0;
+        for (int t = 0; t < B.nz; ++t)
+            tab |= (int64_t)(((e & uload(a.words[B.ztab + 2 * t])) | (base & uload(a.words[B.ztab + 2 * t + 1]))) != 0)
+                   << t;
+        tab = B.coef + tab * dim * dim;
+        int64_t dc = 0;
+        if (dtab) {
+            dc = (int64_t)(base | seg_deposit(a.in, a.nin, (uint32_t)e));
+            for (int c = rho - 1; c >= 0; --c) {
+                const int rp = (int)uload(w[2 * rho + c]);
+                dc = ((dc >> (rp + 1)) << rp) | (dc & ((int64_t(1) << rp) - 1));
+            }
+        }
+        C2<R> y{(R)0, (R)0};
+#pragma unroll 1
+        for (int j = 0; j < dim; ++j) {
+            int at = e;
+            for (int c = 0; c < rho; ++c)
+                if ((j >> c) & 1) at ^= (int)uload(w[rho + c]);
+            const C2<R> x = lds[lds_pos<R>(at)];
+            if (B.form == kGateReal) {
+                const C2<R> xt = (__builtin_popcount(j & B.kmask) & 1) ? turn(x) : x;
+                const R k = mr[tab + (int64_t)own * dim + j];
+                y.re = rfma(k, xt.re, y.re);
+                y.im = rfma(k, xt.im, y.im);
+            } else if (B.form == kGateComplex) {
+                cfma(y, mc[tab + (int64_t)own * dim + j], x);
+            } else {
+                const d2v D = dtab[(int64_t)j * (a.N >> rho) + dc];
+                const int64_t k = tab + (int64_t)j * dim + own;
+                if (B.form == kGateRealD)
+                    cfma(y, d_entry_typed<R>(a.coef64[k], __builtin_popcount((own ^ j) & B.kmask) & 1, D), x);
+                else
+                    cfma(y, d_entry<R>(a.coef64[2 * k], a.coef64[2 * k + 1], D), x);
+            }
+        }
+        if (B.form == kGateReal && (__builtin_popcount(own & B.kmask) & 1)) y = unturn(y);
+        lds[T + i] = y;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int i = tid; i < T; i += nt) lds[lds_pos<R>(i)] = lds[T + i];
+}
+
+__device__ __forceinline__ GateBlock uload_block(const GateBlock &p) {
+    GateBlock r;
+    r.diag = uload(p.diag);
+    r.holes = uload(p.holes);
+    r.kind = uload(p.kind);
+    r.rho = uload(p.rho);
+    r.form = uload(p.form);
+    r.kmask = uload(p.kmask);
+    r.nz = uload(p.nz);
+    r.ztab = uload(p.ztab);
+    r.coef = uload(p.coef);
+    r.wtab = uload(p.wtab);
+    r.nhole = uload(p.nhole);
+    r.ntype = uload(p.ntype);
+    r.lane = uload(p.lane);
+    r.tshift = uload(p.tshift);
+    r.tpos = uload(p.tpos);
+#pragma unroll
+    for (int c = 0; c < kGateMaxCoset; ++c) {
+        r.basis[c] = uload(p.basis[c]);
+        r.rpiv[c] = uload(p.rpiv[c]);
+    }
+    return r;
+}
+
+template <typename R, bool STREAM>
+__global__ __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(4))) void gate_kernel(GateArgs a) {
+    constexpr bool PAIR = sizeof(R) == 4;           // linear phases: two adjacent rows per 16-byte access
+    constexpr int H = PAIR ? 2 : 1;
+    constexpr int G = 8;                            // 16-byte accesses of a thread's linear rows
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    C2<R> *lds = reinterpret_cast<C2<R> *>(smem_raw);
+    const int tid = threadIdx.x;
+    const int nt = blockDim.x;
+    const int T = 1 << a.kt;
+
+    // Tile and state of number g: workgroups are dealt to the 8 XCDs
+    // round-robin, so the states of one tile follow 8 apart on one XCD and
+    // find its D in that XCD's L2.
+    auto place = [&](int g, int &tile, int &b) {
+        if ((a.tiles & 7) == 0) {
+            const int q = g >> 3;
+            b = q % a.batch;
+            tile = (q / a.batch) * 8 + (g & 7);
+        } else {
+            b = g % a.batch;
+            tile = g / a.batch;
+        }
+    };
+    // Linear phases: access p of thread t covers local row(s) first(t, p) (and
+    // + 1 for complex64); the row of a local index is a bit deposit, so it
+    // splits over the bits of the thread and of the access.
+    auto first_of = [&](int t, int p) { return H * (t + p * nt); };
+    auto row_part = [&](uint32_t base, int t) { return base | seg_deposit(a.in, a.nin, (uint32_t)first_of(t, 0)); };
+    auto row_at = [&](uint32_t part, int p) { return (int)(part | seg_deposit(a.in, a.nin, (uint32_t)(H * p * nt))); };
+    // The thread's number, opaque to the compiler: each phase computes its
+    // rows and LDS positions afresh instead of holding them in registers
+    // through the blocks.
+    auto fresh = [&]() {
+        int t = tid;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    C2<R> u[G][H];
+    auto load_tile = [&](int g) {
+        int tile, b;
+        place(g, tile, b);
+        const uint32_t base = seg_deposit(a.out, a.nout, (uint32_t)tile);
+        const C2<R> *psi = reinterpret_cast<const C2<R> *>(a.psi) + (int64_t)b * a.N;
+        const int t = fresh();
+        const uint32_t part = row_part(base, t);
+#pragma unroll
+        for (int p = 0; p < G; ++p) {
+            const int r = first_of(t, p) < T ? row_at(part, p) : (int)base;
+            if constexpr (PAIR) ld2(psi, r, u[p][0], u[p][1]);
+            else u[p][0] = ld1(psi, r);
+        }
+    };
+    const int g = blockIdx.x;
+    load_tile(g);
+    {
+        int tile, b;
+        place(g, tile, b);
+        const uint32_t base = seg_deposit(a.out, a.nout, (uint32_t)tile);
+        {
+            const R scale = inv_norm<R>(a.nrm2, b);
+            const int t = fresh();
+#pragma unroll
+            for (int p = 0; p < G; ++p)
+#pragma unroll
+                for (int h = 0; h < H; ++h) u[p][h] = cscale(u[p][h], scale);
+            if (a.stage_diag) {
+                const C2<R> *dg = reinterpret_cast<const C2<R> *>(a.stage_diag);
+                const uint32_t part = row_part(base, t);
+#pragma unroll
+                for (int p = 0; p < G; ++p) {
+                    const int r = first_of(t, p) < T ? row_at(part, p) : (int)base;
+                    C2<R> k[2];
+                    if constexpr (PAIR) ld2_cached(dg, r, k[0], k[1]);
+                    else k[0] = ld1_cached(dg, r);
+#pragma unroll
+                    for (int h = 0; h < H; ++h) {
+                        C2<R> y{(R)0, (R)0};
+                        cfma(y, k[h], u[p][h]);
+                        u[p][h] = y;
+                    }
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < G; ++p)
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+                    if (first_of(t, p) < T) lds[lds_pos<R>(first_of(t, p) + h)] = u[p][h];
+        }
+        for (int s = 0; s < a.steps; ++s) {
+            const int part = a.steps == 1 ? 0 : s == 0 ? 1 : s == a.steps - 1 ? 3 : 2;
+            const int k1 = a.part[part + 1];
+            for (int k = a.part[part]; k < k1; ++k) {
+                const GateBlock B = uload_block(a.blocks[k]);
+                __syncthreads();
+                if (B.kind == kGateCosets) {
+                    if (B.rho == 3) apply_cosets<R, 3>(a, B, lds, base, fresh(), nt);
+                    else if (B.rho == 2) apply_cosets<R, 2>(a, B, lds, base, fresh(), nt);
+                    else apply_cosets<R, 1>(a, B, lds, base, fresh(), nt);
+                } else if (B.kind == kGateDiag) {
+                    const C2<R> *dg = reinterpret_cast<const C2<R> *>(B.diag);
+#pragma unroll 1
+                    for (int i = H * fresh(); i < T; i += H * nt) {
+                        const int r = (int)(base | seg_deposit(a.in, a.nin, (uint32_t)i));
+                        C2<R> d[2];
+                        if constexpr (PAIR) ld2_cached(dg, r, d[0], d[1]);
+                        else d[0] = ld1_cached(dg, r);
+#pragma unroll
+                        for (int h = 0; h < H; ++h) {
+                            C2<R> y{(R)0, (R)0};
+                            cfma(y, d[h], lds[lds_pos<R>(i + h)]);
+                            lds[lds_pos<R>(i + h)] = y;
+                        }
+                    }
+                } else {
+                    apply_rows<R>(a, B, lds, base, fresh(), nt);
+                }
+            }
+        }
+        __syncthreads();
+
+        {
+            C2<R> *psi = reinterpret_cast<C2<R> *>(a.psi) + (int64_t)b * a.N;
+            const int t = fresh();
+            const uint32_t part = row_part(base, t);
+            double ss = 0.0;
+#pragma unroll
+            for (int p = 0; p < G; ++p)
+                if (first_of(t, p) < T) {
+                    C2<R> y[2];
+#pragma unroll
+                    for (int h = 0; h < H; ++h) {
+                        y[h] = lds[lds_pos<R>(first_of(t, p) + h)];
+                        const double re = (double)y[h].re, im = (double)y[h].im;
+                        if (a.norm_out) ss += re * re + im * im;
+                    }
+                    if constexpr (PAIR) st2<STREAM>(psi, row_at(part, p), y[0], y[1]);
+                    else st1<STREAM>(psi, row_at(part, p), y[0]);
+                }
+            if (a.norm_out) {
+                // FP64 sum of |y|^2 over the tile's rows in a fixed order:
+                // rows per thread, a wave butterfly, then the waves in order
+                __syncthreads();
+                double *red = reinterpret_cast<double *>(smem_raw);
+                const double w = wave_sum(ss);
+                if ((tid & 63) == 0) red[tid >> 6] = w;
+                __syncthreads();
+                if (tid == 0) {
+                    double sum = 0.0;
+                    for (int q = 0; q < (nt >> 6); ++q) sum += red[q];
+                    double *o = a.norm_out + ((size_t)b * a.tiles + tile) * 4;
+                    o[0] = 0.0;
+                    o[1] = 0.0;
+                    o[2] = sum;
+                    o[3] = 0.0;
+                }
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------ launcher
+
+static std::mutex &gate_attr_mutex() {
+    static std::mutex m;
+    return m;
+}
+
+template <typename R, bool STREAM>
+static int gate_launch(const GateArgs &a, void *stream) {
+    auto kern = gate_kernel<R, STREAM>;
+    const int T = 1 << a.kt;
+    const size_t tile = (size_t)T * sizeof(C2<R>) * (a.by_rows ? 2 : 1), lds = tile < 256 ? 256 : tile;
+    // every linear row has a thread (8 accesses of 16 bytes each); a small
+    // tile gets up to two rows per thread
+    constexpr int RPT = 8 * 16 / (int)sizeof(C2<R>);
+    int nt = T / 2;
+    if (nt < 64) nt = 64;
+    if (nt > kGateThreads) nt = kGateThreads;
+    if (nt * RPT < T) return (int)hipErrorInvalidValue;
+    if (lds > 65536) {
+        static std::atomic<int> allowed{65536};
+        if ((int)lds > allowed.load()) {
+            std::lock_guard<std::mutex> lock(gate_attr_mutex());
+            if ((int)lds > allowed.load()) {
+                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                if (e != hipSuccess) return (int)e;
+                allowed.store((int)lds);
+            }
+        }
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)a.total), dim3(nt), lds, reinterpret_cast<hipStream_t>(stream), a);
+    return (int)hipGetLastError();
+}
+
+// The FP64 phases in the order the coset products read them: one thread per
+// row x, element j (its pivot bits) of the coset whose first row is x with
+// the masks of j taken out.
+struct PhaseOrderArgs {
+    const d2v *phase;
+    d2v *out;
+    int64_t N;
+    int32_t rho;
+    uint32_t basis[HS_MAX_SUPPORT];
+};
+__global__ void phase_order_kernel(PhaseOrderArgs a) {
+    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < a.N; x += (int64_t)gridDim.x * blockDim.x) {
+        uint32_t c = (uint32_t)x, j = 0;
+        for (int k = 0; k < a.rho; ++k) {
+            const int q = 31 - __builtin_clz(a.basis[k]);
+            if (((uint32_t)x >> q) & 1u) {
+                j |= 1u << k;
+                c ^= a.basis[k];
+            }
+        }
+        for (int k = a.rho - 1; k >= 0; --k) {
+            const int q = 31 - __builtin_clz(a.basis[k]);
+            c = ((c >> q >> 1) << q) | (c & ((1u << q) - 1));
+        }
+        a.out[(int64_t)j * (a.N >> a.rho) + c] = a.phase[x];
+    }
+}
+
+int launch_phase_order(const double *phase, double *out, int64_t N, const std::vector<uint64_t> &basis, void *stream) {
+    if (basis.size() > HS_MAX_SUPPORT) return (int)hipErrorInvalidValue;
+    PhaseOrderArgs a{};
+    a.phase = reinterpret_cast<const d2v *>(phase);
+    a.out = reinterpret_cast<d2v *>(out);
+    a.N = N;
+    a.rho = (int32_t)basis.size();
+    for (size_t k = 0; k < basis.size(); ++k) a.basis[k] = (uint32_t)basis[k];
+    const int64_t g = (N + 255) / 256;
+    hipLaunchKernelGGL(phase_order_kernel, dim3((unsigned)(g < (1 << 16) ? g : (1 << 16))), dim3(256), 0,
+                       reinterpret_cast<hipStream_t>(stream), a);
+    return (int)hipGetLastError();
+}
+
+int launch_gates(const GateLaunch &L, const GateTables &t, const GateRun &r, bool c128, bool stream_out, void *stream) {
+    GateArgs a{};
+    if (L.in.size() > (size_t)kGateSegs || L.out.size() > (size_t)kGateSegs) return (int)hipErrorInvalidValue;
+    // row pairs of the linear phases are adjacent in the state
+    if (!(L.tile & 1) || L.kt < 1 || L.rows != (int64_t(1) << L.kt)) return (int)hipErrorInvalidValue;
+    const int64_t tiles = r.N / L.rows, total = tiles * r.batch;
+    if (tiles < 1 || total > (int64_t(1) << 30) || (r.steps > 1 && tiles != 1)) return (int)hipErrorInvalidValue;
+    a.psi = r.psi;
+    a.N = r.N;
+    a.batch = r.batch;
+    a.kt = L.kt;
+    a.tiles = (int32_t)tiles;
+    a.total = (int32_t)total;
+    a.nin = (int32_t)L.in.size();
+    a.nout = (int32_t)L.out.size();
+    for (int k = 0; k < a.nin; ++k) a.in[k] = L.in[k];
+    for (int k = 0; k < a.nout; ++k) a.out[k] = L.out[k];
+    a.blocks = t.blocks;
+    a.words = t.words;
+    a.coef = t.coef;
+    a.coef64 = t.coef64;
+    a.stage_diag = r.stage_diag;
+    a.nrm2 = r.nrm2;
+    a.norm_out = r.norm_out;
+    a.by_rows = r.by_rows;
+    a.steps = r.steps;
+    for (int q = 0; q < 5; ++q) a.part[q] = r.part[q];
+    if (c128) return stream_out ? gate_launch<double, true>(a, stream) : gate_launch<double, false>(a, stream);
+    return stream_out ? gate_launch<float, true>(a, stream) : gate_launch<float, false>(a, stream);
+}
+
+}  // namespace hs

@@ -13,7 +13,7 @@ namespace hs {
 
 constexpr double kTau = 1e-15;          // |L[a,b]| <= kTau counts as zero
 constexpr int kMaxRun = 8;              // factors fused into one launch
-constexpr int kMaxDiagsPerLaunch = 128; // descriptors per launch
+constexpr int kMaxDiagsPerLaunch = 128; // stored diagonals per entry of the fusion list
 constexpr size_t kDiagAlignBytes = 256; // start of every stored diagonal
 
 struct Term {
@@ -67,9 +67,6 @@ struct DiagDesc {
     int32_t m;         // d >> qb when regular
     int32_t regular;   // d is a multiple of 2^qb
     int32_t lo, hi;    // rows r with 0 <= r + d < N: [lo, hi)
-    int32_t ps, pc;    // storage order (perm_pos, storage_order.h): split bit s and chunk bits c;
-                       // 0, 0 = natural
-    int32_t plr;       // ((N - |d|) >> s) << c: entries between consecutive chunk columns
     int32_t pad;
 };
 
@@ -78,22 +75,13 @@ struct TileArgs {
     const void *x;
     int64_t stride;          // elements between consecutive states (= N)
     int32_t N;
-    int32_t nf;              // factors in this launch
-    int32_t dstart[kMaxRun + 1];
+    int32_t nd;              // diagonals
     const DiagDesc *desc;
     int32_t qb, kb, logW, nlw_log, T;
-    const double *nrm2;      // per-state squared norms to divide out, or null
-    int *viol;               // closure-violation flag (closed launches)
-    int32_t swizzle;         // deal contiguous eighths of the tiles to the 8 XCDs
     const void *x0;          // Horner launches: y = x0 + alpha (A x), x0 read at the row only
     double alpha_re, alpha_im;
-    int32_t ragged;          // open contiguous launch whose last tile passes row N (any N)
-    double *norm_out;        // or null: per tile and state, the FP64 sum of |y|^2 over the
-                             // tile's rows at [(b * gridDim.x + tile) * 4 + 2] (others 0)
+    int32_t ragged;          // contiguous launch whose last tile passes row N (any N)
     int32_t stream_out;      // write y with non-temporal stores (see kStreamOutBytes)
-    int32_t pairs;           // closed complex64 launch in the pair kernel: 1 even offsets only,
-                             // 2 some odd offsets (contiguous tiles)
-    int32_t perm;            // closed launch with a diagonal stored out of natural order (ps > 0)
 };
 
 // States of at least this many bytes (the chunk of up to HS_MAX_BATCH states
@@ -128,31 +116,13 @@ int launch_construct(const ConstructArgs &a, int nd, int64_t max_len, bool c128,
 // (s, c) (perm_pos), for k < count: the natural order of a stored range
 int launch_perm_gather(const void *src, void *dst, int64_t start, int64_t count, int64_t len, int s, int c,
                        bool c128, void *stream);
-int launch_tile(const TileArgs &a, int batch, bool c128, bool closed, void *stream);
-// open launch with the Horner epilogue y = x0 + alpha (A x); y may alias x0, not x
+int launch_tile(const TileArgs &a, int batch, bool c128, void *stream);
+// the same with the Horner epilogue y = x0 + alpha (A x); y may alias x0, not x
 int launch_tile_horner(const TileArgs &a, int batch, bool c128, void *stream);
-// Whole evolution of small states in one launch (one workgroup per state,
-// the state held in LDS).  Each step part is a list of entries, one per
-// diagonal it applies in order: the diagonal's storage and range, and
-// whether it is the last diagonal of its factor.
-struct WholeEntry {
-    const void *ptr;            // entries of the diagonal, the state's element type
-    int32_t off, lo, hi;        // offset d; rows r with 0 <= r + d < N: [lo, hi)
-    uint32_t last;              // 1 for the last diagonal of a factor
-};
-struct WholeArgs {
-    void *psi;                  // [batch][stride] states of the handle's dtype
-    int64_t stride;
-    int32_t N;
-    int32_t steps;
-    const WholeEntry *walk;     // concatenated entry lists of the step parts
-    int32_t part_off[5];        // part q applies walk[part_off[q] .. part_off[q+1])
-};
-// Largest state (rows) the whole-evolution kernel holds: 8192 complex64 or
+// Largest state (rows) evolved whole by one workgroup: 8192 complex64 or
 // 4096 complex128 rows (64 KiB of LDS).
 constexpr int kWholeRowsC64 = 8192;
 constexpr int kWholeRowsC128 = 4096;
-int launch_whole(const WholeArgs &a, int batch, bool c128, void *stream);
 // the single-diagonal factor applied `steps` times in one pass (N even)
 int launch_diag_steps(void *y, const void *x, const void *diag, int64_t N, int batch, int steps,
                       const double *nrm2, bool c128, bool stream_out, void *stream);

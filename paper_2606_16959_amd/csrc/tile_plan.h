@@ -51,19 +51,9 @@ inline int tile_rows_max(int dtype, int batch, long long N, bool open = false) {
 }
 
 // Launch-plan tuning knobs, read from the environment at every evolve (a
-// handle keeps one plan per batch size and knob setting): HAMSIM_WMIN_BYTES (shortest run of consecutive rows a
-// strided tile may have, default 256), HAMSIM_MAX_FUSE (factors per launch,
-// default 8), HAMSIM_PAIR_LDS (which closed complex64 launches whose every
-// diagonal pairs run the pair kernel: 2 all, odd offsets of contiguous tiles
-// included; 1 all except one-state strided launches whose row runs are
-// under 1 KiB and whose diagonals are stored in natural order --
-// translation-bound launches, where the row-by-row kernel measured faster;
-// 0 none; same results; default 1),
-// HAMSIM_XCD_SWIZZLE (which launches deal each XCD one contiguous
-// eighth of the tiles instead of every eighth tile: 0 none, 1 all, 2 strided
-// tiles only, 3 contiguous tiles only; default 3: strided launches of
-// complex64 states measured 1-4% faster without it, contiguous ones faster
-// with it).
+// handle keeps one plan per batch size and knob setting): HAMSIM_WMIN_BYTES
+// (shortest run of consecutive rows a strided tile may have, default 256) and
+// HAMSIM_MAX_FUSE (factors per launch, default 8: no limit).
 inline int env_int(const char *name, int dflt, int lo, int hi) {
     const char *v = std::getenv(name);
     if (!v || !*v) return dflt;
@@ -73,20 +63,14 @@ inline int env_int(const char *name, int dflt, int lo, int hi) {
     return (int)std::min<long>(hi, std::max<long>(lo, x));
 }
 struct PlanKey {
-    int chunk, fuse, wmin_bytes, max_fuse, swizzle, pairs;
+    int chunk, fuse, wmin_bytes, max_fuse;
     bool operator<(const PlanKey &o) const {
-        return std::tie(chunk, fuse, wmin_bytes, max_fuse, swizzle, pairs) <
-               std::tie(o.chunk, o.fuse, o.wmin_bytes, o.max_fuse, o.swizzle, o.pairs);
+        return std::tie(chunk, fuse, wmin_bytes, max_fuse) < std::tie(o.chunk, o.fuse, o.wmin_bytes, o.max_fuse);
     }
 };
 inline PlanKey plan_key(int chunk, bool fuse) {
     return PlanKey{chunk, fuse ? 1 : 0, env_int("HAMSIM_WMIN_BYTES", 256, 8, 1 << 20),
-                   env_int("HAMSIM_MAX_FUSE", kMaxRun, 1, kMaxRun),
-                   env_int("HAMSIM_XCD_SWIZZLE", 3, 0, 3), env_int("HAMSIM_PAIR_LDS", 1, 0, 2)};
-}
-// Whether a launch of geometry `g` deals contiguous eighths of its tiles to the XCDs.
-inline bool swizzled(int mode, const Geo &g) {
-    return mode == 1 || (mode == 2 && g.qb > 0) || (mode == 3 && g.qb == 0);
+                   env_int("HAMSIM_MAX_FUSE", kMaxRun, 1, kMaxRun)};
 }
 inline int w_min(int dtype, const PlanKey &k) { return std::max(1, k.wmin_bytes / (dtype == HS_C128 ? 16 : 8)); }
 
@@ -179,17 +163,11 @@ inline TileArgs open_args(const Geo &geo, const DiagDesc *ddev, int nd, const vo
     a.x = x;
     a.stride = N;
     a.N = (int32_t)N;
-    a.nf = 1;
-    a.dstart[0] = 0;
-    a.dstart[1] = nd;
+    a.nd = nd;
     a.desc = ddev;
     a.qb = geo.qb; a.kb = geo.kb; a.logW = geo.logW; a.nlw_log = geo.nlw_log; a.T = geo.T;
-    a.nrm2 = nullptr;
-    a.viol = nullptr;
-    a.swizzle = 0;
     a.ragged = (N % geo.T) != 0;
     a.stream_out = 0;
-    a.pairs = 0;
     return a;
 }
 

@@ -125,6 +125,7 @@ __device__ __forceinline__ void ld2_cached(const C2<float> *p, int i, C2<float> 
     a = C2<float>{v.x, v.y};
     b = C2<float>{v.z, v.w};
 }
+__device__ __forceinline__ C2<float> ld1_cached(const C2<float> *p, int i) { return ld1(p, i); }
 __device__ __forceinline__ C2<double> ld1_cached(const C2<double> *p, int i) {
     const d2v u = *((g_d2 *)(p) + i);
     return C2<double>{u.x, u.y};
@@ -136,6 +137,12 @@ __device__ __forceinline__ void ld2_cached(const C2<double> *p, int i, C2<double
     b = C2<double>{v.x, v.y};
 }
 
+// A value of a table at a uniform address that the kernel does not write:
+// constant memory as far as it goes, so the load is a scalar one.
+template <typename V>
+__device__ __forceinline__ V uload(const V &p) {
+    return *(const __attribute__((address_space(4))) V *)&p;
+}
 // wave64 butterfly sum (fixed order)
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll

@@ -50,12 +50,6 @@ __device__ __forceinline__ constexpr int lds_pos(int i) {
     return gate_lds_pos(i, sizeof(R) == 8);
 }
 
-// A value of a program table at a uniform address: constant memory as far as
-// the kernel goes, so the load is a scalar one.
-template <typename V>
-__device__ __forceinline__ V uload(const V &p) {
-    return *(const __attribute__((address_space(4))) V *)&p;
-}
 __device__ __forceinline__ uint32_t seg_deposit(const GateSeg *s, int n, uint32_t i) {
     uint32_t r = 0;
     for (int k = 0; k < n; ++k) r |= ((i >> s[k].sh) & s[k].mask) << s[k].dst;

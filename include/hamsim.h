@@ -368,7 +368,10 @@ hs_status hs_dia_norm_bound(hs_dia A, void *stream, double *nu);
  * by Horner's rule, K stages w <- x + (-i dt / j) H w for j = K .. 1 from
  * w = x, each stage one DIA SpMV of H (Alg. 1) with the update fused into
  * its epilogue.  H is read once per stage; U is never built, so the memory
- * and traffic of the propagator's diagonals (Alg. 2, Section 3.2) vanish.
+ * and traffic of the propagator's diagonals (Alg. 2, Section 3.2) vanish.  An
+ * operator from hs_dia_from_pauli (or its hs_dia_to_c64 copy) is applied by
+ * its X-masks, one partner row each, and of its diagonals only the main one
+ * is read; other operators by their stored diagonals.
  */
 /* Smallest K >= 1 (at most max_terms <= 64) with (|dt| nu(H))^(K+1) / (K+1)!
  * < tol: the first dropped term of the series then has 2-norm below tol.

@@ -9,13 +9,16 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <cstring>
 #include <map>
+#include <memory>
 #include <new>
 #include <set>
 #include <string>
 #include <vector>
 
 #include "hs_internal.h"
+#include "pauli_form.h"
 #include "tile_plan.h"
 
 using namespace hs::plan;
@@ -34,6 +37,7 @@ struct hs_dia_s {
     hipStream_t st = nullptr;           // allocation stream
     int64_t *d_offs = nullptr;          // device copies of offs / ptr (lazy)
     void **d_ptrs = nullptr;
+    std::shared_ptr<const hs::PauliForm> form;   // the Pauli sum it was made from, when it has a form
 
     size_t elem() const { return dtype == HS_C128 ? 16 : 8; }
     int64_t len(size_t j) const { return N - (offs[j] < 0 ? -offs[j] : offs[j]); }
@@ -435,6 +439,8 @@ hs_status hs_dia_from_pauli(int n, int n_terms, const char *const *pauli_terms, 
         }
         A->offs = keep;
         A->ptr = kp;
+        auto form = std::make_shared<hs::PauliForm>();
+        if (hs::pauli_form(terms, *form)) A->form = form;
         (void)hipFreeAsync(A->d_offs, st);
         (void)hipFreeAsync(A->d_ptrs, st);
         A->d_offs = nullptr;
@@ -670,6 +676,7 @@ hs_status hs_dia_to_c64(hs_dia A, void *stream, hs_dia *out) {
     if (le) { delete B; return dhip((hipError_t)le, "convert kernel"); }
     hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) { delete B; return dhip(e, "convert"); }
+    B->form = A->form;
     *out = B;
     return HS_OK;
 }
@@ -791,12 +798,46 @@ hs_status hs_taylor_evolve(hs_dia H, void *psi, int batch, double dt, int K, int
     }
     std::map<int, DiagDesc *> descs;
     std::vector<std::vector<DiagDesc>> host_descs;
+    // an operator made from Pauli strings is applied by its X-masks
+    const hs::PauliForm *form = H->form && !H->form->masks.empty() && N >= 2 ? H->form.get() : nullptr;
+    hs::PauliArgs pa{};
+    std::vector<float> tab32;
+    std::vector<hs::PauliMask> masks;
+    if (form) {
+        hs::PauliMask *dm = nullptr;
+        masks = form->masks;
+        if (c128) {
+            std::complex<double> *dt64 = nullptr;
+            DHIP(tmp.up(form->tab, &dt64), "mask table");
+            pa.tab = dt64;
+        } else {
+            for (const auto &v : form->tab) {
+                tab32.push_back((float)v.real());
+                tab32.push_back((float)v.imag());
+            }
+            for (auto &k : masks) {
+                const float c[4] = {(float)k.c[0], (float)k.c[1], (float)k.c[2], (float)k.c[3]};
+                std::memcpy(k.c, c, sizeof c);
+            }
+            float *dt32 = nullptr;
+            DHIP(tmp.up(tab32, &dt32), "mask table");
+            pa.tab = dt32;
+        }
+        DHIP(tmp.up(masks, &dm), "mask table");
+        pa.masks = dm;
+        pa.host_masks = form->m.data();
+        pa.nmask = (int32_t)form->masks.size();
+        pa.N = N;
+        for (int j = 0; j < nd; ++j)
+            if (H->offs[j] == 0) pa.diag = H->ptr[j];
+    }
     for (int c0 = 0; c0 < batch; c0 += HS_MAX_BATCH) {
         const int chunk = std::min(HS_MAX_BATCH, batch - c0);
         const Geo geo = generic_geometry(offs.data(), nd, N, H->dtype, chunk);
         DiagDesc *dd = nullptr;
         auto it = descs.find(chunk);
-        if (it == descs.end()) {
+        if (form) {
+        } else if (it == descs.end()) {
             host_descs.emplace_back();
             fill_descs(offs.data(), ptrs.data(), nd, N, geo, host_descs.back());
             DHIP(tmp.up(host_descs.back(), &dd), "descriptors");
@@ -815,6 +856,16 @@ hs_status hs_taylor_evolve(hs_dia H, void *psi, int batch, double dt, int K, int
             const void *w = cur;
             for (int j = K; j >= 1; --j) {
                 void *out = (K == 1) ? other : (j == 1 ? cur : buf[(K - j) & 1]);
+                if (form) {
+                    pa.y = out;
+                    pa.x = w;
+                    pa.x0 = cur;
+                    pa.alpha_im = -dt / j;
+                    int le = hs::launch_pauli_horner(pa, chunk, c128, stream_out(chunk, N, H->dtype) != 0, st);
+                    if (le) return dhip((hipError_t)le, "Pauli stage launch");
+                    w = out;
+                    continue;
+                }
                 TileArgs a = open_args(geo, dd, nd, w, out, N);
                 a.stream_out = stream_out(chunk, N, H->dtype);
                 a.x0 = cur;

@@ -17,6 +17,7 @@
 #include <set>
 
 #include "hs_internal.h"
+#include "pauli_form.h"
 
 namespace hs {
 namespace {
@@ -148,6 +149,63 @@ hs_status parse_terms(int n, int n_terms, const char *const *strings, const doub
     }
 
     return HS_OK;
+}
+
+bool pauli_form(const std::vector<Term> &terms, PauliForm &out) {
+    static const std::complex<double> ipow[4] = {{1, 0}, {0, 1}, {-1, 0}, {0, -1}};
+    out = PauliForm();
+    std::map<uint64_t, std::vector<const Term *>> by_mask;
+    for (const Term &t : terms)
+        if (t.x) by_mask[t.x].push_back(&t);
+    if (by_mask.size() > (size_t)kPauliMaxMasks) return false;
+    for (auto it = by_mask.rbegin(); it != by_mask.rend(); ++it) {
+        const uint64_t m = it->first;
+        PauliMask k{};
+        k.m = (uint32_t)m;
+        k.tab = (int32_t)out.tab.size();
+        // independent parity masks, and the sums of them that give each term's
+        std::vector<uint64_t> basis;
+        auto pattern = [&](uint64_t z) {
+            for (uint32_t q = 0; q < (1u << basis.size()); ++q) {
+                uint64_t v = 0;
+                for (size_t j = 0; j < basis.size(); ++j)
+                    if ((q >> j) & 1) v ^= basis[j];
+                if (v == z) return (int)q;
+            }
+            return -1;
+        };
+        for (const Term *t : it->second)
+            if (pattern(t->z) < 0) {
+                if (basis.size() == (size_t)kPauliMaxRank) return false;
+                basis.push_back(t->z);
+            }
+        k.rank = (int32_t)basis.size();
+        for (size_t j = 0; j < basis.size(); ++j) k.z[j] = (uint32_t)basis[j];
+        k.z0 = k.z[0];
+        bool any = false;
+        for (uint32_t q = 0; q < (1u << basis.size()); ++q) {
+            std::complex<double> h = 0.0;
+            for (const Term *t : it->second) {
+                // parity of (r ^ m) & z, r's own parities being q
+                const int odd = (popc((uint64_t)(q & (uint32_t)pattern(t->z))) + popc(m & t->z)) & 1;
+                h += ipow[t->ny & 3] * (odd ? -t->c : t->c);
+            }
+            any = any || h != 0.0;
+            out.tab.push_back(h);
+        }
+        if (!any) {                  // cancelling strings
+            out.tab.resize(k.tab);
+            continue;
+        }
+        const std::complex<double> c0 = out.tab[k.tab], c1 = out.tab[k.tab + (k.rank ? 1 : 0)];
+        k.c[0] = c0.real();
+        k.c[1] = c0.imag();
+        k.c[2] = c1.real();
+        k.c[3] = c1.imag();
+        out.masks.push_back(k);
+        out.m.push_back(k.m);
+    }
+    return true;
 }
 
 void layout_factor(Factor &f, int64_t N, size_t elem_bytes) {

@@ -49,21 +49,41 @@ def test_row_kernel_equals_tiles_and_definition(N, nd, dtype):
     assert np.all(np.abs(many - ref) <= fac * mag + 1e-300)
 
 
-@pytest.mark.parametrize("n,dtype", [(1, "c128"), (6, "c64"), (17, "c128"), (18, "c64")])
-def test_taylor_batches_agree(n, dtype):
-    """A Taylor update of one state gives the bits it has in a batch."""
+@pytest.mark.parametrize("n,dtype", [(1, "c128"), (6, "c64"), (11, "c128"), (12, "c64"), (17, "c128"), (18, "c64")])
+def test_taylor_by_masks(n, dtype):
+    """A Taylor update of an operator from Pauli strings, applied by its
+    X-masks, against the same operator from its stored diagonals (which has no
+    masks); one state gives the bits it has in a batch (n = 17 and 18: the row
+    kernel and the tile kernel).  Strings of one, two and four parities per
+    mask, real and imaginary entries, and a pair that cancels in half the rows."""
     hs, torch = hs_gpu()
     from paper_2606_16959_amd import dia
-    note(f"taylor batches n={n} {dtype}")
+    note(f"taylor by masks n={n} {dtype}")
+    rng = np.random.default_rng(n)
     strings = ["I" * q + "X" + "I" * (n - q - 1) for q in range(n)] + ["Z" * n]
-    H = dia.from_pauli(strings, [0.3 + 0.01 * q for q in range(n)] + [0.7], n)
+    if n >= 6:
+        tail = "I" * (n - 6)
+        strings += ["XXIIII" + tail, "YYIIII" + tail, "XYZIII" + tail, "IXZIII" + tail, "IXIZII" + tail,
+                    "IXIIZI" + tail, "IXIIIZ" + tail, "ZIIIIY" + tail]
+        if n > 6:
+            strings += ["I" * (n - 2) + "YX", "X" + "I" * (n - 2) + "X", "Y" + "Z" * (n - 2) + "Y"]
+    coeffs = rng.uniform(0.2, 1.0, len(strings))
+    coeffs[len(strings) - 1] = coeffs[len(strings) - 2]
+    H = dia.from_pauli(strings, coeffs, n)
+    plain = dia.from_dict(H.to_dict(), 1 << n)
     if dtype == "c64":
-        H = H.to_c64()
+        H, plain = H.to_c64(), plain.to_c64()
     g = torch.Generator(device="cuda")
     g.manual_seed(n)
     real = torch.float64 if dtype == "c128" else torch.float32
     x = torch.view_as_complex(torch.randn((5, 1 << n, 2), generator=g, device="cuda", dtype=real))
-    many, one = x.clone(), x[3:4].clone()
-    dia.taylor_evolve(H, many, 0.1, 4, 2)
-    dia.taylor_evolve(H, one, 0.1, 4, 2)
+    dt = 0.5 / dia.norm_bound(dia.from_dict(H.to_dict(), 1 << n))
+    many, one, ref = x.clone(), x[3:4].clone(), x.clone()
+    dia.taylor_evolve(H, many, dt, 4, 2)
+    dia.taylor_evolve(H, one, dt, 4, 2)
+    dia.taylor_evolve(plain, ref, dt, 4, 2)
     assert torch.equal(many[3], one[0])
+    # |dt| nu = 1/2: 8 stages of at most 2 n + 20 multiply-adds, each of the
+    # step's scale; rounding of the coefficients included
+    eps = 2.0 ** -52 if dtype == "c128" else 2.0 ** -23
+    assert (many - ref).abs().max().item() <= 8 * (2 * n + 20) * eps * x.abs().max().item()

@@ -182,7 +182,7 @@ void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, in
             GateBlock b{};
             out.dfactor.push_back(g.carries_d ? g.factor : -1);
             if (g.diag_only) {
-                b.kind = kGateDiag;
+                b.what = kGateDiag;
                 out.blocks.push_back(b);
                 continue;
             }
@@ -192,10 +192,7 @@ void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, in
                 loc.push_back(pack_bits(v, tile));
                 piv |= top_bit(loc.back());
             }
-            b.rho = (int)loc.size();
-            b.form = g.form;
-            b.kmask = g.kmask;
-            b.nz = (int)g.type_bits.size();
+            const uint32_t rho = (uint32_t)loc.size(), nz = (uint32_t)g.type_bits.size();
             b.ztab = (int)out.words.size();
             for (int zb : g.type_bits) {
                 const uint64_t z = 1ull << zb, zl = pack_bits(z & tile, tile);
@@ -208,8 +205,11 @@ void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, in
             while (dst.size() % 4) dst.push_back(0.0);
             b.coef = (int)(dst.size() / (pairs ? 2 : 1));
             dst.insert(dst.end(), g.entries.begin(), g.entries.end());
-            if (b.rho > kGateMaxCoset || pairs) {
-                b.kind = kGateRows;
+            const bool rows = rho > (uint32_t)kGateMaxCoset || pairs;
+            out.general = out.general || rows || g.kmask != (1 << rho) - 1;
+            b.what = (rows ? kGateRows : kGateCosets) | rho << 4 | (uint32_t)g.form << 8 | nz << 12 |
+                     (uint32_t)g.kmask << 16;
+            if (rows) {
                 out.by_rows = true;
                 b.wtab = (int)out.words.size();
                 for (uint64_t v : loc) out.words.push_back((uint32_t)(63 - __builtin_clzll(v)));
@@ -218,22 +218,23 @@ void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, in
                 out.blocks.push_back(b);
                 continue;
             }
-            const int nt = popc64(types);
+            const uint32_t nt = (uint32_t)popc64(types);
             uint64_t holes = piv;
-            b.tshift = L.kt - b.rho;
-            b.lane = nt != 0;             // (type bits outside the tile are uniform)
-            if (nt && nt <= kGateMaxType && L.kt - b.rho - nt >= 6) {
-                b.lane = 0;
+            uint32_t ntype = 0, nhole = 0;
+            // 64 cosets per type: one type per wave (type bits outside the
+            // tile are one for the workgroup)
+            if (nt && nt <= (uint32_t)kGateMaxType && L.kt >= (int)(rho + nt) + 6) {
                 holes |= types;
-                b.ntype = nt;
-                b.tshift -= nt;
+                ntype = nt;
                 int k = 0;
                 for (uint64_t p = types; p; p &= p - 1) b.tpos |= (uint32_t)__builtin_ctzll(p) << (8 * k++);
             }
-            for (uint64_t p = holes; p; p &= p - 1) b.holes |= (uint64_t)__builtin_ctzll(p) << (8 * b.nhole++);
-            for (int c = 0; c < b.rho; ++c) {
+            for (uint64_t p = holes; p; p &= p - 1) b.holes |= (uint64_t)__builtin_ctzll(p) << (8 * nhole++);
+            b.number = nhole | ntype << 8 | ((uint32_t)L.kt - rho - ntype) << 16 | (nt && !ntype ? 1u << 24 : 0u) |
+                       (ntype && ntype == nz ? 1u << 28 : 0u);
+            for (uint32_t c = 0; c < rho; ++c) {
                 b.basis[c] = (uint32_t)loc[c];
-                b.rpiv[c] = 63 - __builtin_clzll(g.basis[c]);
+                b.rpivots |= (uint32_t)(63 - __builtin_clzll(g.basis[c])) << (8 * c);
             }
             out.blocks.push_back(b);
         }

@@ -57,21 +57,34 @@ enum GateKind { kGateCosets = 0, kGateDiag = 1, kGateRows = 2 };
 // per type they are the same for all lanes of a wave, whose matrix then comes
 // through scalar loads.  With fewer cosets ntype is 0, type bits are no
 // holes, and each lane loads its own matrix.
-struct GateBlock {
+struct alignas(64) GateBlock {     // one scalar load
     const void *diag;              // kGateDiag: N entries; forms with D: FP64 [2^rho][N >> rho],
                                    // element j of coset c (launch_phase_order)
     uint64_t holes;                // ascending local positions, one byte each
-    int32_t kind, rho, form, kmask;
-    int32_t nz, ztab;              // type bits: nz pairs (local bit, row bit outside the tile) in `words`
-    int32_t coef;                  // first entry: table[type][i][j], or [type][j][i] with D
-    int32_t wtab;                  // kGateRows: in `words`, rho local pivots, masks, row pivots
-    int32_t nhole, ntype;
-    int32_t lane, pad;             // lane: each lane loads its own matrix
-    int32_t tshift;                // log2(cosets) - ntype
     uint32_t tpos;                 // local position of type bit t: byte t
     uint32_t basis[kGateMaxCoset]; // reduced masks of the coset, in tile-local index space
-    int32_t rpiv[kGateMaxCoset];   // row bits of the pivots, ascending
+    int32_t coef;                  // first entry: table[type][i][j], or [type][j][i] with D
+    int32_t ztab;                  // in `words`, nz type bits: pairs (local bit, row bit outside the tile)
+    int32_t wtab;                  // kGateRows: in `words`, rho local pivots, masks, row pivots
+    uint32_t what;                 // kind, rho, form, nz: 4 bits each; kmask: 16
+    uint32_t number;               // nhole, ntype, tshift: 8 bits each; lane, direct: 4
+    uint32_t rpivots;              // row bits of the pivots, ascending, one byte each
+    uint32_t pad[2];
+
+    constexpr int kind() const { return (int)(what & 15); }
+    constexpr int rho() const { return (int)(what >> 4 & 15); }
+    constexpr int form() const { return (int)(what >> 8 & 15); }
+    constexpr int nz() const { return (int)(what >> 12 & 15); }
+    constexpr int kmask() const { return (int)(what >> 16); }
+    constexpr int nhole() const { return (int)(number & 255); }
+    constexpr int ntype() const { return (int)(number >> 8 & 255); }
+    constexpr int tshift() const { return (int)(number >> 16 & 255); }   // log2(cosets) - ntype
+    constexpr bool lane() const { return number >> 24 & 15; }            // each lane loads its own matrix
+    constexpr bool direct() const { return number >> 28; }               // the type is the coset number's top bits
+    constexpr int hole(int h) const { return (int)(holes >> (8 * h) & 63); }
+    constexpr int rpiv(int c) const { return (int)(rpivots >> (8 * c) & 31); }
 };
+static_assert(sizeof(GateBlock) == 64, "one scalar load");
 
 // dst bits of a segment: ((i >> sh) & mask) << dst
 struct GateSeg {
@@ -113,6 +126,7 @@ struct GateLaunch {
 
 struct GateProgram {
     bool by_rows = false;               // some block is of kind kGateRows
+    bool general = false;               // ... or some kmask lacks a bit
     std::vector<GateLaunch> launches;
     std::vector<GateBlock> blocks;      // diag filled at upload from dfactor
     std::vector<int> dfactor;           // factor whose D the block reads, or -1
@@ -143,7 +157,7 @@ struct GateRun {
     void *psi = nullptr;
     int64_t N = 0;
     int batch = 1;
-    bool by_rows = false;          // the program has kGateRows blocks
+    bool by_rows = false, general = false;   // as GateProgram's
     const void *stage_diag = nullptr;
     const double *nrm2 = nullptr;
     double *norm_out = nullptr;    // partials of state b, tile t at [(b * tiles + t) * 4]

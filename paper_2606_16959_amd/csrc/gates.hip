@@ -128,33 +128,58 @@ __device__ __forceinline__ void apply_real_d(const C2<R> (&x)[1 << RHO], const d
 
 constexpr int kGateThreads = 512;
 
-// One kGateCosets block of rank RHO on the tile in LDS.
-template <typename R, int RHO>
+// One kGateCosets block of rank RHO on the tile in LDS.  Spreading a coset's
+// number over the index bits, LDS positions and rows of D are all linear over
+// XOR, and a thread's cosets t, t + nt, ... differ in bits that t leaves 0: the
+// thread's part is computed once, the rest in scalar registers.
+// GENERAL: some kmask lacks a bit.
+template <typename R, int RHO, bool GENERAL>
 __device__ __forceinline__ void apply_cosets(const GateArgs &a, const GateBlock &B, C2<R> *lds, uint32_t base, int first,
                                              int nt) {
     constexpr int D = 1 << RHO;
     const int cosets = (1 << a.kt) >> RHO;
+    const int ntype = B.ntype(), tshift = B.tshift(), nhole = B.nhole(), kmask = B.kmask();
+    // the coset's first row: its number's bits around the holes
+    auto spread = [&](int cs) {
+        int rep = ntype ? cs & ((1 << tshift) - 1) : cs;
+        for (int h = 0; h < nhole; ++h) {
+            const int low = (1 << B.hole(h)) - 1;
+            rep = ((rep & ~low) << 1) | (rep & low);
+        }
+        for (int t = 0; t < ntype; ++t) rep |= ((cs >> (tshift + t)) & 1) << ((B.tpos >> (8 * t)) & 31);
+        return rep;
+    };
+    // the row's bits without the pivots (base's included)
+    auto squeeze = [&](uint32_t r) {
+#pragma unroll
+        for (int c = RHO - 1; c >= 0; --c) {
+            const int rp = B.rpiv(c);
+            r = ((r >> rp >> 1) << rp) | (r & ((1u << rp) - 1));
+        }
+        return r;
+    };
+    const bool with_d = B.form() != kGateReal, lane = B.lane();
     int step[RHO];
 #pragma unroll
     for (int q = 0; q < RHO; ++q) step[q] = lds_pos<R>((int)B.basis[q]);
+    const int rep_t = spread(first), pos_t = lds_pos<R>(rep_t);
+    const uint32_t row_t = with_d ? squeeze(base | seg_deposit(a.in, a.nin, (uint32_t)rep_t)) : 0;
+    if (first >= cosets) return;
 #pragma unroll 1
-    for (int cs = first; cs < cosets; cs += nt) {
-        // the coset's first row: its number's bits around the holes
-        int rep = B.ntype ? cs & ((1 << B.tshift) - 1) : cs;
-        for (int h = 0; h < B.nhole; ++h) {
-            const int low = (1 << ((int)(B.holes >> (8 * h)) & 63)) - 1;
-            rep = ((rep & ~low) << 1) | (rep & low);
-        }
-        for (int t = 0; t < B.ntype; ++t)
-            rep |= ((cs >> (B.tshift + t)) & 1) << ((B.tpos >> (8 * t)) & 31);
+    for (int c0 = 0; c0 < cosets; c0 += nt) {
+        const int rep_s = spread(c0), pos0 = pos_t ^ lds_pos<R>(rep_s);
         int type = 0;
-        for (int t = 0; t < B.nz; ++t)
-            type |= (int)(((rep & uload(a.words[B.ztab + 2 * t])) | (base & uload(a.words[B.ztab + 2 * t + 1]))) != 0)
-                    << t;
-        const bool lane = B.lane != 0;
-        if (!lane) type = __builtin_amdgcn_readfirstlane(type);
-        const int64_t k0 = B.coef + ((int64_t)type << (2 * RHO));
-        const int pos0 = lds_pos<R>(rep);
+        if (B.direct()) {
+            type = (first + c0) >> tshift;
+        } else {
+            const int rep = rep_t ^ rep_s;
+            for (int t = 0; t < B.nz(); ++t)
+                type |= (int)(((rep & uload(a.words[B.ztab + 2 * t])) | (base & uload(a.words[B.ztab + 2 * t + 1]))) != 0)
+                        << t;
+        }
+        // the matrix of the lane, and of the wave where it has but one
+        const int64_t kl = B.coef + ((int64_t)type << (2 * RHO));
+        const int64_t ku = B.coef + ((int64_t)__builtin_amdgcn_readfirstlane(type) << (2 * RHO));
         auto at = [&](int j) -> C2<R> & {
             int m = 0;
 #pragma unroll
@@ -164,26 +189,21 @@ __device__ __forceinline__ void apply_cosets(const GateArgs &a, const GateBlock 
         };
         C2<R> x[D];
         auto out = [&](int i, C2<R> y) { at(i) = y; };
-        if (B.form == kGateReal) {
-            const R *m = reinterpret_cast<const R *>(a.coef) + k0;
+        if (!with_d) {
+            const R *ml = reinterpret_cast<const R *>(a.coef) + kl, *mu = reinterpret_cast<const R *>(a.coef) + ku;
 #pragma unroll
             for (int j = 0; j < D; ++j) x[j] = at(j);
-            if (B.kmask == D - 1) {
-                if (lane) apply_real<R, RHO, true, true>(x, m, B.kmask, out);
-                else apply_real<R, RHO, true, false>(x, m, B.kmask, out);
+            if (!GENERAL || kmask == D - 1) {
+                if (lane) apply_real<R, RHO, true, true>(x, ml, kmask, out);
+                else apply_real<R, RHO, true, false>(x, mu, kmask, out);
             } else {
-                if (lane) apply_real<R, RHO, false, true>(x, m, B.kmask, out);
-                else apply_real<R, RHO, false, false>(x, m, B.kmask, out);
+                if (lane) apply_real<R, RHO, false, true>(x, ml, kmask, out);
+                else apply_real<R, RHO, false, false>(x, mu, kmask, out);
             }
         } else {
-            const double *m = a.coef64 + k0;
-            uint32_t r = base | seg_deposit(a.in, a.nin, (uint32_t)rep);
-#pragma unroll
-            for (int c = RHO - 1; c >= 0; --c) {
-                const int rp = B.rpiv[c];
-                r = ((r >> rp >> 1) << rp) | (r & ((1u << rp) - 1));
-            }
-            g_d2 *dp = (g_d2 *)B.diag + r;
+            const double *ml = a.coef64 + kl, *mu = a.coef64 + ku;
+            const uint32_t row_s = squeeze(seg_deposit(a.in, a.nin, (uint32_t)rep_s));
+            g_d2 *dp = (g_d2 *)B.diag + (row_t ^ row_s);
             const int64_t len = a.N >> RHO;
             // complex64 holds every D of the coset, loaded before the rows;
             // complex128 has no registers for that
@@ -198,12 +218,12 @@ __device__ __forceinline__ void apply_cosets(const GateArgs &a, const GateBlock 
             };
 #pragma unroll
             for (int j = 0; j < D; ++j) x[j] = at(j);
-            if (B.kmask == D - 1) {
-                if (lane) apply_real_d<R, RHO, true, true>(x, m, B.kmask, d, out);
-                else apply_real_d<R, RHO, true, false>(x, m, B.kmask, d, out);
+            if (!GENERAL || kmask == D - 1) {
+                if (lane) apply_real_d<R, RHO, true, true>(x, ml, kmask, d, out);
+                else apply_real_d<R, RHO, true, false>(x, mu, kmask, d, out);
             } else {
-                if (lane) apply_real_d<R, RHO, false, true>(x, m, B.kmask, d, out);
-                else apply_real_d<R, RHO, false, false>(x, m, B.kmask, d, out);
+                if (lane) apply_real_d<R, RHO, false, true>(x, ml, kmask, d, out);
+                else apply_real_d<R, RHO, false, false>(x, mu, kmask, d, out);
             }
         }
     }
@@ -216,7 +236,7 @@ __device__ __forceinline__ void apply_rows(const GateArgs &a, const GateBlock &B
                                            int nt) {
     const int T = 1 << a.kt;
     const uint32_t *w = a.words + B.wtab;
-    const int rho = B.rho, dim = 1 << rho;
+    const int rho = B.rho(), form = B.form(), kmask = B.kmask(), nz = B.nz(), dim = 1 << rho;
     g_d2 *dtab = (g_d2 *)B.diag;
     const C2<R> *mc = reinterpret_cast<const C2<R> *>(a.coef);
     const R *mr = reinterpret_cast<const R *>(a.coef);
@@ -229,7 +249,7 @@ __device__ __forceinline__ void apply_rows(const GateArgs &a, const GateBlock &B
                 e ^= (int)uload(w[rho + c]);
             }
         int64_t tab = 0;
-        for (int t = 0; t < B.nz; ++t)
+        for (int t = 0; t < nz; ++t)
             tab |= (int64_t)(((e & uload(a.words[B.ztab + 2 * t])) | (base & uload(a.words[B.ztab + 2 * t + 1]))) != 0)
                    << t;
         tab = B.coef + tab * dim * dim;
@@ -248,23 +268,23 @@ __device__ __forceinline__ void apply_rows(const GateArgs &a, const GateBlock &B
             for (int c = 0; c < rho; ++c)
                 if ((j >> c) & 1) at ^= (int)uload(w[rho + c]);
             const C2<R> x = lds[lds_pos<R>(at)];
-            if (B.form == kGateReal) {
-                const C2<R> xt = (__builtin_popcount(j & B.kmask) & 1) ? turn(x) : x;
+            if (form == kGateReal) {
+                const C2<R> xt = (__builtin_popcount(j & kmask) & 1) ? turn(x) : x;
                 const R k = mr[tab + (int64_t)own * dim + j];
                 y.re = rfma(k, xt.re, y.re);
                 y.im = rfma(k, xt.im, y.im);
-            } else if (B.form == kGateComplex) {
+            } else if (form == kGateComplex) {
                 cfma(y, mc[tab + (int64_t)own * dim + j], x);
             } else {
                 const d2v D = dtab[(int64_t)j * (a.N >> rho) + dc];
                 const int64_t k = tab + (int64_t)j * dim + own;
-                if (B.form == kGateRealD)
-                    cfma(y, d_entry_typed<R>(a.coef64[k], __builtin_popcount((own ^ j) & B.kmask) & 1, D), x);
+                if (form == kGateRealD)
+                    cfma(y, d_entry_typed<R>(a.coef64[k], __builtin_popcount((own ^ j) & kmask) & 1, D), x);
                 else
                     cfma(y, d_entry<R>(a.coef64[2 * k], a.coef64[2 * k + 1], D), x);
             }
         }
-        if (B.form == kGateReal && (__builtin_popcount(own & B.kmask) & 1)) y = unturn(y);
+        if (form == kGateReal && (__builtin_popcount(own & kmask) & 1)) y = unturn(y);
         lds[T + i] = y;
     }
     __syncthreads();
@@ -276,28 +296,22 @@ __device__ __forceinline__ GateBlock uload_block(const GateBlock &p) {
     GateBlock r;
     r.diag = uload(p.diag);
     r.holes = uload(p.holes);
-    r.kind = uload(p.kind);
-    r.rho = uload(p.rho);
-    r.form = uload(p.form);
-    r.kmask = uload(p.kmask);
-    r.nz = uload(p.nz);
-    r.ztab = uload(p.ztab);
-    r.coef = uload(p.coef);
-    r.wtab = uload(p.wtab);
-    r.nhole = uload(p.nhole);
-    r.ntype = uload(p.ntype);
-    r.lane = uload(p.lane);
-    r.tshift = uload(p.tshift);
     r.tpos = uload(p.tpos);
 #pragma unroll
-    for (int c = 0; c < kGateMaxCoset; ++c) {
-        r.basis[c] = uload(p.basis[c]);
-        r.rpiv[c] = uload(p.rpiv[c]);
-    }
+    for (int c = 0; c < kGateMaxCoset; ++c) r.basis[c] = uload(p.basis[c]);
+    r.coef = uload(p.coef);
+    r.ztab = uload(p.ztab);
+    r.wtab = uload(p.wtab);
+    r.what = uload(p.what);
+    r.number = uload(p.number);
+    r.rpivots = uload(p.rpivots);
     return r;
 }
 
-template <typename R, bool STREAM>
+// GENERAL: the program has kGateRows blocks or products whose entries are not
+// imaginary for every single flip; without them (transverse fields, XX + YY
+// bonds: most programs) the kernel is a third of the code.
+template <typename R, bool STREAM, bool GENERAL>
 __global__ __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(4))) void gate_kernel(GateArgs a) {
     constexpr bool PAIR = sizeof(R) == 4;           // linear phases: two adjacent rows per 16-byte access
     constexpr int H = PAIR ? 2 : 1;
@@ -321,12 +335,10 @@ __global__ __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(4)
             tile = g / a.batch;
         }
     };
-    // Linear phases: access p of thread t covers local row(s) first(t, p) (and
-    // + 1 for complex64); the row of a local index is a bit deposit, so it
-    // splits over the bits of the thread and of the access.
-    auto first_of = [&](int t, int p) { return H * (t + p * nt); };
-    auto row_part = [&](uint32_t base, int t) { return base | seg_deposit(a.in, a.nin, (uint32_t)first_of(t, 0)); };
-    auto row_at = [&](uint32_t part, int p) { return (int)(part | seg_deposit(a.in, a.nin, (uint32_t)(H * p * nt))); };
+    // Linear phases: access p of thread t covers local row(s) H (t + p nt) (and
+    // + 1 for complex64).  Rows and LDS positions are linear over the bits of
+    // the thread and of the access, as in apply_cosets.
+    auto row_part = [&](int p) { return seg_deposit(a.in, a.nin, (uint32_t)(H * p * nt)); };       // scalar
     // The thread's number, opaque to the compiler: each phase computes its
     // rows and LDS positions afresh instead of holding them in registers
     // through the blocks.
@@ -335,43 +347,36 @@ __global__ __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(4)
         asm volatile("" : "+v"(t));
         return t;
     };
-    C2<R> u[G][H];
-    auto load_tile = [&](int g) {
-        int tile, b;
-        place(g, tile, b);
-        const uint32_t base = seg_deposit(a.out, a.nout, (uint32_t)tile);
-        const C2<R> *psi = reinterpret_cast<const C2<R> *>(a.psi) + (int64_t)b * a.N;
-        const int t = fresh();
-        const uint32_t part = row_part(base, t);
-#pragma unroll
-        for (int p = 0; p < G; ++p) {
-            const int r = first_of(t, p) < T ? row_at(part, p) : (int)base;
-            if constexpr (PAIR) ld2(psi, r, u[p][0], u[p][1]);
-            else u[p][0] = ld1(psi, r);
-        }
-    };
-    const int g = blockIdx.x;
-    load_tile(g);
+    int tile, b;
+    place(blockIdx.x, tile, b);
+    const uint32_t base = seg_deposit(a.out, a.nout, (uint32_t)tile);
+    C2<R> *psi = reinterpret_cast<C2<R> *>(a.psi) + (int64_t)b * a.N + base;
     {
-        int tile, b;
-        place(g, tile, b);
-        const uint32_t base = seg_deposit(a.out, a.nout, (uint32_t)tile);
-        {
+        C2<R> u[G][H];
+        const int t = fresh();
+        const uint32_t row_t = seg_deposit(a.in, a.nin, (uint32_t)(H * t));
+        const C2<R> *src = psi + row_t;
+#pragma unroll
+        for (int p = 0; p < G; ++p)
+            if (H * p * nt < T) {
+                if constexpr (PAIR) ld2(src + row_part(p), 0, u[p][0], u[p][1]);
+                else u[p][0] = ld1(src + row_part(p), 0);
+            }
+        if (a.nrm2) {
             const R scale = inv_norm<R>(a.nrm2, b);
-            const int t = fresh();
 #pragma unroll
             for (int p = 0; p < G; ++p)
 #pragma unroll
                 for (int h = 0; h < H; ++h) u[p][h] = cscale(u[p][h], scale);
-            if (a.stage_diag) {
-                const C2<R> *dg = reinterpret_cast<const C2<R> *>(a.stage_diag);
-                const uint32_t part = row_part(base, t);
+        }
+        if (a.stage_diag) {
+            const C2<R> *dg = reinterpret_cast<const C2<R> *>(a.stage_diag) + base + row_t;
 #pragma unroll
-                for (int p = 0; p < G; ++p) {
-                    const int r = first_of(t, p) < T ? row_at(part, p) : (int)base;
+            for (int p = 0; p < G; ++p)
+                if (H * p * nt < T) {
                     C2<R> k[2];
-                    if constexpr (PAIR) ld2_cached(dg, r, k[0], k[1]);
-                    else k[0] = ld1_cached(dg, r);
+                    if constexpr (PAIR) ld2_cached(dg + row_part(p), 0, k[0], k[1]);
+                    else k[0] = ld1_cached(dg + row_part(p), 0);
 #pragma unroll
                     for (int h = 0; h < H; ++h) {
                         C2<R> y{(R)0, (R)0};
@@ -379,24 +384,28 @@ __global__ __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(4)
                         u[p][h] = y;
                     }
                 }
-            }
+        }
+        const int pos_t = lds_pos<R>(H * t);
+        if (H * t < T)
 #pragma unroll
             for (int p = 0; p < G; ++p)
+                if (H * p * nt < T)
 #pragma unroll
-                for (int h = 0; h < H; ++h)
-                    if (first_of(t, p) < T) lds[lds_pos<R>(first_of(t, p) + h)] = u[p][h];
-        }
+                    for (int h = 0; h < H; ++h) lds[pos_t ^ lds_pos<R>(H * p * nt + h)] = u[p][h];
+    }
+
+    {
         for (int s = 0; s < a.steps; ++s) {
             const int part = a.steps == 1 ? 0 : s == 0 ? 1 : s == a.steps - 1 ? 3 : 2;
             const int k1 = a.part[part + 1];
             for (int k = a.part[part]; k < k1; ++k) {
                 const GateBlock B = uload_block(a.blocks[k]);
                 __syncthreads();
-                if (B.kind == kGateCosets) {
-                    if (B.rho == 3) apply_cosets<R, 3>(a, B, lds, base, fresh(), nt);
-                    else if (B.rho == 2) apply_cosets<R, 2>(a, B, lds, base, fresh(), nt);
-                    else apply_cosets<R, 1>(a, B, lds, base, fresh(), nt);
-                } else if (B.kind == kGateDiag) {
+                if (B.kind() == kGateCosets) {
+                    if (B.rho() == 3) apply_cosets<R, 3, GENERAL>(a, B, lds, base, fresh(), nt);
+                    else if (B.rho() == 2) apply_cosets<R, 2, GENERAL>(a, B, lds, base, fresh(), nt);
+                    else apply_cosets<R, 1, GENERAL>(a, B, lds, base, fresh(), nt);
+                } else if (B.kind() == kGateDiag) {
                     const C2<R> *dg = reinterpret_cast<const C2<R> *>(B.diag);
 #pragma unroll 1
                     for (int i = H * fresh(); i < T; i += H * nt) {
@@ -411,7 +420,7 @@ __global__ __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(4)
                             lds[lds_pos<R>(i + h)] = y;
                         }
                     }
-                } else {
+                } else if constexpr (GENERAL) {
                     apply_rows<R>(a, B, lds, base, fresh(), nt);
                 }
             }
@@ -419,23 +428,26 @@ __global__ __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(4)
         __syncthreads();
 
         {
-            C2<R> *psi = reinterpret_cast<C2<R> *>(a.psi) + (int64_t)b * a.N;
             const int t = fresh();
-            const uint32_t part = row_part(base, t);
+            C2<R> *dst = psi + seg_deposit(a.in, a.nin, (uint32_t)(H * t));
+            const int pos_t = lds_pos<R>(H * t);
             double ss = 0.0;
+            if (H * t < T)
 #pragma unroll
-            for (int p = 0; p < G; ++p)
-                if (first_of(t, p) < T) {
-                    C2<R> y[2];
+                for (int p = 0; p < G; ++p)
+                    if (H * p * nt < T) {
+                        C2<R> y[2];
 #pragma unroll
-                    for (int h = 0; h < H; ++h) {
-                        y[h] = lds[lds_pos<R>(first_of(t, p) + h)];
-                        const double re = (double)y[h].re, im = (double)y[h].im;
-                        if (a.norm_out) ss += re * re + im * im;
+                        for (int h = 0; h < H; ++h) y[h] = lds[pos_t ^ lds_pos<R>(H * p * nt + h)];
+                        if (a.norm_out)
+#pragma unroll
+                            for (int h = 0; h < H; ++h) {
+                                const double re = (double)y[h].re, im = (double)y[h].im;
+                                ss += re * re + im * im;
+                            }
+                        if constexpr (PAIR) st2<STREAM>(dst + row_part(p), 0, y[0], y[1]);
+                        else st1<STREAM>(dst + row_part(p), 0, y[0]);
                     }
-                    if constexpr (PAIR) st2<STREAM>(psi, row_at(part, p), y[0], y[1]);
-                    else st1<STREAM>(psi, row_at(part, p), y[0]);
-                }
             if (a.norm_out) {
                 // FP64 sum of |y|^2 over the tile's rows in a fixed order:
                 // rows per thread, a wave butterfly, then the waves in order
@@ -465,15 +477,15 @@ static std::mutex &gate_attr_mutex() {
     return m;
 }
 
-template <typename R, bool STREAM>
+template <typename R, bool STREAM, bool GENERAL>
 static int gate_launch(const GateArgs &a, void *stream) {
-    auto kern = gate_kernel<R, STREAM>;
+    auto kern = gate_kernel<R, STREAM, GENERAL>;
     const int T = 1 << a.kt;
     const size_t tile = (size_t)T * sizeof(C2<R>) * (a.by_rows ? 2 : 1), lds = tile < 256 ? 256 : tile;
-    // every linear row has a thread (8 accesses of 16 bytes each); a small
-    // tile gets up to two rows per thread
+    // every linear row has a thread (8 accesses of 16 bytes each); launches of
+    // few tiles get up to one thread per two rows
     constexpr int RPT = 8 * 16 / (int)sizeof(C2<R>);
-    int nt = T / 2;
+    int nt = a.total < 1024 ? T / 2 : T / RPT;
     if (nt < 64) nt = 64;
     if (nt > kGateThreads) nt = kGateThreads;
     if (nt * RPT < T) return (int)hipErrorInvalidValue;
@@ -562,8 +574,13 @@ int launch_gates(const GateLaunch &L, const GateTables &t, const GateRun &r, boo
     a.by_rows = r.by_rows;
     a.steps = r.steps;
     for (int q = 0; q < 5; ++q) a.part[q] = r.part[q];
-    if (c128) return stream_out ? gate_launch<double, true>(a, stream) : gate_launch<double, false>(a, stream);
-    return stream_out ? gate_launch<float, true>(a, stream) : gate_launch<float, false>(a, stream);
+    if (r.general) {
+        if (c128) return stream_out ? gate_launch<double, true, true>(a, stream) : gate_launch<double, false, true>(a, stream);
+        return stream_out ? gate_launch<float, true, true>(a, stream) : gate_launch<float, false, true>(a, stream);
+    }
+    if (r.by_rows) return (int)hipErrorInvalidValue;
+    if (c128) return stream_out ? gate_launch<double, true, false>(a, stream) : gate_launch<double, false, false>(a, stream);
+    return stream_out ? gate_launch<float, true, false>(a, stream) : gate_launch<float, false, false>(a, stream);
 }
 
 }  // namespace hs

@@ -50,10 +50,10 @@ static int pop(uint64_t v) { return __builtin_popcountll(v) & 1; }
 
 // entry M[i][j] of an operation, as the kernel reads its table (D excluded)
 static cd entry(const hs::GateProgram &G, const hs::GateBlock &op, int64_t type, int i, int j) {
-    const int R = 1 << op.rho;
-    const int ki = pop(i & op.kmask), kj = pop(j & op.kmask);
+    const int R = 1 << op.rho();
+    const int ki = pop(i & op.kmask()), kj = pop(j & op.kmask());
     const int64_t tab = op.coef + type * R * R;
-    switch (op.form) {
+    switch (op.form()) {
         case hs::kGateReal: {          // M = i^(kappa_j - kappa_i) M'
             const double m = G.coef[tab + i * R + j];
             return ki == kj ? cd(m, 0) : (ki ? cd(0, -m) : cd(0, m));
@@ -84,48 +84,49 @@ static int walk(const hs::Plan &P, const hs::GateProgram &G, const hs::GateLaunc
         }
         for (int k = L.block0; k < L.block1; ++k) {
             const hs::GateBlock &B = G.blocks[k];
-            const int df = G.dfactor[k], R = 1 << B.rho;
-            if (B.kind == hs::kGateDiag) {
+            const int df = G.dfactor[k], R = 1 << B.rho();
+            if (B.kind() == hs::kGateDiag) {
                 for (int i = 0; i < T; ++i) lds[i] *= diag(df, base | deposit(L.in, i));
                 continue;
             }
-            const bool rows = B.kind == hs::kGateRows;
-            if (!rows && (B.rho > hs::kGateMaxCoset || B.form == hs::kGateComplex || B.form == hs::kGateComplexD)) return 5;
+            const bool rows = B.kind() == hs::kGateRows;
+            if (!rows && (B.rho() > hs::kGateMaxCoset || B.form() == hs::kGateComplex || B.form() == hs::kGateComplexD)) return 5;
             const uint32_t *w = rows ? &G.words[B.wtab] : nullptr;
             std::vector<char> hit(T, 0);
             int64_t wave_type = 0;
-            for (int t = 0; t < (T >> B.rho); ++t) {
+            for (int t = 0; t < (T >> B.rho()); ++t) {
                 int rep = t;
                 if (rows) {                            // the t-th row with its pivot bits 0
-                    for (int c = 0; c < B.rho; ++c) {
+                    for (int c = 0; c < B.rho(); ++c) {
                         const int low = (1 << w[c]) - 1;
                         rep = ((rep & ~low) << 1) | (rep & low);
                     }
                 } else {
-                    if (B.nhole != B.rho + B.ntype || B.tshift != L.kt - B.rho - B.ntype) return 3;
-                    rep = B.ntype ? t & ((1 << B.tshift) - 1) : t;
-                    for (int h = 0; h < B.nhole; ++h) {
-                        const int low = (1 << ((B.holes >> (8 * h)) & 63)) - 1;
+                    if (B.nhole() != B.rho() + B.ntype() || B.tshift() != L.kt - B.rho() - B.ntype()) return 3;
+                    rep = B.ntype() ? t & ((1 << B.tshift()) - 1) : t;
+                    for (int h = 0; h < B.nhole(); ++h) {
+                        const int low = (1 << B.hole(h)) - 1;
                         rep = ((rep & ~low) << 1) | (rep & low);
                     }
-                    for (int q = 0; q < B.ntype; ++q)
-                        rep |= ((t >> (B.tshift + q)) & 1) << ((B.tpos >> (8 * q)) & 31);
+                    for (int q = 0; q < B.ntype(); ++q)
+                        rep |= ((t >> (B.tshift() + q)) & 1) << ((B.tpos >> (8 * q)) & 31);
                 }
                 int64_t type = 0;
-                for (int z = 0; z < B.nz; ++z)
+                for (int z = 0; z < B.nz(); ++z)
                     type |= (int64_t)(((rep & G.words[B.ztab + 2 * z]) | (base & G.words[B.ztab + 2 * z + 1])) != 0) << z;
+                if (!rows && B.direct() && type != (t >> B.tshift())) return 12;
                 if ((t & 63) == 0) wave_type = type;
-                if (!rows && !B.lane && type != wave_type) return 11;    // one matrix per wave
+                if (!rows && !B.lane() && type != wave_type) return 11;    // one matrix per wave
                 std::vector<cd> y(R, 0.0);
                 std::vector<int> at(R);
                 for (int j = 0; j < R; ++j) {
                     at[j] = rep;
-                    for (int q = 0; q < B.rho; ++q)
-                        if ((j >> q) & 1) at[j] ^= (int)(rows ? w[B.rho + q] : B.basis[q]);
+                    for (int q = 0; q < B.rho(); ++q)
+                        if ((j >> q) & 1) at[j] ^= (int)(rows ? w[B.rho() + q] : B.basis[q]);
                     if (at[j] < 0 || at[j] >= T || hit[at[j]]++ || (j && at[j] <= at[j - 1])) return 4;
                     const int64_t row = base | deposit(L.in, at[j]);
                     int own = 0;                       // a row's coordinate is its pivot bits
-                    for (int c = 0; c < B.rho; ++c) own |= (int)((row >> (rows ? w[2 * B.rho + c] : B.rpiv[c])) & 1) << c;
+                    for (int c = 0; c < B.rho(); ++c) own |= (int)((row >> (rows ? w[2 * B.rho() + c] : B.rpiv(c))) & 1) << c;
                     if (own != j) return 7;
                     cd x = lds[at[j]];
                     if (df >= 0) x *= diag(df, row);

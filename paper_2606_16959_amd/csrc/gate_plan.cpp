@@ -226,11 +226,15 @@ void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, in
             if (nt && nt <= (uint32_t)kGateMaxType && L.kt >= (int)(rho + nt) + 6) {
                 holes |= types;
                 ntype = nt;
+            }
+            const bool inside = nt == nz && nz <= 4;
+            if (nt <= 4) {
                 int k = 0;
                 for (uint64_t p = types; p; p &= p - 1) b.tpos |= (uint32_t)__builtin_ctzll(p) << (8 * k++);
             }
             for (uint64_t p = holes; p; p &= p - 1) b.holes |= (uint64_t)__builtin_ctzll(p) << (8 * nhole++);
             b.number = nhole | ntype << 8 | ((uint32_t)L.kt - rho - ntype) << 16 | (nt && !ntype ? 1u << 24 : 0u) |
+                       (inside ? 1u << 25 : 0u) |
                        (ntype && ntype == nz ? 1u << 28 : 0u);
             for (uint32_t c = 0; c < rho; ++c) {
                 b.basis[c] = (uint32_t)loc[c];

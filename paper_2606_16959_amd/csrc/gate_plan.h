@@ -67,7 +67,7 @@ struct alignas(64) GateBlock {     // one scalar load
     int32_t ztab;                  // in `words`, nz type bits: pairs (local bit, row bit outside the tile)
     int32_t wtab;                  // kGateRows: in `words`, rho local pivots, masks, row pivots
     uint32_t what;                 // kind, rho, form, nz: 4 bits each; kmask: 16
-    uint32_t number;               // nhole, ntype, tshift: 8 bits each; lane, direct: 4
+    uint32_t number;               // nhole, ntype, tshift: 8 bits each; lane, inside, direct: flags
     uint32_t rpivots;              // row bits of the pivots, ascending, one byte each
     uint32_t pad[2];
 
@@ -79,7 +79,8 @@ struct alignas(64) GateBlock {     // one scalar load
     constexpr int nhole() const { return (int)(number & 255); }
     constexpr int ntype() const { return (int)(number >> 8 & 255); }
     constexpr int tshift() const { return (int)(number >> 16 & 255); }   // log2(cosets) - ntype
-    constexpr bool lane() const { return number >> 24 & 15; }            // each lane loads its own matrix
+    constexpr bool lane() const { return number >> 24 & 1; }             // each lane loads its own matrix
+    constexpr bool inside() const { return number >> 25 & 1; }           // every type bit is in the tile, at tpos
     constexpr bool direct() const { return number >> 28; }               // the type is the coset number's top bits
     constexpr int hole(int h) const { return (int)(holes >> (8 * h) & 63); }
     constexpr int rpiv(int c) const { return (int)(rpivots >> (8 * c) & 31); }

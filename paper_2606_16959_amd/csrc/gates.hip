@@ -30,9 +30,10 @@ struct GateArgs {
     int64_t N;                     // rows of a state, and elements between states
     int32_t batch;
     int32_t kt;                    // log2 of the tile's rows
-    int32_t tiles, total;          // tiles of a state, and of all states
+    int32_t tiles;                 // of a state
     int32_t nin, nout;
-    GateSeg in[kGateSegs], out[kGateSegs];
+    GateSeg in[kGateSegs], out[kGateSegs];     // the rest zero: deposits nothing
+    uint32_t access_row[8];        // row bits of the linear phases' access p (local rows H p nt)
     const GateBlock *blocks;
     const uint32_t *words;
     const void *coef;
@@ -52,7 +53,9 @@ __device__ __forceinline__ constexpr int lds_pos(int i) {
 
 __device__ __forceinline__ uint32_t seg_deposit(const GateSeg *s, int n, uint32_t i) {
     uint32_t r = 0;
-    for (int k = 0; k < n; ++k) r |= ((i >> s[k].sh) & s[k].mask) << s[k].dst;
+    for (int k = 0; k < n; k += 2)              // two segments per round of scalar loads
+#pragma unroll
+        for (int u = 0; u < 2; ++u) r |= ((i >> s[k + u].sh) & s[k + u].mask) << s[k + u].dst;
     return r;
 }
 
@@ -171,6 +174,9 @@ __device__ __forceinline__ void apply_cosets(const GateArgs &a, const GateBlock 
         int type = 0;
         if (B.direct()) {
             type = (first + c0) >> tshift;
+        } else if (B.inside()) {
+            const int rep = rep_t ^ rep_s;
+            for (int t = 0; t < B.nz(); ++t) type |= ((rep >> (B.tpos >> (8 * t) & 31)) & 1) << t;
         } else {
             const int rep = rep_t ^ rep_s;
             for (int t = 0; t < B.nz(); ++t)
@@ -322,23 +328,14 @@ __global__ __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(4)
     const int nt = blockDim.x;
     const int T = 1 << a.kt;
 
-    // Tile and state of number g: workgroups are dealt to the 8 XCDs
+    // Workgroups (8 tiles, states, eighths) are dealt to the 8 XCDs
     // round-robin, so the states of one tile follow 8 apart on one XCD and
     // find its D in that XCD's L2.
-    auto place = [&](int g, int &tile, int &b) {
-        if ((a.tiles & 7) == 0) {
-            const int q = g >> 3;
-            b = q % a.batch;
-            tile = (q / a.batch) * 8 + (g & 7);
-        } else {
-            b = g % a.batch;
-            tile = g / a.batch;
-        }
-    };
+    const int tile = (int)(blockIdx.z * gridDim.x + blockIdx.x), b = (int)blockIdx.y;
     // Linear phases: access p of thread t covers local row(s) H (t + p nt) (and
     // + 1 for complex64).  Rows and LDS positions are linear over the bits of
     // the thread and of the access, as in apply_cosets.
-    auto row_part = [&](int p) { return seg_deposit(a.in, a.nin, (uint32_t)(H * p * nt)); };       // scalar
+    auto row_part = [&](int p) { return a.access_row[p]; };
     // The thread's number, opaque to the compiler: each phase computes its
     // rows and LDS positions afresh instead of holding them in registers
     // through the blocks.
@@ -347,8 +344,6 @@ __global__ __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(4)
         asm volatile("" : "+v"(t));
         return t;
     };
-    int tile, b;
-    place(blockIdx.x, tile, b);
     const uint32_t base = seg_deposit(a.out, a.nout, (uint32_t)tile);
     C2<R> *psi = reinterpret_cast<C2<R> *>(a.psi) + (int64_t)b * a.N + base;
     {
@@ -478,14 +473,14 @@ static std::mutex &gate_attr_mutex() {
 }
 
 template <typename R, bool STREAM, bool GENERAL>
-static int gate_launch(const GateArgs &a, void *stream) {
+static int gate_launch(GateArgs &a, void *stream) {
     auto kern = gate_kernel<R, STREAM, GENERAL>;
     const int T = 1 << a.kt;
     const size_t tile = (size_t)T * sizeof(C2<R>) * (a.by_rows ? 2 : 1), lds = tile < 256 ? 256 : tile;
     // every linear row has a thread (8 accesses of 16 bytes each); launches of
     // few tiles get up to one thread per two rows
     constexpr int RPT = 8 * 16 / (int)sizeof(C2<R>);
-    int nt = a.total < 1024 ? T / 2 : T / RPT;
+    int nt = (int64_t)a.tiles * a.batch < 1024 ? T / 2 : T / RPT;
     if (nt < 64) nt = 64;
     if (nt > kGateThreads) nt = kGateThreads;
     if (nt * RPT < T) return (int)hipErrorInvalidValue;
@@ -501,7 +496,17 @@ static int gate_launch(const GateArgs &a, void *stream) {
             }
         }
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)a.total), dim3(nt), lds, reinterpret_cast<hipStream_t>(stream), a);
+    constexpr int H = sizeof(R) == 4 ? 2 : 1;
+    for (int p = 0; p < 8; ++p) {
+        const uint32_t i = (uint32_t)(H * p * nt);
+        a.access_row[p] = 0;
+        if (i < (uint32_t)T)
+            for (int k = 0; k < a.nin; ++k) a.access_row[p] |= ((i >> a.in[k].sh) & a.in[k].mask) << a.in[k].dst;
+    }
+    unsigned gx = a.tiles < 8 ? a.tiles : 8;
+    while ((unsigned)a.tiles / gx > 32768) gx *= 2;
+    hipLaunchKernelGGL(kern, dim3(gx, (unsigned)a.batch, (unsigned)a.tiles / gx), dim3(nt), lds,
+                       reinterpret_cast<hipStream_t>(stream), a);
     return (int)hipGetLastError();
 }
 
@@ -552,14 +557,13 @@ int launch_gates(const GateLaunch &L, const GateTables &t, const GateRun &r, boo
     if (L.in.size() > (size_t)kGateSegs || L.out.size() > (size_t)kGateSegs) return (int)hipErrorInvalidValue;
     // row pairs of the linear phases are adjacent in the state
     if (!(L.tile & 1) || L.kt < 1 || L.rows != (int64_t(1) << L.kt)) return (int)hipErrorInvalidValue;
-    const int64_t tiles = r.N / L.rows, total = tiles * r.batch;
-    if (tiles < 1 || total > (int64_t(1) << 30) || (r.steps > 1 && tiles != 1)) return (int)hipErrorInvalidValue;
+    const int64_t tiles = r.N / L.rows;            // a power of two
+    if (tiles < 1 || tiles > (1 << 24) || r.batch > 65535 || (r.steps > 1 && tiles != 1)) return (int)hipErrorInvalidValue;
     a.psi = r.psi;
     a.N = r.N;
     a.batch = r.batch;
     a.kt = L.kt;
     a.tiles = (int32_t)tiles;
-    a.total = (int32_t)total;
     a.nin = (int32_t)L.in.size();
     a.nout = (int32_t)L.out.size();
     for (int k = 0; k < a.nin; ++k) a.in[k] = L.in[k];

@@ -115,6 +115,11 @@ static int walk(const hs::Plan &P, const hs::GateProgram &G, const hs::GateLaunc
                 for (int z = 0; z < B.nz(); ++z)
                     type |= (int64_t)(((rep & G.words[B.ztab + 2 * z]) | (base & G.words[B.ztab + 2 * z + 1])) != 0) << z;
                 if (!rows && B.direct() && type != (t >> B.tshift())) return 12;
+                if (!rows && B.inside()) {
+                    int64_t at_pos = 0;
+                    for (int z = 0; z < B.nz(); ++z) at_pos |= (int64_t)((rep >> (B.tpos >> (8 * z) & 31)) & 1) << z;
+                    if (at_pos != type) return 13;
+                }
                 if ((t & 63) == 0) wave_type = type;
                 if (!rows && !B.lane() && type != wave_type) return 11;    // one matrix per wave
                 std::vector<cd> y(R, 0.0);

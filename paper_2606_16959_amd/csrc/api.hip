@@ -126,6 +126,7 @@ struct GatePlan {
     int launch0[kParts + 1] = {0, 0, 0, 0, 0};   // part q makes launches [launch0[q], launch0[q + 1])
     std::vector<hs::GateBlock> blocks;           // prog.blocks with their diagonals' addresses
     std::vector<float> coef32;
+    std::vector<char> host;                      // the tables as uploaded; alive as long as the plan
     void *dev = nullptr;
     hs::GateTables tab;
 };
@@ -150,7 +151,7 @@ struct hs_factors_s {
     // own diagonal, or one of diag_own), else FP64 entries in the order the
     // factor's coset product reads them
     std::vector<const void *> diag_of;
-    std::vector<void *> diag_own;
+    std::vector<void *> owned;       // device allocations of the build
 
     double *partials() { return work_dev; }
     double *records() { return work_dev + (size_t)HS_MAX_BATCH * hs::kReduceBlocks * 4; }
@@ -158,15 +159,11 @@ struct hs_factors_s {
     // Stream-ordered frees (hipFree would wait for the whole device, stalling
     // other handles' work on other streams).
     ~hs_factors_s() {
-        for (auto &f : plan.factors)
-            if (f.dev) (void)hipFreeAsync(f.dev, alloc_stream);
-        for (void *p : diag_own) (void)hipFreeAsync(p, alloc_stream);
+        for (void *p : owned) (void)hipFreeAsync(p, alloc_stream);
         for (auto &kv : plans)
             if (kv.second->dev) (void)hipFreeAsync(kv.second->dev, alloc_stream);
         if (whole && whole->dev) (void)hipFreeAsync(whole->dev, alloc_stream);
-        if (viol_dev) (void)hipFreeAsync(viol_dev, alloc_stream);
         if (norm_dev) (void)hipFreeAsync(norm_dev, alloc_stream);
-        if (work_dev) (void)hipFreeAsync(work_dev, alloc_stream);
     }
 };
 
@@ -291,8 +288,8 @@ int gate_tile_bits(int dtype, int64_t N, int batch) {
     return kt;
 }
 
-// Uploads a program's tables; the host copies live as long as the plan, so
-// the ordered copies are safe.
+// Uploads a program's tables in one copy; the host copy lives as long as the
+// plan, so the ordered copy is safe.
 hs_status upload_gates(hs_factors_s *h, GatePlan &gp, hipStream_t st) {
     const hs::GateProgram &p = gp.prog;
     gp.blocks = p.blocks;
@@ -309,17 +306,16 @@ hs_status upload_gates(hs_factors_s *h, GatePlan &gp, hipStream_t st) {
                      {c128 ? (const void *)p.coef.data() : (const void *)gp.coef32.data(),
                       p.coef.size() * (c128 ? 8 : 4)},
                      {p.coef64.data(), p.coef64.size() * 8}};
-    size_t off[kTabs], total = 0;
+    size_t off[kTabs];
+    gp.host.clear();
     for (int k = 0; k < kTabs; ++k) {
-        off[k] = total;
-        total += (part[k].bytes + 255) / 256 * 256;
+        off[k] = gp.host.size();
+        gp.host.resize(off[k] + (part[k].bytes + 255) / 256 * 256);
+        if (part[k].bytes) std::memcpy(gp.host.data() + off[k], part[k].src, part[k].bytes);
     }
-    HS_HIP(hipMallocAsync(&gp.dev, std::max<size_t>(total, 256), st), "hipMallocAsync(coset tables)");
+    HS_HIP(hipMallocAsync(&gp.dev, gp.host.size(), st), "hipMallocAsync(coset tables)");
     char *base = static_cast<char *>(gp.dev);
-    for (int k = 0; k < kTabs; ++k)
-        if (part[k].bytes)
-            HS_HIP(hipMemcpyAsync(base + off[k], part[k].src, part[k].bytes, hipMemcpyHostToDevice, st),
-                   "coset tables");
+    HS_HIP(hipMemcpyAsync(base, gp.host.data(), gp.host.size(), hipMemcpyHostToDevice, st), "coset tables");
     gp.tab.blocks = reinterpret_cast<const hs::GateBlock *>(base + off[0]);
     gp.tab.words = reinterpret_cast<const uint32_t *>(base + off[1]);
     gp.tab.coef = base + off[2];
@@ -365,10 +361,12 @@ hs_status make_gate_plan(hs_factors_s *h, const PlanKey &key, bool loop, std::un
 
 // Rows up to which hs_evolve runs a whole evolution in one launch
 // (HAMSIM_WHOLE_MAX_ROWS, capped by the tile one workgroup holds; 0 never).
+// The default is where one workgroup per state stops beating a launch per run
+// and step: n = 12 11.8 against 13.5 us a step (complex128 13.1 against 14.4),
+// n = 13 18.5 against 14.1 us.
 int64_t whole_max_rows(int dtype) {
     const int lim = dtype == HS_C128 ? hs::kWholeRowsC128 : hs::kWholeRowsC64;
-    const int dflt = dtype == HS_C128 ? 1024 : 2048;
-    return env_int("HAMSIM_WHOLE_MAX_ROWS", dflt, 0, lim);
+    return env_int("HAMSIM_WHOLE_MAX_ROWS", 4096, 0, lim);
 }
 
 hs_status check_handle(hs_factors f) {
@@ -402,6 +400,9 @@ hs_status hs_plan(int n_qubits, int n_terms, const char *const *pauli_terms, con
     return HS_OK;
 }
 
+// Handles up to this size live in one allocation.
+constexpr size_t kOneAllocation = size_t(256) << 20;
+
 static hs_status build_device(hs_factors_s *h, void *stream) {
     Plan &P = h->plan;
     const size_t sc = elem_bytes(h->dtype);
@@ -410,47 +411,88 @@ static hs_status build_device(hs_factors_s *h, void *stream) {
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     h->alloc_stream = st;
     choose_storage_order(P, h->dtype);
-    for (auto &f : P.factors) {
+    // Device memory.  A small handle is one allocation (an allocation costs
+    // more host time than building its diagonals takes); a large one has an
+    // allocation per factor.
+    struct Piece {
+        size_t bytes;
+        void **where;
+    };
+    std::vector<Piece> pieces;
+    std::vector<void *> dtab(P.factors.size(), nullptr);
+    for (size_t k = 0; k < P.factors.size(); ++k) {
+        hs::Factor &f = P.factors[k];
         hs::layout_factor(f, P.N, sc);
-        HS_HIP(hipMallocAsync(&f.dev, f.elems_total * sc, st), "hipMallocAsync(factor diagonals)");
+        pieces.push_back({f.elems_total * sc, &f.dev});
+        // D beside the factor's diagonals, unless it is the factor in natural order
+        if (f.has_diag && !(f.terms.empty() && f.perm_s == 0))
+            pieces.push_back({(size_t)P.N * (f.terms.empty() ? sc : 16), &dtab[k]});
     }
-    HS_HIP(hipMallocAsync(reinterpret_cast<void **>(&h->viol_dev), sizeof(int), st), "hipMallocAsync(flag)");
+    pieces.push_back({sizeof(int), reinterpret_cast<void **>(&h->viol_dev)});
+    pieces.push_back({sizeof(double) * ((size_t)HS_MAX_BATCH * hs::kReduceBlocks * 4 + HS_MAX_BATCH * 4),
+                      reinterpret_cast<void **>(&h->work_dev)});
+    size_t sum = 0;
+    for (const Piece &q : pieces) sum += (q.bytes + 255) / 256 * 256;
+    if (sum <= kOneAllocation) {
+        void *slab = nullptr;
+        HS_HIP(hipMallocAsync(&slab, sum, st), "hipMallocAsync(factors)");
+        h->owned.push_back(slab);
+        char *at = static_cast<char *>(slab);
+        for (const Piece &q : pieces) {
+            *q.where = at;
+            at += (q.bytes + 255) / 256 * 256;
+        }
+    } else {
+        for (const Piece &q : pieces) {
+            HS_HIP(hipMallocAsync(q.where, q.bytes, st), "hipMallocAsync(factor diagonals)");
+            h->owned.push_back(*q.where);
+        }
+    }
     HS_HIP(hipMemsetAsync(h->viol_dev, 0, sizeof(int), st), "hipMemsetAsync(flag)");
-    HS_HIP(hipMallocAsync(reinterpret_cast<void **>(&h->work_dev),
-                          sizeof(double) * ((size_t)HS_MAX_BATCH * hs::kReduceBlocks * 4 + HS_MAX_BATCH * 4), st),
-           "hipMallocAsync(workspace)");
 
-    // temporaries: phase table and per-factor tables
-    std::vector<void *> temps;
-    std::vector<std::vector<uint64_t>> host_keep;   // sources of async uploads, alive until the sync
-    std::vector<std::vector<double>> host_keep_d;
+    // every host table in one upload: Z masks and coefficients of the diagonal
+    // terms, then per factor offsets, element offsets and the local unitary
+    std::vector<char> host;
+    auto put = [&](const void *src, size_t bytes) {
+        const size_t at = host.size();
+        host.resize(at + (bytes + 15) / 16 * 16);
+        if (bytes) std::memcpy(host.data() + at, src, bytes);
+        return at;
+    };
+    std::vector<uint64_t> zm;
+    std::vector<double> cf;
+    for (int k : P.diag) {
+        zm.push_back(P.terms[k].z);
+        cf.push_back(P.terms[k].c);
+    }
+    const size_t at_zm = put(zm.data(), zm.size() * 8), at_cf = put(cf.data(), cf.size() * 8);
+    const int64_t zero_off = 0;
+    const size_t at_zero = put(&zero_off, 8);
+    struct At {
+        size_t offs, eo, L;
+    };
+    std::vector<At> at;
+    for (auto &f : P.factors) {
+        const std::vector<uint64_t> eo(f.elem_off.begin(), f.elem_off.end());
+        At x{};
+        x.offs = put(f.offs.data(), f.offs.size() * 8);
+        x.eo = put(eo.data(), eo.size() * 8);
+        x.L = put(f.L.data(), f.terms.empty() ? 0 : f.L.size() * 16);
+        at.push_back(x);
+    }
+    std::vector<void *> temps;          // freed once the stream is synchronised
     auto cleanup = [&]() {
         for (void *p : temps) (void)hipFreeAsync(p, st);
     };
-    auto upload = [&](const void *src, size_t bytes, void **dst) -> hipError_t {
-        // host sources stay alive until the stream is synchronised below
-        hipError_t e = hipMallocAsync(dst, std::max<size_t>(bytes, 16), st);
-        if (e != hipSuccess) return e;
-        temps.push_back(*dst);
-        return hipMemcpyAsync(*dst, src, bytes, hipMemcpyHostToDevice, st);
-    };
     hipError_t e = hipSuccess;
-    void *dzm = nullptr, *dcf = nullptr;
-    if (!P.diag.empty()) {
-        host_keep.emplace_back();
-        host_keep_d.emplace_back();
-        std::vector<uint64_t> &zm = host_keep.back();
-        std::vector<double> &cf = host_keep_d.back();
-        for (int k : P.diag) {
-            zm.push_back(P.terms[k].z);
-            cf.push_back(P.terms[k].c);
-        }
-        if ((e = upload(zm.data(), zm.size() * 8, &dzm)) != hipSuccess ||
-            (e = upload(cf.data(), cf.size() * 8, &dcf)) != hipSuccess) {
-            cleanup();
-            return hip_fail(e, "phase table setup");
-        }
+    void *tab = nullptr;
+    if ((e = hipMallocAsync(&tab, host.size(), st)) != hipSuccess) return hip_fail(e, "hipMallocAsync(tables)");
+    temps.push_back(tab);
+    if ((e = hipMemcpyAsync(tab, host.data(), host.size(), hipMemcpyHostToDevice, st)) != hipSuccess) {
+        cleanup();
+        return hip_fail(e, "table upload");
     }
+    char *dt = static_cast<char *>(tab);
     // one FP64 phase table exp(-i h E(x)) per distinct time step h of the
     // factors that carry D
     std::map<double, double *> phases;
@@ -462,76 +504,47 @@ static hs_status build_device(hs_factors_s *h, void *stream) {
             return hip_fail(e, "phase table setup");
         }
         temps.push_back(phase);
-        int le = hs::launch_phase_table(P.N, (int)P.diag.size(), static_cast<uint64_t *>(dzm),
-                                        static_cast<double *>(dcf), f.dt, phase, stream);
+        int le = hs::launch_phase_table(P.N, (int)P.diag.size(), reinterpret_cast<uint64_t *>(dt + at_zm),
+                                        reinterpret_cast<double *>(dt + at_cf), f.dt, phase, stream);
         if (le) { cleanup(); return hip_fail((hipError_t)le, "phase table kernel"); }
         phases[f.dt] = phase;
     }
-    for (auto &f : P.factors) {
+    for (size_t k = 0; k < P.factors.size(); ++k) {
+        const hs::Factor &f = P.factors[k];
         hs::ConstructArgs a{};
         a.base = f.dev;
         a.N = (int32_t)P.N;
         a.smask = (uint32_t)f.smask;
-        host_keep.emplace_back(f.elem_off.begin(), f.elem_off.end());
-        const std::vector<uint64_t> &eo = host_keep.back();
-        void *doffs = nullptr, *deo = nullptr, *dL = nullptr;
-        if ((e = upload(f.offs.data(), f.offs.size() * 8, &doffs)) != hipSuccess ||
-            (e = upload(eo.data(), eo.size() * 8, &deo)) != hipSuccess) {
-            cleanup();
-            return hip_fail(e, "factor table upload");
-        }
-        a.offs = static_cast<int64_t *>(doffs);
-        a.elem_off = static_cast<uint64_t *>(deo);
+        a.offs = reinterpret_cast<int64_t *>(dt + at[k].offs);
+        a.elem_off = reinterpret_cast<uint64_t *>(dt + at[k].eo);
+        a.K = 1;
         if (!f.terms.empty()) {
-            if ((e = upload(f.L.data(), f.L.size() * 16, &dL)) != hipSuccess) {
-                cleanup();
-                return hip_fail(e, "local unitary upload");
-            }
-            a.L = static_cast<double *>(dL);
+            a.L = reinterpret_cast<double *>(dt + at[k].L);
             a.K = 1 << f.bits.size();
             a.nbits = (int)f.bits.size();
             for (int q = 0; q < a.nbits; ++q) a.bits[q] = (int8_t)f.bits[q];
             a.lb = f.bits.empty() ? 0 : f.bits[0];
             a.contiguous = f.bits.empty() || f.bits.back() - f.bits.front() + 1 == (int)f.bits.size();
-        } else {
-            a.L = nullptr;
-            a.K = 1;
         }
         a.phase = f.has_diag ? phases[f.dt] : nullptr;
         a.perm_s = f.perm_s;
         a.perm_c = f.perm_c;
         int le = hs::launch_construct(a, (int)f.offs.size(), P.N, c128, stream);
         if (le) { cleanup(); return hip_fail((hipError_t)le, "construct kernel"); }
-        const void *dtab = nullptr;
-        if (f.has_diag && f.terms.empty() && f.perm_s == 0) {
-            dtab = f.dev;
-        } else if (f.has_diag) {
-            void *own = nullptr;
-            if ((e = hipMallocAsync(&own, (size_t)P.N * (f.terms.empty() ? sc : 16), st)) != hipSuccess) {
-                cleanup();
-                return hip_fail(e, "hipMallocAsync(diagonal)");
-            }
-            h->diag_own.push_back(own);
-            if (f.terms.empty()) {          // stored out of natural order: once more in order
-                static const int64_t zero_off[1] = {0};
-                void *d0 = nullptr;
-                if ((e = upload(zero_off, 8, &d0)) != hipSuccess) { cleanup(); return hip_fail(e, "diagonal table"); }
-                hs::ConstructArgs d = a;
-                d.base = own;
-                d.offs = static_cast<int64_t *>(d0);
-                d.elem_off = static_cast<uint64_t *>(d0);
-                d.perm_s = d.perm_c = 0;
-                le = hs::launch_construct(d, 1, P.N, c128, stream);
-            } else {
-                le = hs::launch_phase_order(a.phase, static_cast<double *>(own), P.N,
-                                            hs::gate_step(P, (int)h->diag_of.size(), 0).basis, stream);
-            }
-            if (le) { cleanup(); return hip_fail((hipError_t)le, "diagonal kernel"); }
-            dtab = own;
+        if (dtab[k] && f.terms.empty()) {       // stored out of natural order: once more in order
+            a.base = dtab[k];
+            a.offs = reinterpret_cast<int64_t *>(dt + at_zero);
+            a.elem_off = reinterpret_cast<uint64_t *>(dt + at_zero);
+            a.perm_s = a.perm_c = 0;
+            le = hs::launch_construct(a, 1, P.N, c128, stream);
+        } else if (dtab[k]) {
+            le = hs::launch_phase_order(a.phase, static_cast<double *>(dtab[k]), P.N,
+                                        hs::gate_step(P, (int)k, 0).basis, stream);
         }
-        h->diag_of.push_back(dtab);
+        if (le) { cleanup(); return hip_fail((hipError_t)le, "diagonal kernel"); }
+        h->diag_of.push_back(dtab[k] ? dtab[k] : f.has_diag ? f.dev : nullptr);
     }
-    e = hipStreamSynchronize(reinterpret_cast<hipStream_t>(stream));
+    e = hipStreamSynchronize(st);
     cleanup();
     if (e != hipSuccess) return hip_fail(e, "construction");
     h->built = true;
@@ -601,17 +614,19 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
         if (!f->whole)
             if (hs_status s = make_gate_plan(f, plan_key(1, true), true, f->whole, stream)) return s;
         const GatePlan &gp = *f->whole;
-        hs::GateRun r;
-        r.psi = psi;
-        r.N = P.N;
-        r.batch = batch;
-        r.by_rows = gp.prog.by_rows;
-        r.general = gp.prog.general;
-        r.steps = steps;
-        for (int q = 0; q < kParts; ++q) r.part[q] = gp.prog.launches[q].block0;
-        r.part[kParts] = gp.prog.launches[kParts - 1].block1;
-        int e = hs::launch_gates(gp.prog.launches[0], gp.tab, r, c128, false, stream);
-        if (e) return hip_fail((hipError_t)e, "whole-evolution kernel launch");
+        for (int64_t c0 = 0; c0 < batch; c0 += 32768) {
+            hs::GateRun r;
+            r.psi = static_cast<char *>(psi) + (size_t)c0 * P.N * sc;
+            r.N = P.N;
+            r.batch = (int)std::min<int64_t>(32768, batch - c0);
+            r.by_rows = gp.prog.by_rows;
+            r.general = gp.prog.general;
+            r.steps = steps;
+            for (int q = 0; q < kParts; ++q) r.part[q] = gp.prog.launches[q].block0;
+            r.part[kParts] = gp.prog.launches[kParts - 1].block1;
+            int e = hs::launch_gates(gp.prog.launches[0], gp.tab, r, c128, false, stream);
+            if (e) return hip_fail((hipError_t)e, "whole-evolution kernel launch");
+        }
         return HS_OK;
     }
     for (int c0 = 0; c0 < batch; c0 += HS_MAX_BATCH) {

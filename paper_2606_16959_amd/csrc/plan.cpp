@@ -40,53 +40,95 @@ int64_t spread_bits(uint64_t a, const std::vector<int> &bits) {
     return o;
 }
 
-// L = prod over members (first member applied first) of cos(th) I - i sin(th) P,
-// restricted to the support bits.  P[y, y^m] = i^ny (-1)^{popcount((y^m) & z)}.
-void local_unitary(const std::vector<Term> &terms, const std::vector<int> &members, double dt,
-                   std::vector<int> &bits, std::vector<std::complex<double>> &L) {
+// The product over members (first member applied first) of
+// cos(th) I - i sin(th) P, restricted to the support bits, with
+// P[y, y^m] = i^ny (-1)^{popcount((y^m) & z)}.  Row y has entries only at
+// y ^ s for s in the span of the members' flips, so the product is kept as
+// those: masks in ascending order, entry (y, y ^ masks[j]) at v[y * S + j].
+struct LocalUnitary {
+    std::vector<int> bits;
+    std::vector<uint64_t> masks;
+    std::vector<std::complex<double>> v;
+};
+
+void local_unitary(const std::vector<Term> &terms, const std::vector<int> &members, double dt, LocalUnitary &u) {
     uint64_t s = 0;
     for (int k : members) s |= terms[k].x | terms[k].z;
-    bits.clear();
+    u.bits.clear();
     for (int q = 0; q < 64; ++q)
-        if ((s >> q) & 1ull) bits.push_back(q);
-    const int K = 1 << bits.size();
-    L.assign((size_t)K * K, 0.0);
-    for (int a = 0; a < K; ++a) L[(size_t)a * K + a] = 1.0;
-    std::vector<std::complex<double>> nL((size_t)K * K);
+        if ((s >> q) & 1ull) u.bits.push_back(q);
+    const uint64_t K = 1ull << u.bits.size();
+    u.masks.assign(1, 0);
+    u.v.assign(K, 1.0);
+    std::vector<std::complex<double>> nv;
+    std::vector<uint64_t> nm;
+    std::vector<int> own, other;                // index of a new mask, and of it ^ m, among the old; -1 none
     static const std::complex<double> ipow[4] = {{1, 0}, {0, 1}, {-1, 0}, {0, -1}};
+    auto find = [&](uint64_t m) {
+        auto it = std::lower_bound(u.masks.begin(), u.masks.end(), m);
+        return it != u.masks.end() && *it == m ? (int)(it - u.masks.begin()) : -1;
+    };
     for (int k : members) {
         const Term &t = terms[k];
-        const uint64_t m = pext_bits(t.x, bits), z = pext_bits(t.z, bits);
+        const uint64_t m = pext_bits(t.x, u.bits), z = pext_bits(t.z, u.bits);
         const double th = t.c * dt;
         const double c = std::cos(th), sn = std::sin(th);
         const std::complex<double> ph = ipow[t.ny & 3];
-        for (int y = 0; y < K; ++y) {
-            const uint64_t src = (uint64_t)y ^ m;
+        nm = u.masks;
+        if (find(m) < 0)
+            for (uint64_t q : u.masks) nm.push_back(q ^ m);
+        std::sort(nm.begin(), nm.end());
+        const size_t S = u.masks.size(), NS = nm.size();
+        own.assign(NS, -1);
+        other.assign(NS, -1);
+        for (size_t j = 0; j < NS; ++j) {
+            own[j] = find(nm[j]);
+            other[j] = find(nm[j] ^ m);
+        }
+        nv.assign(K * NS, 0.0);
+        for (uint64_t y = 0; y < K; ++y) {
+            const uint64_t src = y ^ m;
             const double sg = (popc(src & z) & 1) ? -1.0 : 1.0;
             // -i sin(th) * (i^ny * sg)
             const std::complex<double> w = std::complex<double>(0.0, -sn) * (ph * sg);
-            for (int b = 0; b < K; ++b)
-                nL[(size_t)y * K + b] = c * L[(size_t)y * K + b] + w * L[(size_t)src * K + b];
+            for (size_t j = 0; j < NS; ++j) {
+                const std::complex<double> a = own[j] < 0 ? 0.0 : u.v[y * S + own[j]];
+                const std::complex<double> b = other[j] < 0 ? 0.0 : u.v[src * S + other[j]];
+                nv[y * NS + j] = c * a + w * b;
+            }
         }
-        L.swap(nL);
+        u.masks.swap(nm);
+        u.v.swap(nv);
     }
 }
 
-// Offsets spr(b) - spr(a) of the entries above the threshold; zeroes the rest.
-std::vector<int64_t> offsets_of(const std::vector<int> &bits, std::vector<std::complex<double>> &L) {
-    const int K = 1 << bits.size();
-    std::vector<int64_t> spr(K);
-    for (int a = 0; a < K; ++a) spr[a] = spread_bits((uint64_t)a, bits);
-    std::set<int64_t> offs;
-    for (int a = 0; a < K; ++a)
-        for (int b = 0; b < K; ++b) {
-            std::complex<double> &v = L[(size_t)a * K + b];
+// Offsets spr(y ^ s) - spr(y) of the entries above the threshold, ascending;
+// zeroes the rest.
+std::vector<int64_t> offsets_of(LocalUnitary &u) {
+    const size_t K = (size_t)1 << u.bits.size(), S = u.masks.size();
+    std::vector<int64_t> spr(K), offs;
+    for (size_t a = 0; a < K; ++a) spr[a] = spread_bits((uint64_t)a, u.bits);
+    offs.reserve(K * S);
+    for (size_t y = 0; y < K; ++y)
+        for (size_t j = 0; j < S; ++j) {
+            std::complex<double> &v = u.v[y * S + j];
             if (std::abs(v) > kTau)
-                offs.insert(spr[b] - spr[a]);
+                offs.push_back(spr[y ^ u.masks[j]] - spr[y]);
             else
                 v = 0.0;
         }
-    return std::vector<int64_t>(offs.begin(), offs.end());
+    std::sort(offs.begin(), offs.end());
+    offs.erase(std::unique(offs.begin(), offs.end()), offs.end());
+    return offs;
+}
+
+// K x K row-major matrix
+std::vector<std::complex<double>> dense(const LocalUnitary &u) {
+    const size_t K = (size_t)1 << u.bits.size(), S = u.masks.size();
+    std::vector<std::complex<double>> L(K * K, 0.0);
+    for (size_t y = 0; y < K; ++y)
+        for (size_t j = 0; j < S; ++j) L[y * K + (y ^ u.masks[j])] = u.v[y * S + j];
+    return L;
 }
 
 bool support_ok(const std::vector<Term> &terms, const std::vector<int> &members) {
@@ -96,10 +138,9 @@ bool support_ok(const std::vector<Term> &terms, const std::vector<int> &members)
 }
 
 int count_diags(const std::vector<Term> &terms, const std::vector<int> &members, double dt) {
-    std::vector<int> bits;
-    std::vector<std::complex<double>> L;
-    local_unitary(terms, members, dt, bits, L);
-    return (int)offsets_of(bits, L).size();
+    LocalUnitary u;
+    local_unitary(terms, members, dt, u);
+    return (int)offsets_of(u).size();
 }
 
 }  // namespace
@@ -296,8 +337,11 @@ hs_status make_plan(int n, int n_terms, const char *const *strings, const double
         f.has_diag = with_diag;
         f.dt = h;
         f.terms = g;
-        local_unitary(P.terms, f.terms, h, f.bits, f.L);
-        f.offs = offsets_of(f.bits, f.L);
+        LocalUnitary u;
+        local_unitary(P.terms, f.terms, h, u);
+        f.offs = offsets_of(u);
+        f.bits = u.bits;
+        f.L = dense(u);
         for (int q : f.bits) f.smask |= 1ull << q;
         for (int k : f.terms) f.xmask_union |= P.terms[k].x;
         return f;

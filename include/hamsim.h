@@ -149,9 +149,9 @@ hs_status hs_build_factors(int n_qubits, int n_terms, const char *const *pauli_t
  * one stream.
  * The state is checked (device memory, batch * N elements inside one
  * allocation) before anything else, also when steps is 0.
- * Small states (N <= 2048 complex64 or 1024 complex128 rows by default; the
- * environment variable HAMSIM_WHOLE_MAX_ROWS sets the cap, at most 8192 /
- * 4096 rows, 0 = never) evolve without HS_RENORM or HS_NO_FUSE in one launch
+ * Small states (N <= 4096 rows by default; the environment variable
+ * HAMSIM_WHOLE_MAX_ROWS sets the cap, at most 8192 complex64 / 4096 complex128
+ * rows, 0 = never) evolve without HS_RENORM or HS_NO_FUSE in one launch
  * for all steps and states, each state held in LDS by one workgroup (same
  * values as the launch per run and step).
  */
@@ -206,15 +206,16 @@ hs_status hs_factor_copy_diagonal(hs_factors f, int k, int j, long long start, l
 hs_status hs_factor_storage(hs_factors f, int k, int *split_bit, int *chunk_bits);
 /* Bytes of device memory an evolution of `batch` states needs: the stored
  * diagonals (Eq. 6: N - |d| entries per diagonal, each start aligned to 256
- * bytes), the caller's states and the library's workspace (the scratch state
- * of an open launch, reduction partials).  Used for admission by HBM
+ * bytes), the exponentials of D (16 bytes per row) of each factor that carries
+ * it, the caller's states and the library's workspace (reduction partials, and
+ * room for one more batch of states where a factor flips bits too far apart
+ * for a tile of consecutive bits).  Used for admission by HBM
  * footprint in a served loop.  Counts the handle's dtype (complex64 for a
  * handle from hs_plan, which has none yet). */
 hs_status hs_footprint(hs_factors f, int batch, size_t *bytes);
 /* The same figure for the handle built with `dtype`: element size, diagonal
  * alignment and the dtype's own tile limits (a complex128 tile holds half
- * the rows, so a factor closed in complex64 can need the open launch and its
- * scratch state in complex128).  For admission before building. */
+ * the rows, so a factor can need that room in complex128 only).  For admission before building. */
 hs_status hs_footprint_dtype(hs_factors f, int batch, hs_dtype dtype, size_t *bytes);
 /* The fusion list of one Trotter step for `batch` states with evolve `flags`:
  * *n_launches receives its length; entry i holds the factors at positions

@@ -279,9 +279,10 @@ void choose_storage_order(Plan &P, int dtype) {
     }
 }
 
-// log2 rows of an evolution's tiles: 64 KiB of LDS, so that two workgroups
-// share a CU, halved (down to 1024 rows) while the launch would have fewer
-// than 256 of them, one per compute unit.
+// log2 rows of an evolution's largest tiles: 64 KiB of LDS, so that two
+// workgroups share a CU, halved (down to 1024 rows) while the launch would
+// have fewer than 256 of them, one per compute unit.  make_gate_plan takes
+// half of it where that needs no more launches.
 int gate_tile_bits(int dtype, int64_t N, int batch) {
     int kt = dtype == HS_C128 ? 12 : 13;
     while (kt > 10 && ((N * batch) >> kt) < 256) --kt;
@@ -670,7 +671,7 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
                 r.N = P.N;
                 r.batch = chunk;
                 r.by_rows = gp.prog.by_rows;
-        r.general = gp.prog.general;
+                r.general = gp.prog.general;
                 r.stage_diag = L.stage_diag >= 0 ? f->diag_of[L.stage_diag] : nullptr;
                 r.nrm2 = (renorm && s > 0 && l == l0) ? rec : nullptr;
                 r.norm_out = (renorm && l + 1 == l1) ? f->norm_dev : nullptr;

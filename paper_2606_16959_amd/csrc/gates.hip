@@ -13,8 +13,16 @@
 // What bounds it: HBM for large states (state read and written once per
 // launch, and 16 bytes of D per row where a factor carries it).  A factor
 // that flips three bits costs 16 FMAs per row, the one that carries D about
-// 80 operations, which take less time than the bytes.  Two 64 KiB tiles fit a
-// CU's LDS, so one tile's loads and stores overlap the other's arithmetic.
+// 80 operations, which take less time than the bytes.  Four 32 KiB tiles (two
+// of 64 KiB where the larger tile saves a launch) fit a CU's LDS, so one
+// tile's loads and stores overlap the others' arithmetic.  States that stay in
+// cache are bound by the chain inside a workgroup: per block a scalar-load
+// round trip, an LDS round trip and a barrier, 17-24 us a launch of a
+// complex128 state of 2^20 rows.
+// Measured against one DIA SpMV per factor over the stored diagonals, a step:
+// n = 26 lattice complex64 10.3 -> 0.79 ms (4.3 GB moved in three launches),
+// n = 24 MaxCut with 8 states 4.5 -> 1.44 ms, n = 20 chain complex128
+// 232 -> 58 us, n = 17 second order 82 -> 37 us.
 #include <hip/hip_runtime.h>
 
 #include <atomic>

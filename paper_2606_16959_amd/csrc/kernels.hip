@@ -543,20 +543,57 @@ __global__ void scale_kernel(C2<R> *psi, int64_t N, const double *nrm2) {
 // FP64; wave64 butterfly, then the four waves in fixed order.  Pass 2: one
 // block per state sums the G partials in a fixed tree.  No atomics, so the
 // result is bit-reproducible.
+//
+// What bounds it: HBM for states beyond the last-level cache, which are read
+// with streaming loads (n = 24, a complex64 against a complex128 pair of
+// states, 768 MiB: 120 us = 6.7 TB/s in the kernel, 167 us a call; through the
+// caches 186 us a call).  A norm has one stream of loads per thread and few
+// waves for a lone state, so it keeps four in flight (n = 26 complex64 186 ->
+// 123 us a call); the overlap's two streams were slower that way (182 -> 190).
 
-template <typename TA, typename TB, bool DOT>
+// One amplitude through a streaming load (STREAM) or the caches; callers' states
+// are aligned to their real type only.
+template <bool STREAM>
+__device__ __forceinline__ C2<float> ld_state(const C2<float> *p) {
+    typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+    typedef const __attribute__((address_space(1))) f2u g_f2u;
+    const f2u v = STREAM ? __builtin_nontemporal_load((g_f2u *)p) : *(g_f2u *)p;
+    return C2<float>{v.x, v.y};
+}
+template <bool STREAM>
+__device__ __forceinline__ C2<double> ld_state(const C2<double> *p) {
+    typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+    typedef const __attribute__((address_space(1))) d2u g_d2u;
+    const d2u v = STREAM ? __builtin_nontemporal_load((g_d2u *)p) : *(g_d2u *)p;
+    return C2<double>{v.x, v.y};
+}
+
+template <typename TA, typename TB, bool DOT, bool STREAM>
 __global__ __launch_bounds__(256) void reduce_partial_kernel(const void *A, const void *Bv, int64_t N,
                                                              int G, double *partial) {
     const int b = blockIdx.y;
     const C2<TA> *pa = reinterpret_cast<const C2<TA> *>(A) + b * N;
     const C2<TB> *pb = reinterpret_cast<const C2<TB> *>(Bv) + b * N;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < N; i += (int64_t)G * 256) {
-        const C2<TA> u = pa[i];
+    const int64_t step = (int64_t)G * 256;
+    int64_t i = blockIdx.x * 256 + threadIdx.x;
+    if (!DOT)
+        for (; i + 3 * step < N; i += 4 * step) {
+            C2<TA> u[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) u[k] = ld_state<STREAM>(pa + i + k * step);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double ar = (double)u[k].re, ai = (double)u[k].im;
+                s[2] += ar * ar + ai * ai;
+            }
+        }
+    for (; i < N; i += step) {
+        const C2<TA> u = ld_state<STREAM>(pa + i);
         const double ar = (double)u.re, ai = (double)u.im;
         s[2] += ar * ar + ai * ai;
         if (DOT) {
-            const C2<TB> w = pb[i];
+            const C2<TB> w = ld_state<STREAM>(pb + i);
             const double br = (double)w.re, bi = (double)w.im;
             s[0] += ar * br + ai * bi;
             s[1] += ar * bi - ai * br;
@@ -794,27 +831,32 @@ int launch_scale(void *psi, int64_t N, int batch, const double *nrm2, bool c128,
     return (int)hipGetLastError();
 }
 
+// Bytes of a reduction's states above which they are read past the caches: at
+// 256 MiB (the last-level cache) streaming is slower, 92 against 84 us a call
+// for two complex64 states of 2^24 rows, at 384 MiB faster, 107 against 116 us.
+static constexpr size_t kReduceStream = size_t(256) << 20;
+
+template <typename TA, typename TB, bool DOT>
+static void reduce_partials(const void *A, const void *Bv, int batch, int64_t N, int G, double *partial, void *stream) {
+    const size_t bytes = (size_t)batch * N * 2 * (sizeof(TA) + (DOT ? sizeof(TB) : 0));
+    auto k = bytes > kReduceStream ? reduce_partial_kernel<TA, TB, DOT, true> : reduce_partial_kernel<TA, TB, DOT, false>;
+    hipLaunchKernelGGL(k, dim3(G, batch), dim3(256), 0, S(stream), A, Bv, N, G, partial);
+}
+
 int launch_reduce(const void *A, int ta, const void *Bv, int tb, int batch, int64_t N,
                   double *partial, int G, double *out, bool dot, void *stream) {
-    dim3 g(G, batch), blk(256);
     if (!dot) {
-        if (ta == HS_C128)
-            hipLaunchKernelGGL((reduce_partial_kernel<double, double, false>), g, blk, 0, S(stream), A, A, N, G, partial);
-        else
-            hipLaunchKernelGGL((reduce_partial_kernel<float, float, false>), g, blk, 0, S(stream), A, A, N, G, partial);
+        if (ta == HS_C128) reduce_partials<double, double, false>(A, A, batch, N, G, partial, stream);
+        else reduce_partials<float, float, false>(A, A, batch, N, G, partial, stream);
     } else {
-        if (ta == HS_C128 && tb == HS_C128)
-            hipLaunchKernelGGL((reduce_partial_kernel<double, double, true>), g, blk, 0, S(stream), A, Bv, N, G, partial);
-        else if (ta == HS_C128)
-            hipLaunchKernelGGL((reduce_partial_kernel<double, float, true>), g, blk, 0, S(stream), A, Bv, N, G, partial);
-        else if (tb == HS_C128)
-            hipLaunchKernelGGL((reduce_partial_kernel<float, double, true>), g, blk, 0, S(stream), A, Bv, N, G, partial);
-        else
-            hipLaunchKernelGGL((reduce_partial_kernel<float, float, true>), g, blk, 0, S(stream), A, Bv, N, G, partial);
+        if (ta == HS_C128 && tb == HS_C128) reduce_partials<double, double, true>(A, Bv, batch, N, G, partial, stream);
+        else if (ta == HS_C128) reduce_partials<double, float, true>(A, Bv, batch, N, G, partial, stream);
+        else if (tb == HS_C128) reduce_partials<float, double, true>(A, Bv, batch, N, G, partial, stream);
+        else reduce_partials<float, float, true>(A, Bv, batch, N, G, partial, stream);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
-    hipLaunchKernelGGL(reduce_final_kernel, dim3(batch), blk, 0, S(stream), partial, G, out);
+    hipLaunchKernelGGL(reduce_final_kernel, dim3(batch), dim3(256), 0, S(stream), partial, G, out);
     return (int)hipGetLastError();
 }
 

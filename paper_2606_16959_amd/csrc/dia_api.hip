@@ -695,6 +695,25 @@ hs_status hs_dia_evolve(hs_dia U, void *psi, int batch, int steps, void *stream)
     const int64_t N = U->N;
     const size_t sc = U->elem();
     const int nd = (int)U->offs.size();
+    if (hs::loop_fits(N, nd, U->dtype == HS_C128)) {
+        // every step in one launch wherever a workgroup holds the operator:
+        // at its largest, 1024 complex128 rows of 21 diagonals, a step is 1.2
+        // us against 4.1 us a launch, and one step alone 23 against 69 us with
+        // the scratch state, the descriptors and the copy back
+        hs::LoopArgs a{};
+        a.x = psi;
+        a.N = (int32_t)N;
+        a.nd = nd;
+        a.steps = steps;
+        for (int j = 0; j < hs::kLoopDiags; ++j) {
+            a.off[j] = j < nd ? (int32_t)U->offs[j] : 0;
+            a.ptr[j] = U->ptr[std::min(j, nd - 1)];
+        }
+        int le = hs::launch_loop(a, batch, U->dtype == HS_C128, st);
+        if (le) return dhip((hipError_t)le, "loop kernel launch");
+        DHIP(hipStreamSynchronize(st), "hipStreamSynchronize");
+        return HS_OK;
+    }
     std::vector<long long> offs(U->offs.begin(), U->offs.end());
     std::vector<const void *> ptrs(U->ptr.begin(), U->ptr.end());
     Temps tmp(st);

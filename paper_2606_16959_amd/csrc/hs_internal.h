@@ -84,6 +84,15 @@ struct TileArgs {
     int32_t stream_out;      // write y with non-temporal stores (see kStreamOutBytes)
 };
 
+constexpr int kLoopDiags = 24;   // diagonals whose coefficients a thread of the loop kernel holds
+
+struct LoopArgs {
+    void *x;                     // states back to back, in place
+    int32_t N, nd, steps;
+    int32_t off[kLoopDiags];     // ascending; 0 past nd
+    const void *ptr[kLoopDiags]; // the last one again past nd
+};
+
 // States of at least this many bytes (the chunk of up to HS_MAX_BATCH states
 // that a call takes through all its launches before the next chunk) are
 // written with non-temporal stores: they cannot stay in the 256 MB
@@ -118,6 +127,9 @@ int launch_perm_gather(const void *src, void *dst, int64_t start, int64_t count,
                        bool c128, void *stream);
 int launch_tile(const TileArgs &a, int batch, bool c128, void *stream);
 // the same with the Horner epilogue y = x0 + alpha (A x); y may alias x0, not x
+// `steps` products x <- A x of every state in one launch (loop_fits)
+bool loop_fits(int64_t N, int nd, bool c128);
+int launch_loop(const LoopArgs &a, int batch, bool c128, void *stream);
 int launch_tile_horner(const TileArgs &a, int batch, bool c128, void *stream);
 // Largest state (rows) evolved whole by one workgroup: 8192 complex64 or
 // 4096 complex128 rows (64 KiB of LDS).

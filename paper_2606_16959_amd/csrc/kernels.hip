@@ -492,6 +492,71 @@ __global__ __launch_bounds__(kRowsThreads) void dia_rows_kernel(TileArgs a) {
     reinterpret_cast<C2<R> *>(a.y)[(int64_t)blockIdx.y * a.stride + r] = acc;
 }
 
+// ------------------------------------------------------------ DIA loop kernel
+//
+// All steps x <- A x of a small operator in one launch: a workgroup per state
+// keeps the state in LDS and every coefficient of its rows in registers (24
+// complex128 diagonals of two rows are 192 of a thread's 256 VGPRs), so a step is one LDS
+// read and the multiply-adds per diagonal and two barriers.  Zeros on both
+// sides of the state stand for partners outside it.  The sum runs in the order
+// and with the multiply-adds of the row kernel, so the values are the same.
+//
+// What bounds it: the LDS reads, 16 KiB per diagonal and step of 1024 complex128
+// rows.  A step of 21 diagonals there takes 1.17 us where a launch of the row
+// kernel per step takes 4.1 (17 diagonals at N = 256: 0.59 us; 600 states 3.7
+// us).  512 threads of twice the rows: 1.30 us.
+template <typename R>
+constexpr int kLoopRowsPer = sizeof(R) == 8 ? 1 : 2;         // rows of a thread
+template <typename R>
+constexpr int kLoopRows = 1024 * kLoopRowsPer<R>;            // 48 KiB of LDS with the zeros
+
+template <typename R, int ND>
+__global__ __launch_bounds__(1024) void dia_loop_kernel(LoopArgs a) {
+    constexpr int E = kLoopRowsPer<R>;
+    __shared__ C2<R> lds[3 * kLoopRows<R>];                  // zeros, the state, zeros
+    const int N = a.N, nt = blockDim.x, tid = threadIdx.x;
+    C2<R> *x = reinterpret_cast<C2<R> *>(a.x) + (int64_t)blockIdx.x * N;
+    for (int i = tid; i < 3 * N; i += nt) lds[i] = i >= N && i < 2 * N ? x[i - N] : C2<R>{(R)0, (R)0};
+    C2<R> c[ND][E];
+#pragma unroll
+    for (int j = 0; j < ND; ++j) {
+        const int d = a.off[j];                              // past the last diagonal: 0, no entries
+        const int len = j < a.nd ? N - (d < 0 ? -d : d) : 0;
+        const __amdgpu_buffer_rsrc_t cb = buffer_of<R>(a.ptr[j], len);
+#pragma unroll
+        for (int e = 0; e < E; ++e) buffer_get(cb, tid + e * nt + (d < 0 ? d : 0), c[j][e]);
+    }
+    // a thread past the last row reads row N - 1's partners and writes nothing
+    int row[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) row[e] = N + (tid + e * nt < N ? tid + e * nt : N - 1);
+    __syncthreads();
+    for (int s = 0; s < a.steps; ++s) {
+        C2<R> acc[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            acc[e] = C2<R>{(R)0, (R)0};
+            asm volatile("" : "+v"(row[e]));                 // keeps ND * E addresses out of the registers
+        }
+#pragma unroll
+        for (int j = 0; j < ND; ++j) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) cfma(acc[e], c[j][e], lds[row[e] + a.off[j]]);
+            if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // four diagonals' partners in flight
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) asm volatile("" : "+v"(acc[e].re), "+v"(acc[e].im));   // sums end here, not below
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (tid + e * nt < N) lds[row[e]] = acc[e];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (tid + e * nt < N) x[tid + e * nt] = lds[row[e]];
+}
+
 // Single main-diagonal factor applied `steps` times: y[i] = v[i]^steps x[i]
 // for N even, each thread two adjacent entries (one 16-byte load of the
 // coefficients and of each state for complex64), the powers taken as
@@ -785,6 +850,23 @@ static int product_launch(const TileArgs &a, int batch, bool horner, void *strea
 
 int launch_tile(const TileArgs &a, int batch, bool c128, void *stream) {
     return c128 ? product_launch<double>(a, batch, false, stream) : product_launch<float>(a, batch, false, stream);
+}
+
+bool loop_fits(int64_t N, int nd, bool c128) {
+    return nd >= 1 && nd <= kLoopDiags && N <= (c128 ? kLoopRows<double> : kLoopRows<float>);
+}
+
+template <typename R>
+static int loop_launch(const LoopArgs &a, int batch, void *stream) {
+    const int nt = ((a.N + kLoopRowsPer<R> - 1) / kLoopRowsPer<R> + 63) / 64 * 64;
+    auto k = a.nd <= 8 ? dia_loop_kernel<R, 8> : a.nd <= 16 ? dia_loop_kernel<R, 16> : dia_loop_kernel<R, kLoopDiags>;
+    hipLaunchKernelGGL(k, dim3(batch), dim3(nt), 0, S(stream), a);
+    return (int)hipGetLastError();
+}
+
+int launch_loop(const LoopArgs &a, int batch, bool c128, void *stream) {
+    if (!loop_fits(a.N, a.nd, c128) || a.N < 1 || batch < 1) return (int)hipErrorInvalidValue;
+    return c128 ? loop_launch<double>(a, batch, stream) : loop_launch<float>(a, batch, stream);
 }
 
 int launch_tile_horner(const TileArgs &a, int batch, bool c128, void *stream) {

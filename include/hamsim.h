@@ -355,7 +355,8 @@ hs_status hs_estimate_timesteps(hs_dia H, double t, int budget, double tol, int 
 hs_status hs_dia_to_c64(hs_dia A, void *stream, hs_dia *out);
 /* Alg. 3's loop: psi <- U^steps psi for `batch` device states of U's dtype,
  * by repeated DIA SpMV (out of place with library scratch, result written
- * back to psi).  The state is checked before anything else, also when
+ * back to psi; small operators run every step in one launch, in place, with
+ * the same result).  The state is checked before anything else, also when
  * steps is 0.  Synchronises `stream`. */
 hs_status hs_dia_evolve(hs_dia U, void *psi, int batch, int steps, void *stream);
 /* nu(A) = sum over A's stored diagonals (ascending offset) of each one's

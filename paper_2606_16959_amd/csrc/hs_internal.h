@@ -84,7 +84,7 @@ struct TileArgs {
     int32_t stream_out;      // write y with non-temporal stores (see kStreamOutBytes)
 };
 
-constexpr int kLoopDiags = 24;   // diagonals whose coefficients a thread of the loop kernel holds
+constexpr int kLoopDiags = 48;   // diagonals whose coefficients a thread of the loop kernel holds
 
 struct LoopArgs {
     void *x;                     // states back to back, in place

@@ -496,24 +496,26 @@ __global__ __launch_bounds__(kRowsThreads) void dia_rows_kernel(TileArgs a) {
 //
 // All steps x <- A x of a small operator in one launch: a workgroup per state
 // keeps the state in LDS and every coefficient of its rows in registers (24
-// complex128 diagonals of two rows are 192 of a thread's 256 VGPRs), so a step is one LDS
-// read and the multiply-adds per diagonal and two barriers.  Zeros on both
-// sides of the state stand for partners outside it.  The sum runs in the order
-// and with the multiply-adds of the row kernel, so the values are the same.
+// complex128 diagonals are 96 of the 128 VGPRs of one of 1024 threads, 48 are
+// 192 of 256 of one of 512), so a step is one LDS read and the multiply-adds
+// per diagonal and two barriers.  Zeros on both sides of the state stand for
+// partners outside it.  The sum runs in the order and with the multiply-adds
+// of the row kernel, so the values are the same.
 //
 // What bounds it: the LDS reads, 16 KiB per diagonal and step of 1024 complex128
 // rows.  A step of 21 diagonals there takes 1.17 us where a launch of the row
 // kernel per step takes 4.1 (17 diagonals at N = 256: 0.59 us; 600 states 3.7
-// us).  512 threads of twice the rows: 1.30 us.
+// us); 48 diagonals at N = 512 take 1.29 against 4.1 us.  512 threads of twice
+// the rows for 21 diagonals: 1.30 us.
 template <typename R>
 constexpr int kLoopRowsPer = sizeof(R) == 8 ? 1 : 2;         // rows of a thread
 template <typename R>
 constexpr int kLoopRows = 1024 * kLoopRowsPer<R>;            // 48 KiB of LDS with the zeros
 
-template <typename R, int ND>
-__global__ __launch_bounds__(1024) void dia_loop_kernel(LoopArgs a) {
+template <typename R, int ND, int NT>
+__global__ __launch_bounds__(NT) void dia_loop_kernel(LoopArgs a) {
     constexpr int E = kLoopRowsPer<R>;
-    __shared__ C2<R> lds[3 * kLoopRows<R>];                  // zeros, the state, zeros
+    __shared__ C2<R> lds[3 * E * NT];                        // zeros, the state, zeros
     const int N = a.N, nt = blockDim.x, tid = threadIdx.x;
     C2<R> *x = reinterpret_cast<C2<R> *>(a.x) + (int64_t)blockIdx.x * N;
     for (int i = tid; i < 3 * N; i += nt) lds[i] = i >= N && i < 2 * N ? x[i - N] : C2<R>{(R)0, (R)0};
@@ -853,13 +855,17 @@ int launch_tile(const TileArgs &a, int batch, bool c128, void *stream) {
 }
 
 bool loop_fits(int64_t N, int nd, bool c128) {
-    return nd >= 1 && nd <= kLoopDiags && N <= (c128 ? kLoopRows<double> : kLoopRows<float>);
+    const int64_t rows = c128 ? kLoopRows<double> : kLoopRows<float>;
+    return nd >= 1 && (nd <= kLoopDiags / 2 ? N <= rows : nd <= kLoopDiags && N <= rows / 2);
 }
 
 template <typename R>
 static int loop_launch(const LoopArgs &a, int batch, void *stream) {
     const int nt = ((a.N + kLoopRowsPer<R> - 1) / kLoopRowsPer<R> + 63) / 64 * 64;
-    auto k = a.nd <= 8 ? dia_loop_kernel<R, 8> : a.nd <= 16 ? dia_loop_kernel<R, 16> : dia_loop_kernel<R, kLoopDiags>;
+    auto k = a.nd <= 8                ? dia_loop_kernel<R, 8, 1024>
+             : a.nd <= 16             ? dia_loop_kernel<R, 16, 1024>
+             : a.nd <= kLoopDiags / 2 ? dia_loop_kernel<R, kLoopDiags / 2, 1024>
+                                      : dia_loop_kernel<R, kLoopDiags, 512>;
     hipLaunchKernelGGL(k, dim3(batch), dim3(nt), 0, S(stream), a);
     return (int)hipGetLastError();
 }

@@ -1,6 +1,7 @@
 """Alg. 3's loop in one launch (operators of up to 1024 complex128 or 2048
-complex64 rows and 24 diagonals) gives the bits of one product after the other
-through the general entry, at the edges of its sizes and just beyond them."""
+complex64 rows and 24 diagonals, or half the rows and 48 diagonals) gives the
+bits of one product after the other through the general entry, at the edges of
+its sizes and just beyond them."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,8 @@ pytestmark = pytest.mark.gpu
     (1, 1, "c128", 3, 4), (2, 3, "c64", 1, 1), (63, 8, "c128", 1, 2), (64, 9, "c64", 3, 5), (65, 16, "c128", 2, 3),
     (129, 17, "c64", 9, 2), (1000, 24, "c128", 2, 3), (1023, 24, "c64", 1, 4), (1024, 21, "c128", 3, 7),
     (1024, 25, "c128", 1, 2), (1025, 24, "c128", 1, 2), (2047, 23, "c64", 2, 3), (2048, 24, "c64", 1, 5),
-    (2049, 24, "c64", 1, 2)])
+    (2049, 24, "c64", 1, 2), (512, 48, "c128", 2, 3), (511, 25, "c128", 1, 2), (512, 49, "c128", 1, 2),
+    (513, 48, "c128", 1, 2), (1024, 48, "c64", 3, 2), (1023, 33, "c64", 1, 3), (1025, 48, "c64", 1, 2)])
 def test_loop_equals_single_products(N, nd, dtype, batch, steps):
     hs, torch = hs_gpu()
     from paper_2606_16959_amd import dia

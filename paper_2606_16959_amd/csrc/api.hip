@@ -352,6 +352,9 @@ hs_status make_gate_plan(hs_factors_s *h, const PlanKey &key, bool loop, std::un
         if (half.prog.launches.size() <= gp->prog.launches.size()) std::swap(*gp, half);
     }
     gp->launch0[kParts] = (int)gp->prog.launches.size();
+    // the looped form applies a part's blocks from one launch
+    for (int q = 0; loop && q < kParts; ++q)
+        if (gp->launch0[q + 1] != gp->launch0[q] + 1) return fail(HS_EDEVICE, "looped coset program of several launches");
     if (hs_status s = upload_gates(h, *gp, reinterpret_cast<hipStream_t>(stream))) {
         if (gp->dev) (void)hipFreeAsync(gp->dev, reinterpret_cast<hipStream_t>(stream));
         return s;
@@ -623,8 +626,8 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
             r.by_rows = gp.prog.by_rows;
             r.general = gp.prog.general;
             r.steps = steps;
-            for (int q = 0; q < kParts; ++q) r.part[q] = gp.prog.launches[q].block0;
-            r.part[kParts] = gp.prog.launches[kParts - 1].block1;
+            for (int q = 0; q < kParts; ++q) r.part[q] = gp.prog.launches[gp.launch0[q]].block0;
+            r.part[kParts] = gp.prog.launches[gp.launch0[kParts] - 1].block1;
             int e = hs::launch_gates(gp.prog.launches[0], gp.tab, r, c128, false, stream);
             if (e) return hip_fail((hipError_t)e, "whole-evolution kernel launch");
         }

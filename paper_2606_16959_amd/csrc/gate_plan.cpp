@@ -155,7 +155,7 @@ void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, in
         int w = wlog;
         while (j < steps.size()) {
             const uint64_t nx = need | steps[j].flips;
-            if (max_factors > 0 && (int)(j - i) >= max_factors) break;
+            if (!loop && max_factors > 0 && (int)(j - i) >= max_factors) break;
             if (popc64(nx | ((1ull << w) - 1)) > kt) {
                 if (j > i) break;
                 // a single wide factor: shorten the runs, down to row pairs

@@ -143,7 +143,8 @@ std::vector<GateStep> gate_steps(const Plan &P, const std::vector<int> &seq);
 // 2^kt rows that holds the low wlog bits (rows in one run) holds every bit
 // they flip; at most max_factors factors per launch (0: any number).
 // `loop`: one launch of the whole state whose blocks are applied again and
-// again (no diagonal folded into the load).  Appends to `out`.
+// again (no diagonal folded into the load), whatever max_factors says.
+// Appends to `out`.
 void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, int wlog, int max_factors, bool loop,
                    GateProgram &out);
 

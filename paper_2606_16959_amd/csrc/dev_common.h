@@ -26,6 +26,12 @@ __device__ __forceinline__ void cfma(C2<double> &acc, C2<double> c, C2<double> x
     acc.im = __builtin_fma(c.im, x.re, acc.im);
 }
 
+// (vr + i vi)(pr + i pi) in FP64: the product of an entry with D.  Spelled out,
+// so that every kernel that forms a coefficient rounds it the same way.
+__device__ __forceinline__ C2<double> cmul_d(double vr, double vi, double pr, double pi) {
+    return C2<double>{__builtin_fma(vr, pr, -(vi * pi)), __builtin_fma(vi, pr, vr * pi)};
+}
+
 template <typename R>
 __device__ __forceinline__ C2<R> cscale(C2<R> v, R s) {
     return C2<R>{v.re * s, v.im * s};

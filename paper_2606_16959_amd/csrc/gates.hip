@@ -98,13 +98,12 @@ __device__ __forceinline__ void apply_real(C2<R> (&x)[1 << RHO], const R *m, int
     }
 }
 
-// The coefficient v D of one entry, rounded to the state's dtype as the
-// stored diagonals are.
+// The coefficient v D of one entry, multiplied and rounded to the state's dtype
+// as the stored diagonals are (cmul_d).
 template <typename R>
 __device__ __forceinline__ C2<R> d_entry(double vr, double vi, d2v D) {
-    const double tr = vr * D.x - vi * D.y;
-    const double ti = vr * D.y + vi * D.x;
-    return C2<R>{(R)tr, (R)ti};
+    const C2<double> t = cmul_d(vr, vi, D.x, D.y);
+    return C2<R>{(R)t.re, (R)t.im};
 }
 // v real, or imaginary (imag): i v D
 template <typename R>

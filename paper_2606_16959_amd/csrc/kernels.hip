@@ -67,11 +67,9 @@ __global__ void construct_kernel(ConstructArgs a) {
             vi = a.L[2 * e + 1];
         }
         if (a.phase && (vr != 0.0 || vi != 0.0)) {
-            const double pr = a.phase[2 * p], pi = a.phase[2 * p + 1];
-            const double tr = vr * pr - vi * pi;
-            const double ti = vr * pi + vi * pr;
-            vr = tr;
-            vi = ti;
+            const C2<double> t = cmul_d(vr, vi, a.phase[2 * p], a.phase[2 * p + 1]);
+            vr = t.re;
+            vi = t.im;
         }
         out[perm_pos(i, a.perm_s, a.perm_c, clr)] = C2<R>{(R)vr, (R)vi};
     }

@@ -747,8 +747,8 @@ def _step_kernel(name):
 
 
 def _kernel_form(name):
-    """The instance: gate_kernel<R, STREAM, GENERAL>."""
-    return "cosets, " + ("general" if _template_args(name)[2] == "true" else "lean")
+    """The instance: gate_kernel<R, STREAM, LEVEL>."""
+    return "cosets, " + {"0": "lean", "1": "general"}.get(_template_args(name)[2], "units")
 
 
 def request_bytes(counters, j=None, L=1):

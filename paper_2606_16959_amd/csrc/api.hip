@@ -624,7 +624,7 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
             r.N = P.N;
             r.batch = (int)std::min<int64_t>(32768, batch - c0);
             r.by_rows = gp.prog.by_rows;
-            r.general = gp.prog.general;
+            r.level = gp.prog.level;
             r.steps = steps;
             for (int q = 0; q < kParts; ++q) r.part[q] = gp.prog.launches[gp.launch0[q]].block0;
             r.part[kParts] = gp.prog.launches[gp.launch0[kParts] - 1].block1;
@@ -674,7 +674,7 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
                 r.N = P.N;
                 r.batch = chunk;
                 r.by_rows = gp.prog.by_rows;
-                r.general = gp.prog.general;
+                r.level = gp.prog.level;
                 r.stage_diag = L.stage_diag >= 0 ? f->diag_of[L.stage_diag] : nullptr;
                 r.nrm2 = (renorm && s > 0 && l == l0) ? rec : nullptr;
                 r.norm_out = (renorm && l + 1 == l1) ? f->norm_dev : nullptr;

@@ -206,15 +206,27 @@ void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, in
             b.coef = (int)(dst.size() / (pairs ? 2 : 1));
             dst.insert(dst.end(), g.entries.begin(), g.entries.end());
             const bool rows = rho > (uint32_t)kGateMaxCoset || pairs;
-            out.general = out.general || rows || g.kmask != (1 << rho) - 1;
+            if (rows || g.kmask != (1 << rho) - 1) out.level = std::max(out.level, rho > (uint32_t)kGateMaxCoset ? 2 : 1);
             b.what = (rows ? kGateRows : kGateCosets) | rho << 4 | (uint32_t)g.form << 8 | nz << 12 |
                      (uint32_t)g.kmask << 16;
             if (rows) {
-                out.by_rows = true;
                 b.wtab = (int)out.words.size();
                 for (uint64_t v : loc) out.words.push_back((uint32_t)(63 - __builtin_clzll(v)));
                 for (uint64_t v : loc) out.words.push_back((uint32_t)v);
                 for (uint64_t v : g.basis) out.words.push_back((uint32_t)(63 - __builtin_clzll(v)));
+                if (rho <= (uint32_t)kGateMaxCoset) {
+                    out.by_rows = true;
+                } else {
+                    // 64 cosets per type: one type and one piece of the matrix per wave
+                    const uint32_t free_bits = (uint32_t)L.kt - rho, nt = (uint32_t)popc64(types);
+                    const bool lane = free_bits < nt + 6;
+                    const uint64_t held = lane ? 0 : types, holes = piv | held;
+                    b.number = (uint32_t)popc64(holes) | (uint32_t)popc64(held) << 8 |
+                               (free_bits - (uint32_t)popc64(held)) << 16 | (lane ? 1u << 24 : 0u);
+                    for (uint64_t p = holes; p; p &= p - 1) out.words.push_back((uint32_t)__builtin_ctzll(p));
+                    for (uint64_t p = held; p; p &= p - 1) out.words.push_back((uint32_t)__builtin_ctzll(p));
+                    for (uint64_t j = 0; j < 1ull << rho; j += 4) out.words.push_back((uint32_t)combine(loc, j));
+                }
                 out.blocks.push_back(b);
                 continue;
             }

@@ -45,8 +45,9 @@ constexpr int gate_lds_pos(int i, bool c128) {
 enum GateForm { kGateReal = 0, kGateComplex = 1, kGateRealD = 2, kGateComplexD = 3 };
 
 // kGateCosets: a thread holds whole cosets (rank up to kGateMaxCoset, forms
-// Real and RealD).  kGateRows: every thread sums its rows one by one, for
-// larger cosets and general entries.  kGateDiag: the product with a diagonal.
+// Real and RealD).  kGateRows: above that rank a thread sums a piece of a
+// coset's rows (below: units), up to it, for general entries, its rows one by
+// one.  kGateDiag: the product with a diagonal.
 enum GateKind { kGateCosets = 0, kGateDiag = 1, kGateRows = 2 };
 
 // One factor on the tile.
@@ -57,6 +58,13 @@ enum GateKind { kGateCosets = 0, kGateDiag = 1, kGateRows = 2 };
 // per type they are the same for all lanes of a wave, whose matrix then comes
 // through scalar loads.  With fewer cosets ntype is 0, type bits are no
 // holes, and each lane loads its own matrix.
+//
+// Units of a kGateRows block of rank above kGateMaxCoset: C consecutive rows of
+// one coset (C a power of two, the launch's choice).  A unit's number is, from
+// the low end, the coset's number without the types (tshift bits), which piece
+// of the coset, and the ntype type bits.  With at least 64 cosets per type the
+// types and pieces are the same for all lanes of a wave (the types are holes);
+// with fewer each lane loads its own entries and ntype is 0.
 struct alignas(64) GateBlock {     // one scalar load
     const void *diag;              // kGateDiag: N entries; forms with D: FP64 [2^rho][N >> rho],
                                    // element j of coset c (launch_phase_order)
@@ -65,7 +73,8 @@ struct alignas(64) GateBlock {     // one scalar load
     uint32_t basis[kGateMaxCoset]; // reduced masks of the coset, in tile-local index space
     int32_t coef;                  // first entry: table[type][i][j], or [type][j][i] with D
     int32_t ztab;                  // in `words`, nz type bits: pairs (local bit, row bit outside the tile)
-    int32_t wtab;                  // kGateRows: in `words`, rho local pivots, masks, row pivots
+    int32_t wtab;                  // kGateRows: in `words`, rho local pivots, masks, row pivots; with units
+                                   // also nhole holes, ntype type positions and the masks of elements 0, 4, ..
     uint32_t what;                 // kind, rho, form, nz: 4 bits each; kmask: 16
     uint32_t number;               // nhole, ntype, tshift: 8 bits each; lane, inside, direct: flags
     uint32_t rpivots;              // row bits of the pivots, ascending, one byte each
@@ -126,8 +135,9 @@ struct GateLaunch {
 };
 
 struct GateProgram {
-    bool by_rows = false;               // some block is of kind kGateRows
-    bool general = false;               // ... or some kmask lacks a bit
+    bool by_rows = false;               // some block sums row by row (twice the LDS)
+    int level = 0;                      // kernel instance: 2 for units, 1 for other kGateRows blocks or a kmask
+                                        // that lacks a bit
     std::vector<GateLaunch> launches;
     std::vector<GateBlock> blocks;      // diag filled at upload from dfactor
     std::vector<int> dfactor;           // factor whose D the block reads, or -1
@@ -159,7 +169,8 @@ struct GateRun {
     void *psi = nullptr;
     int64_t N = 0;
     int batch = 1;
-    bool by_rows = false, general = false;   // as GateProgram's
+    bool by_rows = false;          // as GateProgram's
+    int level = 0;
     const void *stage_diag = nullptr;
     const double *nrm2 = nullptr;
     double *norm_out = nullptr;    // partials of state b, tile t at [(b * tiles + t) * 4]

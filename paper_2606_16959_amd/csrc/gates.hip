@@ -27,6 +27,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "dev_common.h"
 #include "gate_plan.h"
@@ -49,7 +50,7 @@ struct GateArgs {
     const void *stage_diag;        // or null: multiplies the tile as it is loaded
     const double *nrm2;            // per-state squared norms to divide out, or null
     double *norm_out;              // or null: partials of state b, tile t at [(b * tiles + t) * 4]
-    int32_t by_rows;               // a block is of kind kGateRows (twice the LDS)
+    int32_t by_rows;               // a block sums row by row (twice the LDS)
     int32_t steps;                 // > 1 only when the tile is the whole state
     int32_t part[5];               // step part q applies blocks [part[q], part[q + 1])
 };
@@ -242,8 +243,8 @@ __device__ __forceinline__ void apply_cosets(const GateArgs &a, const GateBlock 
     }
 }
 
-// A kGateRows block: every row's sum over its coset goes to the second half
-// of LDS, then replaces the row.
+// A kGateRows block of rank up to kGateMaxCoset (general entries): every row's
+// sum over its coset goes to the second half of LDS, then replaces the row.
 template <typename R>
 __device__ __forceinline__ void apply_rows(const GateArgs &a, const GateBlock &B, C2<R> *lds, uint32_t base, int tid,
                                            int nt) {
@@ -305,6 +306,154 @@ __device__ __forceinline__ void apply_rows(const GateArgs &a, const GateBlock &B
     for (int i = tid; i < T; i += nt) lds[lds_pos<R>(i)] = lds[T + i];
 }
 
+// Sums of one unit (gate_plan.h), rows i0 .. i0 + C - 1 of the coset whose
+// element 0 sits at LDS position pos0: y[i] = sum_j M[i0 + i][j] x[j], j
+// ascending.  tab: the matrix's first entry; dp: D of the coset's element 0,
+// the elements `len` entries apart.  LANE: the entries depend on the lane.
+template <typename R, int C, int FORM, bool LANE>
+__device__ __forceinline__ void unit_sums(const GateArgs &a, const GateBlock &B, const C2<R> *lds, int pos0, int64_t tab, int i0,
+                                          g_d2 *dp, int64_t len, C2<R> (&y)[C]) {
+    constexpr bool PAIRS = FORM == kGateComplex || FORM == kGateComplexD, WITH_D = FORM == kGateRealD || FORM == kGateComplexD;
+    constexpr int E = PAIRS ? 2 : 1;                // reals of an entry
+    using M = typename std::conditional<WITH_D, double, R>::type;
+    // partners per round, whose entries are loaded at once: 64 scalar
+    // registers, or 32 vector registers where they differ between lanes
+    constexpr int FIT = (LANE ? 32 : 64) / (C * E * ((int)sizeof(M) / 4)), JB = FIT > 4 ? 4 : FIT < 1 ? 1 : FIT;
+    const int rho = B.rho(), dim = 1 << rho, kmask = B.kmask();
+    const uint32_t *w = a.words + B.wtab, *jm = w + 3 * rho + B.nhole() + B.ntype();
+    const int s0 = lds_pos<R>((int)uload(w[rho])), s1 = lds_pos<R>((int)uload(w[rho + 1]));
+    const M *m = reinterpret_cast<const M *>(WITH_D ? (const void *)a.coef64 : a.coef) + E * tab;
+#pragma unroll
+    for (int i = 0; i < C; ++i) y[i] = C2<R>{(R)0, (R)0};
+#pragma unroll 1
+    for (int j = 0; j < dim; j += JB) {
+        int pj = pos0 ^ lds_pos<R>((int)uload(jm[j >> 2]));
+        if (JB < 2) pj ^= (j & 1) ? s0 : 0;
+        if (JB < 4) pj ^= (j & 2) ? s1 : 0;
+        C2<R> x[JB];
+        d2v D[JB];
+        M e[C][JB][E];
+#pragma unroll
+        for (int q = 0; q < JB; ++q) {
+            x[q] = lds[pj ^ ((q & 1) ? s0 : 0) ^ ((q & 2) ? s1 : 0)];
+            if constexpr (WITH_D) D[q] = dp[(j + q) * len];
+        }
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+#pragma unroll
+            for (int q = 0; q < JB; ++q)
+#pragma unroll
+                for (int c = 0; c < E; ++c) {
+                    const M &v = m[E * (WITH_D ? (j + q) * dim + i0 + i : (i0 + i) * dim + j + q) + c];
+                    e[i][q][c] = LANE ? v : uload(v);
+                }
+#pragma unroll
+        for (int q = 0; q < JB; ++q) {
+            const bool odd = __builtin_popcount((j + q) & kmask) & 1;
+            if constexpr (FORM == kGateReal) {
+                const C2<R> xt = odd ? turn(x[q]) : x[q];
+#pragma unroll
+                for (int i = 0; i < C; ++i) {
+                    y[i].re = rfma(e[i][q][0], xt.re, y[i].re);
+                    y[i].im = rfma(e[i][q][0], xt.im, y[i].im);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < C; ++i) {
+                    C2<R> k;
+                    if constexpr (FORM == kGateComplex) k = C2<R>{e[i][q][0], e[i][q][1]};
+                    else if constexpr (FORM == kGateRealD)
+                        k = d_entry_typed<R>(e[i][q][0], ((__builtin_popcount((i0 + i) & kmask) & 1) != 0) != odd, D[q]);
+                    else k = d_entry<R>(e[i][q][0], e[i][q][1], D[q]);
+                    cfma(y[i], k, x[q]);
+                }
+            }
+        }
+    }
+    if constexpr (FORM == kGateReal)
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+            if (__builtin_popcount((i0 + i) & kmask) & 1) y[i] = unturn(y[i]);
+}
+
+// A kGateRows block of rank above kGateMaxCoset.  A thread has one unit: it
+// reads every element of its coset once from LDS for C rows and keeps the sums
+// in registers until all threads have read.
+//
+// What bounds it: the multiply-adds, 2^(rank + 1) per row, and at few tiles the
+// chain of partners (a scalar load of entries, an LDS read) of each wave.  C is
+// the rows a thread of the launch has, so that a unit needs no loop and a
+// partner's LDS read and its entries' scalar loads serve C rows.  Two steps of
+// a transverse-field chain, us: stored diagonals streamed / every row summed
+// alone / units: n = 12 complex64 budget 32 (rank 4) 97 / 310 / 57, budget 128
+// (rank 6) 267 / 910 / 114, budget 1024 (rank 9) 1490 / 5130 / 555; n = 18
+// complex128, 8 states, budget 128 740 / 3090 / 397; n = 22 complex64 budget
+// 128 4250 / 6050 / 637.
+template <typename R, int C>
+__device__ __forceinline__ void apply_units(const GateArgs &a, const GateBlock &B, C2<R> *lds, uint32_t base, int tid) {
+    constexpr int LC = C == 16 ? 4 : C == 8 ? 3 : 2;
+    const int rho = B.rho(), nhole = B.nhole(), ntype = B.ntype(), tshift = B.tshift(), nz = B.nz();
+    const uint32_t *w = a.words + B.wtab, *jm = w + 3 * rho + nhole + ntype;
+    const bool active = tid < (1 << a.kt) / C, lane = B.lane();
+    C2<R> y[C];
+    int pos = 0;
+    if (active) {
+        int rep = tid & ((1 << tshift) - 1);
+        for (int h = 0; h < nhole; ++h) {
+            const int low = (1 << uload(w[3 * rho + h])) - 1;
+            rep = ((rep & ~low) << 1) | (rep & low);
+        }
+        for (int t = 0; t < ntype; ++t)
+            rep |= ((tid >> (tshift + rho - LC + t)) & 1) << uload(w[3 * rho + nhole + t]);
+        int i0 = ((tid >> tshift) & ((1 << (rho - LC)) - 1)) << LC, type = 0;
+        for (int t = 0; t < nz; ++t)
+            type |= (int)(((rep & uload(a.words[B.ztab + 2 * t])) | (base & uload(a.words[B.ztab + 2 * t + 1]))) != 0) << t;
+        if (!lane) {
+            i0 = __builtin_amdgcn_readfirstlane(i0);
+            type = __builtin_amdgcn_readfirstlane(type);
+        }
+        const int64_t tab = B.coef + ((int64_t)type << (2 * rho));
+        g_d2 *dp = (g_d2 *)B.diag;
+        if (dp) {
+            uint32_t row = base | seg_deposit(a.in, a.nin, (uint32_t)rep);
+            for (int c = rho - 1; c >= 0; --c) {
+                const int rp = (int)uload(w[2 * rho + c]);
+                row = ((row >> rp >> 1) << rp) | (row & ((1u << rp) - 1));
+            }
+            dp += row;
+        }
+        const int64_t len = a.N >> rho;
+        const int pos0 = lds_pos<R>(rep);
+        pos = pos0 ^ lds_pos<R>((int)jm[i0 >> 2]);
+        const int form = B.form();
+        if (form == kGateReal) {
+            if (lane) unit_sums<R, C, kGateReal, true>(a, B, lds, pos0, tab, i0, dp, len, y);
+            else unit_sums<R, C, kGateReal, false>(a, B, lds, pos0, tab, i0, dp, len, y);
+        } else if (form == kGateRealD) {
+            if (lane) unit_sums<R, C, kGateRealD, true>(a, B, lds, pos0, tab, i0, dp, len, y);
+            else unit_sums<R, C, kGateRealD, false>(a, B, lds, pos0, tab, i0, dp, len, y);
+        } else if (form == kGateComplex) {
+            unit_sums<R, C, kGateComplex, true>(a, B, lds, pos0, tab, i0, dp, len, y);
+        } else {
+            unit_sums<R, C, kGateComplexD, true>(a, B, lds, pos0, tab, i0, dp, len, y);
+        }
+    }
+    __syncthreads();
+    if (active) {
+        int s[LC];
+#pragma unroll
+        for (int c = 0; c < LC; ++c) s[c] = lds_pos<R>((int)uload(w[rho + c]));
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            int p = pos;
+#pragma unroll
+            for (int c = 0; c < LC; ++c)
+                if ((i >> c) & 1) p ^= s[c];
+            lds[p] = y[i];
+        }
+    }
+}
+
 __device__ __forceinline__ GateBlock uload_block(const GateBlock &p) {
     GateBlock r;
     r.diag = uload(p.diag);
@@ -321,14 +470,16 @@ __device__ __forceinline__ GateBlock uload_block(const GateBlock &p) {
     return r;
 }
 
-// GENERAL: the program has kGateRows blocks or products whose entries are not
-// imaginary for every single flip; without them (transverse fields, XX + YY
-// bonds: most programs) the kernel is a third of the code.
-template <typename R, bool STREAM, bool GENERAL>
+// LEVEL 0 is for programs of cosets up to kGateMaxCoset whose entries are
+// imaginary for every single flip (transverse fields, XX + YY bonds: most
+// programs), a third of the code; 1 adds other real and general entries, 2
+// larger cosets.
+template <typename R, bool STREAM, int LEVEL>
 __global__ __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(4))) void gate_kernel(GateArgs a) {
     constexpr bool PAIR = sizeof(R) == 4;           // linear phases: two adjacent rows per 16-byte access
     constexpr int H = PAIR ? 2 : 1;
     constexpr int G = 8;                            // 16-byte accesses of a thread's linear rows
+    constexpr bool GENERAL = LEVEL > 0;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C2<R> *lds = reinterpret_cast<C2<R> *>(smem_raw);
     const int tid = threadIdx.x;
@@ -423,7 +574,14 @@ __global__ __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(4)
                         }
                     }
                 } else if constexpr (GENERAL) {
-                    apply_rows<R>(a, B, lds, base, fresh(), nt);
+                    // rows per thread: 16 or 8 of a full tile, at least 4
+                    if (B.rho() <= kGateMaxCoset) {
+                        apply_rows<R>(a, B, lds, base, fresh(), nt);
+                    } else if constexpr (LEVEL == 2) {
+                        if (PAIR && T >= 16 * nt) apply_units<R, PAIR ? 16 : 8>(a, B, lds, base, fresh());
+                        else if (T >= 8 * nt) apply_units<R, 8>(a, B, lds, base, fresh());
+                        else apply_units<R, 4>(a, B, lds, base, fresh());
+                    }
                 }
             }
         }
@@ -479,9 +637,9 @@ static std::mutex &gate_attr_mutex() {
     return m;
 }
 
-template <typename R, bool STREAM, bool GENERAL>
+template <typename R, bool STREAM, int LEVEL>
 static int gate_launch(GateArgs &a, void *stream) {
-    auto kern = gate_kernel<R, STREAM, GENERAL>;
+    auto kern = gate_kernel<R, STREAM, LEVEL>;
     const int T = 1 << a.kt;
     const size_t tile = (size_t)T * sizeof(C2<R>) * (a.by_rows ? 2 : 1), lds = tile < 256 ? 256 : tile;
     // every linear row has a thread (8 accesses of 16 bytes each); launches of
@@ -515,6 +673,13 @@ static int gate_launch(GateArgs &a, void *stream) {
     hipLaunchKernelGGL(kern, dim3(gx, (unsigned)a.batch, (unsigned)a.tiles / gx), dim3(nt), lds,
                        reinterpret_cast<hipStream_t>(stream), a);
     return (int)hipGetLastError();
+}
+
+template <typename R>
+static int gate_level(GateArgs &a, int level, bool stream_out, void *stream) {
+    if (level == 0) return stream_out ? gate_launch<R, true, 0>(a, stream) : gate_launch<R, false, 0>(a, stream);
+    if (level == 1) return stream_out ? gate_launch<R, true, 1>(a, stream) : gate_launch<R, false, 1>(a, stream);
+    return stream_out ? gate_launch<R, true, 2>(a, stream) : gate_launch<R, false, 2>(a, stream);
 }
 
 // The FP64 phases in the order the coset products read them: one thread per
@@ -585,13 +750,8 @@ int launch_gates(const GateLaunch &L, const GateTables &t, const GateRun &r, boo
     a.by_rows = r.by_rows;
     a.steps = r.steps;
     for (int q = 0; q < 5; ++q) a.part[q] = r.part[q];
-    if (r.general) {
-        if (c128) return stream_out ? gate_launch<double, true, true>(a, stream) : gate_launch<double, false, true>(a, stream);
-        return stream_out ? gate_launch<float, true, true>(a, stream) : gate_launch<float, false, true>(a, stream);
-    }
-    if (r.by_rows) return (int)hipErrorInvalidValue;
-    if (c128) return stream_out ? gate_launch<double, true, false>(a, stream) : gate_launch<double, false, false>(a, stream);
-    return stream_out ? gate_launch<float, true, false>(a, stream) : gate_launch<float, false, false>(a, stream);
+    if (r.by_rows && r.level < 1) return (int)hipErrorInvalidValue;
+    return c128 ? gate_level<double>(a, r.level, stream_out, stream) : gate_level<float>(a, r.level, stream_out, stream);
 }
 
 }  // namespace hs

@@ -1,0 +1,24 @@
+"""Units of the coset programs (factors of rank 4 to 10) walked on the host
+(tests/c/gate_unit_check.cpp).  Host code only."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_units_cover_their_tiles_and_equal_exact_rotations(tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    exe = str(tmp_path / "gate_unit_check")
+    csrc = os.path.join(ROOT, "paper_2606_16959_amd", "csrc")
+    cmd = [gxx, "-std=c++17", "-O2", "-I", os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "c", "gate_unit_check.cpp"),
+           os.path.join(csrc, "plan.cpp"), os.path.join(csrc, "gate_plan.cpp"), "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0, run.stdout[-2000:] + run.stderr[-2000:]
+    assert "units checked" in run.stdout

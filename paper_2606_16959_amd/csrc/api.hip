@@ -123,7 +123,7 @@ std::vector<int> part_sequence(const Plan &P, int part) {
 // (gate_plan.h).
 struct GatePlan {
     hs::GateProgram prog;
-    int launch0[kParts + 1] = {0, 0, 0, 0, 0};   // part q makes launches [launch0[q], launch0[q + 1])
+    int launch0[kParts] = {0}, launch1[kParts] = {0};   // part q makes launches [launch0[q], launch1[q])
     std::vector<hs::GateBlock> blocks;           // prog.blocks with their diagonals' addresses
     std::vector<float> coef32;
     std::vector<char> host;                      // the tables as uploaded; alive as long as the plan
@@ -292,7 +292,7 @@ int gate_tile_bits(int dtype, int64_t N, int batch) {
 // Uploads a program's tables in one copy; the host copy lives as long as the
 // plan, so the ordered copy is safe.
 hs_status upload_gates(hs_factors_s *h, GatePlan &gp, hipStream_t st) {
-    const hs::GateProgram &p = gp.prog;
+    hs::GateProgram &p = gp.prog;
     gp.blocks = p.blocks;
     for (size_t k = 0; k < gp.blocks.size(); ++k)
         gp.blocks[k].diag = p.dfactor[k] >= 0 ? h->diag_of[p.dfactor[k]] : nullptr;
@@ -321,6 +321,10 @@ hs_status upload_gates(hs_factors_s *h, GatePlan &gp, hipStream_t st) {
     gp.tab.words = reinterpret_cast<const uint32_t *>(base + off[1]);
     gp.tab.coef = base + off[2];
     gp.tab.coef64 = reinterpret_cast<const double *>(base + off[3]);
+    // what a launch needs stays: the launches, and `host` for the ordered copy
+    std::vector<double>().swap(gp.prog.coef);
+    std::vector<double>().swap(gp.prog.coef64);
+    std::vector<float>().swap(gp.coef32);
     return HS_OK;
 }
 
@@ -331,13 +335,16 @@ hs_status make_gate_plan(hs_factors_s *h, const PlanKey &key, bool loop, std::un
     std::unique_ptr<GatePlan> gp(new GatePlan());
     const int wlog = ilog2(std::max<int64_t>(2, w_min(h->dtype, key)));
     const int max_factors = !key.fuse ? 1 : key.max_fuse < hs::kMaxRun ? key.max_fuse : 0;
+    const int parts = P.joint < 0 ? 1 : kParts;     // without a joint factor every part is the plain step
+    std::map<int, hs::GateStep> made;
     std::vector<hs::GateStep> steps[kParts];
-    for (int q = 0; q < kParts; ++q) steps[q] = hs::gate_steps(P, part_sequence(P, q));
+    for (int q = 0; q < parts; ++q) steps[q] = hs::gate_steps(P, part_sequence(P, q), &made);
     auto form = [&](int kt, GatePlan &g) {
         g.prog = hs::GateProgram();
         for (int q = 0; q < kParts; ++q) {
-            g.launch0[q] = (int)g.prog.launches.size();
-            hs::gate_launches(P, steps[q], kt, wlog, max_factors, loop, g.prog);
+            g.launch0[q] = q < parts ? (int)g.prog.launches.size() : g.launch0[0];
+            if (q < parts) hs::gate_launches(P, steps[q], kt, wlog, max_factors, loop, g.prog);
+            g.launch1[q] = q < parts ? (int)g.prog.launches.size() : g.launch1[0];
         }
     };
     const int kt = gate_tile_bits(h->dtype, P.N, key.chunk);
@@ -351,10 +358,9 @@ hs_status make_gate_plan(hs_factors_s *h, const PlanKey &key, bool loop, std::un
         form(kt - 1, half);
         if (half.prog.launches.size() <= gp->prog.launches.size()) std::swap(*gp, half);
     }
-    gp->launch0[kParts] = (int)gp->prog.launches.size();
     // the looped form applies a part's blocks from one launch
     for (int q = 0; loop && q < kParts; ++q)
-        if (gp->launch0[q + 1] != gp->launch0[q] + 1) return fail(HS_EDEVICE, "looped coset program of several launches");
+        if (gp->launch1[q] != gp->launch0[q] + 1) return fail(HS_EDEVICE, "looped coset program of several launches");
     if (hs_status s = upload_gates(h, *gp, reinterpret_cast<hipStream_t>(stream))) {
         if (gp->dev) (void)hipFreeAsync(gp->dev, reinterpret_cast<hipStream_t>(stream));
         return s;
@@ -543,7 +549,7 @@ static hs_status build_device(hs_factors_s *h, void *stream) {
             le = hs::launch_construct(a, 1, P.N, c128, stream);
         } else if (dtab[k]) {
             le = hs::launch_phase_order(a.phase, static_cast<double *>(dtab[k]), P.N,
-                                        hs::gate_step(P, (int)k, 0).basis, stream);
+                                        hs::gate_basis(P, (int)k), stream);
         }
         if (le) { cleanup(); return hip_fail((hipError_t)le, "diagonal kernel"); }
         h->diag_of.push_back(dtab[k] ? dtab[k] : f.has_diag ? f.dev : nullptr);
@@ -626,8 +632,10 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
             r.by_rows = gp.prog.by_rows;
             r.level = gp.prog.level;
             r.steps = steps;
-            for (int q = 0; q < kParts; ++q) r.part[q] = gp.prog.launches[gp.launch0[q]].block0;
-            r.part[kParts] = gp.prog.launches[gp.launch0[kParts] - 1].block1;
+            for (int q = 0; q < kParts; ++q) {
+                r.first[q] = gp.prog.launches[gp.launch0[q]].block0;
+                r.last[q] = gp.prog.launches[gp.launch0[q]].block1;
+            }
             int e = hs::launch_gates(gp.prog.launches[0], gp.tab, r, c128, false, stream);
             if (e) return hip_fail((hipError_t)e, "whole-evolution kernel launch");
         }
@@ -647,7 +655,7 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
             // the step's last launch sums |y|^2 per tile: room for its partials
             size_t need = 0;
             for (int q = 0; q < kParts; ++q) {
-                const hs::GateLaunch &L = gp.prog.launches[gp.launch0[q + 1] - 1];
+                const hs::GateLaunch &L = gp.prog.launches[gp.launch1[q] - 1];
                 need = std::max(need, (size_t)chunk * (P.N / L.rows) * 4 * sizeof(double));
             }
             if (need > f->norm_bytes) {
@@ -666,7 +674,7 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
         for (int s = 0; s < steps; ++s) {
             const int part = steps == 1 ? kPartLone
                              : s == 0 ? kPartFirst : s == steps - 1 ? kPartLast : kPartMiddle;
-            const int l0 = gp.launch0[part], l1 = gp.launch0[part + 1];
+            const int l0 = gp.launch0[part], l1 = gp.launch1[part];
             for (int l = l0; l < l1; ++l) {
                 const hs::GateLaunch &L = gp.prog.launches[l];
                 hs::GateRun r;
@@ -678,8 +686,8 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
                 r.stage_diag = L.stage_diag >= 0 ? f->diag_of[L.stage_diag] : nullptr;
                 r.nrm2 = (renorm && s > 0 && l == l0) ? rec : nullptr;
                 r.norm_out = (renorm && l + 1 == l1) ? f->norm_dev : nullptr;
-                r.part[0] = L.block0;
-                r.part[1] = L.block1;
+                r.first[0] = L.block0;
+                r.last[0] = L.block1;
                 int e = hs::launch_gates(L, gp.tab, r, c128, streamed, stream);
                 if (e) return hip_fail((hipError_t)e, "coset kernel launch");
             }

@@ -68,6 +68,12 @@ std::vector<GateSeg> gate_segments(uint64_t mask) {
     return out;
 }
 
+std::vector<uint64_t> gate_basis(const Plan &P, int factor) {
+    std::vector<uint64_t> masks;
+    for (int k : P.factors[factor].terms) masks.push_back(P.terms[k].x);
+    return reduced_span(masks);
+}
+
 GateStep gate_step(const Plan &P, int factor, int pos) {
     const Factor &F = P.factors[factor];
     GateStep g;
@@ -76,40 +82,30 @@ GateStep gate_step(const Plan &P, int factor, int pos) {
     g.carries_d = F.has_diag;
     g.diag_only = F.terms.empty();
     if (g.diag_only) return g;
-    std::vector<uint64_t> masks;
-    for (int k : F.terms) masks.push_back(P.terms[k].x);
-    g.basis = reduced_span(masks);
-    for (uint64_t m : masks) g.flips |= m;
+    for (int k : F.terms) g.flips |= P.terms[k].x;
+    g.basis = gate_basis(P, factor);
     const int rho = (int)g.basis.size(), R = 1 << rho, K = 1 << F.bits.size();
     uint64_t support = 0;
     for (int q : F.bits) support |= 1ull << q;
     const uint64_t free_bits = support & ~g.pivots();
     for (int q : F.bits)
         if ((free_bits >> q) & 1) g.type_bits.push_back(q);
-    // the products, one per setting of the free support bits
+    // the products, one per setting of the free support bits; local indices are
+    // linear over XOR
     const int types = 1 << g.type_bits.size();
-    std::vector<std::complex<double>> M((size_t)types * R * R);
-    for (int t = 0; t < types; ++t) {
-        const uint64_t a0 = spread_bits((uint64_t)t, free_bits);
-        for (int i = 0; i < R; ++i)
-            for (int j = 0; j < R; ++j)
-                M[((size_t)t * R + i) * R + j] =
-                    F.L[pack_bits(a0 ^ combine(g.basis, i), support) * K + pack_bits(a0 ^ combine(g.basis, j), support)];
-    }
+    std::vector<int> el(R), ty(types);
+    for (int j = 0; j < R; ++j) el[j] = (int)pack_bits(combine(g.basis, j), support);
+    for (int t = 0; t < types; ++t) ty[t] = (int)pack_bits(spread_bits((uint64_t)t, free_bits), support);
+    auto at = [&](int t, int i, int j) { return F.L[(size_t)(ty[t] ^ el[i]) * K + (ty[t] ^ el[j])]; };
     // one parity of the flip that decides between real and imaginary entries
     // (unit flips first; every entry must agree)
-    auto kinds = [&](int m) {        // 1 real, 2 imaginary entries among the flips by m
-        int k = 0;
-        for (int t = 0; t < types; ++t)
-            for (int i = 0; i < R; ++i) {
-                const std::complex<double> v = M[((size_t)t * R + i) * R + (i ^ m)];
-                if (v.real() != 0.0) k |= 1;
-                if (v.imag() != 0.0) k |= 2;
+    std::vector<int> kd(R, 0);       // by flip: 1 real, 2 imaginary entries
+    for (int t = 0; t < types; ++t)
+        for (int i = 0; i < R; ++i)
+            for (int j = 0; j < R; ++j) {
+                const std::complex<double> v = at(t, i, j);
+                kd[i ^ j] |= (v.real() != 0.0 ? 1 : 0) | (v.imag() != 0.0 ? 2 : 0);
             }
-        return k;
-    };
-    std::vector<int> kd(R);
-    for (int m = 0; m < R; ++m) kd[m] = kinds(m);
     bool typed = false;
     for (int km = R - 1; km >= 0 && !typed; --km) {      // R <= 1024; R - 1 (every flip imaginary) fits most
         bool ok = true;
@@ -120,25 +116,38 @@ GateStep gate_step(const Plan &P, int factor, int pos) {
         }
     }
     g.form = typed ? (g.carries_d ? kGateRealD : kGateReal) : (g.carries_d ? kGateComplexD : kGateComplex);
+    std::vector<char> kap(R);
+    for (int j = 0; j < R; ++j) kap[j] = (char)(popc64(j & g.kmask) & 1);
+    auto out = std::make_shared<std::vector<double>>();
+    out->reserve((size_t)types * R * R * (typed ? 1 : 2));
     for (int t = 0; t < types; ++t)
-        for (int p = 0; p < R * R; ++p) {
-                const int i = g.carries_d ? p % R : p / R, j = g.carries_d ? p / R : p % R;
-                const std::complex<double> v = M[((size_t)t * R + i) * R + j];
+        for (int p = 0; p < R; ++p)
+            for (int q = 0; q < R; ++q) {
+                const int i = g.carries_d ? q : p, j = g.carries_d ? p : q;
+                const std::complex<double> v = at(t, i, j);
                 if (!typed) {
-                    g.entries.push_back(v.real());
-                    g.entries.push_back(v.imag());
-                    continue;
+                    out->push_back(v.real());
+                    out->push_back(v.imag());
+                } else if (kap[i] == kap[j]) {
+                    out->push_back(v.real());
+                } else {
+                    out->push_back(!g.carries_d && kap[i] ? -v.imag() : v.imag());
                 }
-                const int ki = popc64(i & g.kmask) & 1, kj = popc64(j & g.kmask) & 1;
-                if (ki == kj) g.entries.push_back(v.real());
-                else g.entries.push_back(!g.carries_d && ki ? -v.imag() : v.imag());
             }
+    g.entries = out;
     return g;
 }
 
-std::vector<GateStep> gate_steps(const Plan &P, const std::vector<int> &seq) {
+std::vector<GateStep> gate_steps(const Plan &P, const std::vector<int> &seq, std::map<int, GateStep> *made) {
+    std::map<int, GateStep> own;
+    if (!made) made = &own;
     std::vector<GateStep> out;
-    for (size_t pos = 0; pos < seq.size(); ++pos) out.push_back(gate_step(P, seq[pos], (int)pos));
+    for (size_t pos = 0; pos < seq.size(); ++pos) {
+        auto it = made->find(seq[pos]);
+        if (it == made->end()) it = made->emplace(seq[pos], gate_step(P, seq[pos], 0)).first;
+        out.push_back(it->second);
+        out.back().pos = (int)pos;
+    }
     return out;
 }
 
@@ -202,9 +211,13 @@ void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, in
             }
             std::vector<double> &dst = g.carries_d ? out.coef64 : out.coef;
             const bool pairs = g.form == kGateComplex || g.form == kGateComplexD;
-            while (dst.size() % 4) dst.push_back(0.0);
-            b.coef = (int)(dst.size() / (pairs ? 2 : 1));
-            dst.insert(dst.end(), g.entries.begin(), g.entries.end());
+            auto tab = out.coef_of.find(g.factor);        // a factor's entries are held once
+            if (tab == out.coef_of.end()) {
+                while (dst.size() % 4) dst.push_back(0.0);
+                tab = out.coef_of.emplace(g.factor, (int)(dst.size() / (pairs ? 2 : 1))).first;
+                dst.insert(dst.end(), g.entries->begin(), g.entries->end());
+            }
+            b.coef = tab->second;
             const bool rows = rho > (uint32_t)kGateMaxCoset || pairs;
             if (rows || g.kmask != (1 << rho) - 1) out.level = std::max(out.level, rho > (uint32_t)kGateMaxCoset ? 2 : 1);
             b.what = (rows ? kGateRows : kGateCosets) | rho << 4 | (uint32_t)g.form << 8 | nz << 12 |

@@ -14,6 +14,8 @@
 #pragma once
 
 #include <cstdint>
+#include <map>
+#include <memory>
 #include <vector>
 
 #include "hs_internal.h"
@@ -117,7 +119,7 @@ struct GateStep {
     std::vector<int> type_bits;    // support bits that are no pivots: they select the product
     int form = kGateReal;
     int kmask = 0;
-    std::vector<double> entries;   // [type][i][j] ([type][j][i] with D) as `form` keeps them, in FP64
+    std::shared_ptr<const std::vector<double>> entries;   // [type][i][j] ([type][j][i] with D) as `form` keeps them, in FP64
     uint64_t pivots() const {
         uint64_t p = 0;
         for (uint64_t v : basis) p |= 1ull << (63 - __builtin_clzll(v));
@@ -144,10 +146,13 @@ struct GateProgram {
     std::vector<uint32_t> words;
     std::vector<double> coef;           // forms Real and Complex (rounded to the dtype at upload)
     std::vector<double> coef64;         // forms RealD and ComplexD
+    std::map<int, int> coef_of;         // factor -> first entry
 };
 
+std::vector<uint64_t> gate_basis(const Plan &P, int factor);
 GateStep gate_step(const Plan &P, int factor, int pos);
-std::vector<GateStep> gate_steps(const Plan &P, const std::vector<int> &seq);
+// `made`: steps by factor that are at hand, completed
+std::vector<GateStep> gate_steps(const Plan &P, const std::vector<int> &seq, std::map<int, GateStep> *made = nullptr);
 
 // Launches for `steps`: consecutive steps share a launch while a tile of
 // 2^kt rows that holds the low wlog bits (rows in one run) holds every bit
@@ -175,7 +180,7 @@ struct GateRun {
     const double *nrm2 = nullptr;
     double *norm_out = nullptr;    // partials of state b, tile t at [(b * tiles + t) * 4]
     int steps = 1;
-    int32_t part[5] = {0, 0, 0, 0, 0};
+    int32_t first[4] = {0, 0, 0, 0}, last[4] = {0, 0, 0, 0};   // step part q applies blocks [first[q], last[q])
 };
 int launch_gates(const GateLaunch &L, const GateTables &t, const GateRun &r, bool c128, bool stream_out, void *stream);
 

@@ -52,7 +52,7 @@ struct GateArgs {
     double *norm_out;              // or null: partials of state b, tile t at [(b * tiles + t) * 4]
     int32_t by_rows;               // a block sums row by row (twice the LDS)
     int32_t steps;                 // > 1 only when the tile is the whole state
-    int32_t part[5];               // step part q applies blocks [part[q], part[q + 1])
+    int32_t first[4], last[4];     // step part q applies blocks [first[q], last[q])
 };
 
 template <typename R>
@@ -550,8 +550,8 @@ __global__ __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(4)
     {
         for (int s = 0; s < a.steps; ++s) {
             const int part = a.steps == 1 ? 0 : s == 0 ? 1 : s == a.steps - 1 ? 3 : 2;
-            const int k1 = a.part[part + 1];
-            for (int k = a.part[part]; k < k1; ++k) {
+            const int k1 = a.last[part];
+            for (int k = a.first[part]; k < k1; ++k) {
                 const GateBlock B = uload_block(a.blocks[k]);
                 __syncthreads();
                 if (B.kind() == kGateCosets) {
@@ -749,7 +749,10 @@ int launch_gates(const GateLaunch &L, const GateTables &t, const GateRun &r, boo
     a.norm_out = r.norm_out;
     a.by_rows = r.by_rows;
     a.steps = r.steps;
-    for (int q = 0; q < 5; ++q) a.part[q] = r.part[q];
+    for (int q = 0; q < 4; ++q) {
+        a.first[q] = r.first[q];
+        a.last[q] = r.last[q];
+    }
     if (r.by_rows && r.level < 1) return (int)hipErrorInvalidValue;
     return c128 ? gate_level<double>(a, r.level, stream_out, stream) : gate_level<float>(a, r.level, stream_out, stream);
 }

@@ -695,6 +695,11 @@ hs_status hs_dia_evolve(hs_dia U, void *psi, int batch, int steps, void *stream)
     const int64_t N = U->N;
     const size_t sc = U->elem();
     const int nd = (int)U->offs.size();
+    if (nd == 0) {                      // every string cancelled: U = 0
+        DHIP(hipMemsetAsync(psi, 0, (size_t)batch * N * sc, st), "hipMemsetAsync(state)");
+        DHIP(hipStreamSynchronize(st), "hipStreamSynchronize");
+        return HS_OK;
+    }
     if (hs::loop_fits(N, nd, U->dtype == HS_C128)) {
         // every step in one launch wherever a workgroup holds the operator:
         // at its largest, 1024 complex128 rows of 21 diagonals or 512 of 48, a
@@ -800,7 +805,7 @@ hs_status hs_taylor_evolve(hs_dia H, void *psi, int batch, double dt, int K, int
         std::string msg;
         if (!hs::device_range_ok(psi, (size_t)batch * H->N * H->elem(), "state", msg)) return dfail(HS_EINVAL, msg);
     }
-    if (steps == 0) return HS_OK;
+    if (steps == 0 || H->offs.empty()) return HS_OK;      // H = 0: the polynomial is the identity
     hipStream_t st = S(stream);
     const int64_t N = H->N;
     const size_t sc = H->elem();

@@ -844,6 +844,7 @@ static int rows_launch(const TileArgs &a, int batch, bool horner, void *stream) 
 
 template <typename R>
 static int product_launch(const TileArgs &a, int batch, bool horner, void *stream) {
+    if (a.nd < 1) return (int)hipErrorInvalidValue;      // both kernels read a first descriptor
     if ((int64_t)a.N * batch <= kRowsMax) return rows_launch<R>(a, batch, horner, stream);
     return tile_dispatch<R>(a, batch, horner, stream);
 }

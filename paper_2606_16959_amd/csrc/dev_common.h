@@ -37,6 +37,9 @@ __device__ __forceinline__ C2<R> cscale(C2<R> v, R s) {
     return C2<R>{v.re * s, v.im * s};
 }
 
+template <typename R>
+__device__ __forceinline__ bool finite(C2<R> v) { return __builtin_isfinite(v.re) && __builtin_isfinite(v.im); }
+
 // nrm2 points at the squared norm of state 0 inside [batch][4] reduction
 // records (state b at nrm2[4 b]); null means no rescaling.
 template <typename R>

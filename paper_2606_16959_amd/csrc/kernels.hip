@@ -415,7 +415,10 @@ __global__ __launch_bounds__(NT) void dia_tile_kernel(TileArgs a) {
 // The same product for operators too small to give every compute unit a tile:
 // one thread per row and state, partners read from cache, the coefficients and
 // partners of kRowsAhead diagonals loaded before any is used.  The sum runs in
-// the same order with the same multiply-adds, so the values are the same.
+// the same order with the same multiply-adds, so the values are the same.  A
+// sum that is not finite is taken again without its zero coefficients
+// (nonzero_row), so that an infinite amplitude reaches the rows coupled to it
+// and no others.
 //
 // What bounds it: a handful of waves issuing one after the other, so the inner
 // loop is kept to two loads and the multiply-adds per diagonal: buffer loads
@@ -446,6 +449,21 @@ __device__ __forceinline__ void buffer_get(__amdgpu_buffer_rsrc_t b, int i, C2<d
 __device__ __forceinline__ void buffer_get(__amdgpu_buffer_rsrc_t b, int i, C2<float> &v) {
     const u2v w = __builtin_amdgcn_raw_buffer_load_b64(b, i * 8, 0, 0);
     __builtin_memcpy(&v, &w, 8);
+}
+
+// Row r of A x over the nonzero coefficients alone: diagonal j has the offset
+// off(j) and the entries ptr(j), x(p) is amplitude p.
+template <typename R, typename FO, typename FP, typename FX>
+__device__ __forceinline__ C2<R> nonzero_row(int r, int N, int nd, FO off, FP ptr, FX x) {
+    C2<R> acc{(R)0, (R)0};
+#pragma unroll 1
+    for (int j = 0; j < nd; ++j) {
+        const int d = off(j);
+        if (r + d < 0 || r + d >= N) continue;
+        const C2<R> c = ld1_cached(reinterpret_cast<const C2<R> *>(ptr(j)), r + (d < 0 ? d : 0));
+        if (c.re != (R)0 || c.im != (R)0) cfma(acc, c, x(r + d));
+    }
+    return acc;
 }
 
 template <typename R, bool HORNER>
@@ -482,6 +500,10 @@ __global__ __launch_bounds__(kRowsThreads) void dia_rows_kernel(TileArgs a) {
         for (int u = 0; u < kRowsAhead; ++u) cfma(acc, c[u], v[u]);
     }
     if (r >= N) return;
+    if (!finite(acc))
+        acc = nonzero_row<R>(
+            r, N, nd, [&](int j) { return uload(a.desc[j].off); }, [&](int j) { return uload(a.desc[j].ptr); },
+            [&](int p) { return ld1_cached(x, p); });
     if (HORNER) {
         C2<R> y = reinterpret_cast<const C2<R> *>(a.x0)[(int64_t)blockIdx.y * a.stride + r];
         cfma(y, C2<R>{(R)a.alpha_re, (R)a.alpha_im}, acc);
@@ -498,7 +520,8 @@ __global__ __launch_bounds__(kRowsThreads) void dia_rows_kernel(TileArgs a) {
 // 192 of 256 of one of 512), so a step is one LDS read and the multiply-adds
 // per diagonal and two barriers.  Zeros on both sides of the state stand for
 // partners outside it.  The sum runs in the order and with the multiply-adds
-// of the row kernel, so the values are the same.
+// of the row kernel, and the steps are taken again as there when a sum is not
+// finite, so the values are the same.
 //
 // What bounds it: the LDS reads, 16 KiB per diagonal and step of 1024 complex128
 // rows.  A step of 21 diagonals there takes 1.17 us where a launch of the row
@@ -514,7 +537,9 @@ template <typename R, int ND, int NT>
 __global__ __launch_bounds__(NT) void dia_loop_kernel(LoopArgs a) {
     constexpr int E = kLoopRowsPer<R>;
     __shared__ C2<R> lds[3 * E * NT];                        // zeros, the state, zeros
+    __shared__ int again;                                    // some sum is not finite
     const int N = a.N, nt = blockDim.x, tid = threadIdx.x;
+    if (tid == 0) again = 0;
     C2<R> *x = reinterpret_cast<C2<R> *>(a.x) + (int64_t)blockIdx.x * N;
     for (int i = tid; i < 3 * N; i += nt) lds[i] = i >= N && i < 2 * N ? x[i - N] : C2<R>{(R)0, (R)0};
     C2<R> c[ND][E];
@@ -551,6 +576,31 @@ __global__ __launch_bounds__(NT) void dia_loop_kernel(LoopArgs a) {
         for (int e = 0; e < E; ++e)
             if (tid + e * nt < N) lds[row[e]] = acc[e];
         __syncthreads();
+    }
+    // an amplitude that is not finite makes every row whose diagonals reach it
+    // so, down to the last step: the steps again, from x, if any is left
+    bool bad = false;
+#pragma unroll
+    for (int e = 0; e < E; ++e) bad = bad || !finite(lds[row[e]]);
+    if (bad) again = 1;
+    __syncthreads();
+    if (again) {
+        for (int i = tid; i < N; i += nt) lds[N + i] = x[i];
+        __syncthreads();
+#pragma unroll 1
+        for (int s = 0; s < a.steps; ++s) {
+            C2<R> acc[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                acc[e] = nonzero_row<R>(
+                    row[e] - N, N, a.nd, [&](int j) { return a.off[j]; }, [&](int j) { return a.ptr[j]; },
+                    [&](int p) { return lds[N + p]; });
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (tid + e * nt < N) lds[row[e]] = acc[e];
+            __syncthreads();
+        }
     }
 #pragma unroll
     for (int e = 0; e < E; ++e)

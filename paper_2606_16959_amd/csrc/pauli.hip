@@ -80,6 +80,31 @@ struct MaskRec {
     }
 };
 
+// Row r of H x over the nonzero coefficients alone, for sums that are not
+// finite: an infinite amplitude reaches the rows coupled to it and no others.
+template <typename R>
+__device__ __forceinline__ C2<R> pauli_nonzero_row(const PauliArgs &a, const C2<R> *x, uint32_t r) {
+    C2<R> acc{(R)0, (R)0};
+    if (a.diag) {
+        const C2<R> d = ld1_cached(reinterpret_cast<const C2<R> *>(a.diag), (int)r);
+        if (d.re != (R)0 || d.im != (R)0) cfma(acc, d, ld1_cached(x, (int)r));
+    }
+#pragma unroll 1
+    for (int k = 0; k < a.nmask; ++k) {
+        const PauliMask &m = a.masks[k];
+        int q = 0;
+        for (int t = 0; t < m.rank; ++t) q |= (__popc(r & m.z[t]) & 1) << t;
+        const C2<R> c = reinterpret_cast<const C2<R> *>(a.tab)[m.tab + q], v = ld1_cached(x, (int)(r ^ m.m));
+        if (c.im != (R)0) {
+            cfma(acc, c, v);
+        } else if (c.re != (R)0) {
+            acc.re = rfma(c.re, v.re, acc.re);
+            acc.im = rfma(c.re, v.im, acc.im);
+        }
+    }
+    return acc;
+}
+
 // 16 bytes at a byte offset from a uniform base
 __device__ __forceinline__ void get16(const char *base, uint32_t off, C2<float> (&v)[2]) {
     const f4v w = *(g_f4 *)((const __attribute__((address_space(1))) char *)base + off);
@@ -181,6 +206,9 @@ void pauli_tile_kernel(PauliArgs a) {
     C2<R> *y = reinterpret_cast<C2<R> *>(a.y) + (int64_t)b * a.N + base;
     const C2<R> al{(R)a.alpha_re, (R)a.alpha_im};
 #pragma unroll
+    for (int e = 0; e < G * H; ++e)
+        if (!finite(acc[e])) acc[e] = pauli_nonzero_row(a, x, row(e));
+#pragma unroll
     for (int p = 0; p < G; ++p) {
         C2<R> v[2];
         if constexpr (PAIR) ld2(x0, at(p), v[0], v[1]);
@@ -219,6 +247,7 @@ __global__ __launch_bounds__(kPauliRowThreads) void pauli_rows_kernel(PauliArgs 
             if (k0 + u < a.nmask)
                 rec[u].add(acc, a.masks[k0 + u], table, [&](int) { return (uint32_t)r; }, [&](int) { return v[u]; });
     }
+    if (!finite(acc[0])) acc[0] = pauli_nonzero_row(a, x, (uint32_t)r);
     C2<R> y = v0;
     cfma(y, C2<R>{(R)a.alpha_re, (R)a.alpha_im}, acc[0]);
     reinterpret_cast<C2<R> *>(a.y)[(int64_t)blockIdx.y * a.N + r] = y;

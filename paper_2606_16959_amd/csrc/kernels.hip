@@ -662,9 +662,11 @@ __global__ void scale_kernel(C2<R> *psi, int64_t N, const double *nrm2) {
 // What bounds it: HBM for states beyond the last-level cache, which are read
 // with streaming loads (n = 24, a complex64 against a complex128 pair of
 // states, 768 MiB: 120 us = 6.7 TB/s in the kernel, 167 us a call; through the
-// caches 186 us a call).  A norm has one stream of loads per thread and few
-// waves for a lone state, so it keeps four in flight (n = 26 complex64 186 ->
-// 123 us a call); the overlap's two streams were slower that way (182 -> 190).
+// caches 186 us a call).  A norm of complex64 states has one stream of 8-byte
+// loads per thread and few waves for a lone state, so it keeps four in flight
+// (n = 26 181 -> 124 us a call); with 16-byte loads four are slower (n = 25,
+// two complex128 states 233 against 200 us), as are the overlap's two streams
+// (182 against 190).
 
 // One amplitude through a streaming load (STREAM) or the caches; callers' states
 // are aligned to their real type only.
@@ -692,7 +694,7 @@ __global__ __launch_bounds__(256) void reduce_partial_kernel(const void *A, cons
     double s[4] = {0.0, 0.0, 0.0, 0.0};
     const int64_t step = (int64_t)G * 256;
     int64_t i = blockIdx.x * 256 + threadIdx.x;
-    if (!DOT)
+    if (!DOT && sizeof(TA) == 4)                             // complex64 norms: four loads in flight
         for (; i + 3 * step < N; i += 4 * step) {
             C2<TA> u[4];
 #pragma unroll

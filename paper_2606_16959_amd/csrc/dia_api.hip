@@ -825,30 +825,29 @@ hs_status hs_taylor_evolve(hs_dia H, void *psi, int batch, double dt, int K, int
     // an operator made from Pauli strings is applied by its X-masks
     const hs::PauliForm *form = H->form && !H->form->masks.empty() && N >= 2 ? H->form.get() : nullptr;
     hs::PauliArgs pa{};
-    std::vector<float> tab32;
-    std::vector<hs::PauliMask> masks;
+    std::vector<char> tables;                            // masks, then coefficients in the dtype: one upload
     if (form) {
-        hs::PauliMask *dm = nullptr;
-        masks = form->masks;
+        std::vector<hs::PauliMask> masks = form->masks;
+        const size_t nc = form->tab.size(), at = masks.size() * sizeof(hs::PauliMask);
+        tables.resize(at + nc * sc);
         if (c128) {
-            std::complex<double> *dt64 = nullptr;
-            DHIP(tmp.up(form->tab, &dt64), "mask table");
-            pa.tab = dt64;
+            std::memcpy(tables.data() + at, form->tab.data(), nc * sc);
         } else {
-            for (const auto &v : form->tab) {
-                tab32.push_back((float)v.real());
-                tab32.push_back((float)v.imag());
+            float *t = reinterpret_cast<float *>(tables.data() + at);
+            for (size_t k = 0; k < nc; ++k) {
+                t[2 * k] = (float)form->tab[k].real();
+                t[2 * k + 1] = (float)form->tab[k].imag();
             }
             for (auto &k : masks) {
                 const float c[4] = {(float)k.c[0], (float)k.c[1], (float)k.c[2], (float)k.c[3]};
                 std::memcpy(k.c, c, sizeof c);
             }
-            float *dt32 = nullptr;
-            DHIP(tmp.up(tab32, &dt32), "mask table");
-            pa.tab = dt32;
         }
-        DHIP(tmp.up(masks, &dm), "mask table");
-        pa.masks = dm;
+        std::memcpy(tables.data(), masks.data(), at);
+        char *dev = nullptr;
+        DHIP(tmp.up(tables, &dev), "mask tables");
+        pa.masks = reinterpret_cast<const hs::PauliMask *>(dev);
+        pa.tab = dev + at;
         pa.host_masks = form->m.data();
         pa.nmask = (int32_t)form->masks.size();
         pa.N = N;

@@ -204,14 +204,15 @@ hs_status hs_factor_copy_diagonal(hs_factors f, int k, int j, long long start, l
  * runs of four of those tiles' row windows; s = c = 0 is the natural order.
  * Either output may be null. */
 hs_status hs_factor_storage(hs_factors f, int k, int *split_bit, int *chunk_bits);
-/* Bytes of device memory an evolution of `batch` states needs: the stored
- * diagonals (Eq. 6: N - |d| entries per diagonal, each start aligned to 256
- * bytes), the exponentials of D (16 bytes per row) of each factor that carries
- * it, the caller's states and the library's workspace (reduction partials, and
- * room for one more batch of states where a factor flips bits too far apart
- * for a tile of consecutive bits).  Used for admission by HBM
- * footprint in a served loop.  Counts the handle's dtype (complex64 for a
- * handle from hs_plan, which has none yet). */
+/* Bytes of device memory that building the handle and an evolution of `batch`
+ * states take at most: the stored diagonals (Eq. 6: N - |d| entries per
+ * diagonal, each start aligned to 256 bytes), room for the exponentials of D (at
+ * least 16 bytes per row) of each factor that carries it, the coset matrices and
+ * the build's tables, the caller's states and the library's workspace
+ * (reduction partials, and a reserve of one more batch of states where a factor
+ * flips bits too far apart for a tile of consecutive bits).  An upper bound, for
+ * admission by HBM footprint in a served loop.  Counts the handle's dtype
+ * (complex64 for a handle from hs_plan, which has none yet). */
 hs_status hs_footprint(hs_factors f, int batch, size_t *bytes);
 /* The same figure for the handle built with `dtype`: element size, diagonal
  * alignment and the dtype's own tile limits (a complex128 tile holds half

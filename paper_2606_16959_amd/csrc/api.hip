@@ -503,21 +503,26 @@ static hs_status build_device(hs_factors_s *h, void *stream) {
         return hip_fail(e, "table upload");
     }
     char *dt = static_cast<char *>(tab);
-    // one FP64 phase table exp(-i h E(x)) per distinct time step h of the
-    // factors that carry D
+    // D of a factor with further terms stays with the handle, in the order its
+    // coset product reads; a factor that is D alone is rounded from a temporary
+    // FP64 table in natural order, one per distinct time step
     std::map<double, double *> phases;
-    for (auto &f : P.factors) {
-        if (!f.has_diag || phases.count(f.dt)) continue;
-        double *phase = nullptr;
-        if ((e = hipMallocAsync(reinterpret_cast<void **>(&phase), (size_t)P.N * 16, st)) != hipSuccess) {
-            cleanup();
-            return hip_fail(e, "phase table setup");
+    for (size_t k = 0; k < P.factors.size(); ++k) {
+        const hs::Factor &f = P.factors[k];
+        if (!f.has_diag || (f.terms.empty() && phases.count(f.dt))) continue;
+        double *phase = static_cast<double *>(dtab[k]);
+        if (f.terms.empty()) {
+            if ((e = hipMallocAsync(reinterpret_cast<void **>(&phase), (size_t)P.N * 16, st)) != hipSuccess) {
+                cleanup();
+                return hip_fail(e, "phase table setup");
+            }
+            temps.push_back(phase);
+            phases[f.dt] = phase;
         }
-        temps.push_back(phase);
         int le = hs::launch_phase_table(P.N, (int)P.diag.size(), reinterpret_cast<uint64_t *>(dt + at_zm),
-                                        reinterpret_cast<double *>(dt + at_cf), f.dt, phase, stream);
+                                        reinterpret_cast<double *>(dt + at_cf), f.dt,
+                                        f.terms.empty() ? std::vector<uint64_t>() : hs::gate_basis(P, (int)k), phase, stream);
         if (le) { cleanup(); return hip_fail((hipError_t)le, "phase table kernel"); }
-        phases[f.dt] = phase;
     }
     for (size_t k = 0; k < P.factors.size(); ++k) {
         const hs::Factor &f = P.factors[k];
@@ -536,7 +541,9 @@ static hs_status build_device(hs_factors_s *h, void *stream) {
             a.lb = f.bits.empty() ? 0 : f.bits[0];
             a.contiguous = f.bits.empty() || f.bits.back() - f.bits.front() + 1 == (int)f.bits.size();
         }
-        a.phase = f.has_diag ? phases[f.dt] : nullptr;
+        if (f.has_diag) a.phase = f.terms.empty() ? phases[f.dt] : static_cast<double *>(dtab[k]);
+        if (f.has_diag && !f.terms.empty())
+            for (uint64_t m : hs::gate_basis(P, (int)k)) a.basis[a.rho++] = (uint32_t)m;
         a.perm_s = f.perm_s;
         a.perm_c = f.perm_c;
         int le = hs::launch_construct(a, (int)f.offs.size(), P.N, c128, stream);
@@ -547,11 +554,8 @@ static hs_status build_device(hs_factors_s *h, void *stream) {
             a.elem_off = reinterpret_cast<uint64_t *>(dt + at_zero);
             a.perm_s = a.perm_c = 0;
             le = hs::launch_construct(a, 1, P.N, c128, stream);
-        } else if (dtab[k]) {
-            le = hs::launch_phase_order(a.phase, static_cast<double *>(dtab[k]), P.N,
-                                        hs::gate_basis(P, (int)k), stream);
+            if (le) { cleanup(); return hip_fail((hipError_t)le, "diagonal kernel"); }
         }
-        if (le) { cleanup(); return hip_fail((hipError_t)le, "diagonal kernel"); }
         h->diag_of.push_back(dtab[k] ? dtab[k] : f.has_diag ? f.dev : nullptr);
     }
     e = hipStreamSynchronize(st);
@@ -872,17 +876,29 @@ static size_t footprint_bytes(const Plan &P, int dtype, int batch) {
         }
     }
     total += (size_t)batch * P.N * sc;                                // the states
-    for (const auto &F : P.factors)
-        if (F.has_diag) total += (size_t)P.N * 2 * sc;                // D in FP64 beside the factor's diagonals
-                                                                      // (complex128: and the table it comes from)
+    for (size_t k = 0; k < P.factors.size(); ++k) {
+        const Factor &F = P.factors[k];
+        // D in FP64 beside the factor's diagonals, or the table that a factor of
+        // D alone is built from: 16 N (complex128 states have room for two)
+        if (F.has_diag) total += (size_t)P.N * 2 * sc;
+        // its matrices in the coset tables, at most a complex value per entry;
+        // a batch with a remainder has a program of its own for it
+        if (!F.terms.empty())
+            total += ((size_t)2 << (F.bits.size() + hs::gate_basis(P, (int)k).size())) * (F.has_diag ? 8 : sc / 2) *
+                     (batch > HS_MAX_BATCH && batch % HS_MAX_BATCH ? 2 : 1);
+    }
+    for (int k : P.seq)                                               // and its blocks, in every step part
+        total += (P.joint < 0 ? 1 : kParts) * (sizeof(hs::GateBlock) + 4 * (64 + ((size_t)1 << hs::gate_basis(P, k).size()) / 4)) *
+                 (batch > HS_MAX_BATCH && batch % HS_MAX_BATCH ? 2 : 1);
     bool open = false;                                                // a factor no closed tile holds
     for (const auto &F : P.factors)
         if (F.xmask_union && !geometry(F.xlb, F.xhb, P.n, tile_rows_max(dtype, 1, P.N)).ok) open = true;
-    if (open) total += (size_t)std::min(batch, HS_MAX_BATCH) * P.N * sc;   // its scratch state
+    if (open) total += (size_t)std::min(batch, HS_MAX_BATCH) * P.N * sc;   // a reserve, as for a scratch state
     // per-tile norm partials when renormalising (tiles of at least 64 rows)
     total += (size_t)std::min(batch, HS_MAX_BATCH) * (size_t)(P.N / 64 + 1) * 4 * sizeof(double);
     total += sizeof(double) * ((size_t)HS_MAX_BATCH * hs::kReduceBlocks * 4 + HS_MAX_BATCH * 4);
-    total += 64 * 1024;                                               // descriptors, flag
+    for (const auto &F : P.factors) total += F.L.size() * 16;         // local unitaries while building
+    total += 64 * 1024;                                               // the build's other tables, flag
     return total;
 }
 

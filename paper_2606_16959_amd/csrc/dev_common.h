@@ -152,6 +152,24 @@ template <typename V>
 __device__ __forceinline__ V uload(const V &p) {
     return *(const __attribute__((address_space(4))) V *)&p;
 }
+
+// Where GateBlock::diag keeps the exponential of row x: entry j * (N >> rho) + c
+// is element j (its pivot bits) of the coset of the reduced masks `basis`
+// whose first row, the pivot bits taken out, is c.
+__device__ __forceinline__ int64_t coset_index(uint32_t x, int rho, const uint32_t *basis, int64_t N) {
+    uint32_t c = x, j = 0;
+    for (int k = 0; k < rho; ++k)
+        if ((x >> (31 - __builtin_clz(basis[k]))) & 1u) {
+            j |= 1u << k;
+            c ^= basis[k];
+        }
+    for (int k = rho - 1; k >= 0; --k) {
+        const int q = 31 - __builtin_clz(basis[k]);
+        c = ((c >> q >> 1) << q) | (c & ((1u << q) - 1));
+    }
+    return (int64_t)j * (N >> rho) + c;
+}
+
 // wave64 butterfly sum (fixed order)
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll

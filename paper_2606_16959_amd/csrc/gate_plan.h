@@ -69,7 +69,7 @@ enum GateKind { kGateCosets = 0, kGateDiag = 1, kGateRows = 2 };
 // with fewer each lane loads its own entries and ntype is 0.
 struct alignas(64) GateBlock {     // one scalar load
     const void *diag;              // kGateDiag: N entries; forms with D: FP64 [2^rho][N >> rho],
-                                   // element j of coset c (launch_phase_order)
+                                   // element j of coset c (coset_index)
     uint64_t holes;                // ascending local positions, one byte each
     uint32_t tpos;                 // local position of type bit t: byte t
     uint32_t basis[kGateMaxCoset]; // reduced masks of the coset, in tile-local index space
@@ -183,11 +183,6 @@ struct GateRun {
     int32_t first[4] = {0, 0, 0, 0}, last[4] = {0, 0, 0, 0};   // step part q applies blocks [first[q], last[q])
 };
 int launch_gates(const GateLaunch &L, const GateTables &t, const GateRun &r, bool c128, bool stream_out, void *stream);
-
-// FP64 phase table in the order GateBlock::diag holds it: entry j * (N >> rho) + c
-// belongs to element j of the coset (reduced masks `basis`) whose first row,
-// its pivot bits taken out, is c.
-int launch_phase_order(const double *phase, double *out, int64_t N, const std::vector<uint64_t> &basis, void *stream);
 
 // Segments that deposit consecutive index bits into the set bits of `mask`.
 std::vector<GateSeg> gate_segments(uint64_t mask);

@@ -682,48 +682,6 @@ static int gate_level(GateArgs &a, int level, bool stream_out, void *stream) {
     return stream_out ? gate_launch<R, true, 2>(a, stream) : gate_launch<R, false, 2>(a, stream);
 }
 
-// The FP64 phases in the order the coset products read them: one thread per
-// row x, element j (its pivot bits) of the coset whose first row is x with
-// the masks of j taken out.
-struct PhaseOrderArgs {
-    const d2v *phase;
-    d2v *out;
-    int64_t N;
-    int32_t rho;
-    uint32_t basis[HS_MAX_SUPPORT];
-};
-__global__ void phase_order_kernel(PhaseOrderArgs a) {
-    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < a.N; x += (int64_t)gridDim.x * blockDim.x) {
-        uint32_t c = (uint32_t)x, j = 0;
-        for (int k = 0; k < a.rho; ++k) {
-            const int q = 31 - __builtin_clz(a.basis[k]);
-            if (((uint32_t)x >> q) & 1u) {
-                j |= 1u << k;
-                c ^= a.basis[k];
-            }
-        }
-        for (int k = a.rho - 1; k >= 0; --k) {
-            const int q = 31 - __builtin_clz(a.basis[k]);
-            c = ((c >> q >> 1) << q) | (c & ((1u << q) - 1));
-        }
-        a.out[(int64_t)j * (a.N >> a.rho) + c] = a.phase[x];
-    }
-}
-
-int launch_phase_order(const double *phase, double *out, int64_t N, const std::vector<uint64_t> &basis, void *stream) {
-    if (basis.size() > HS_MAX_SUPPORT) return (int)hipErrorInvalidValue;
-    PhaseOrderArgs a{};
-    a.phase = reinterpret_cast<const d2v *>(phase);
-    a.out = reinterpret_cast<d2v *>(out);
-    a.N = N;
-    a.rho = (int32_t)basis.size();
-    for (size_t k = 0; k < basis.size(); ++k) a.basis[k] = (uint32_t)basis[k];
-    const int64_t g = (N + 255) / 256;
-    hipLaunchKernelGGL(phase_order_kernel, dim3((unsigned)(g < (1 << 16) ? g : (1 << 16))), dim3(256), 0,
-                       reinterpret_cast<hipStream_t>(stream), a);
-    return (int)hipGetLastError();
-}
-
 int launch_gates(const GateLaunch &L, const GateTables &t, const GateRun &r, bool c128, bool stream_out, void *stream) {
     GateArgs a{};
     if (L.in.size() > (size_t)kGateSegs || L.out.size() > (size_t)kGateSegs) return (int)hipErrorInvalidValue;

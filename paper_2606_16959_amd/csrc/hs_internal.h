@@ -106,7 +106,9 @@ struct ConstructArgs {
     const int64_t *offs;     // [nd]
     const uint64_t *elem_off;// [nd]
     const double *L;         // K*K interleaved complex
-    const double *phase;     // N interleaved complex, or null
+    const double *phase;     // D, N interleaved complex entries in the order of coset_index, or null
+    int32_t rho;             // masks of that order (0: natural)
+    uint32_t basis[HS_MAX_SUPPORT];
     int32_t N;
     int32_t K;
     uint32_t smask;
@@ -118,8 +120,10 @@ struct ConstructArgs {
 };
 
 // launchers (kernels.hip); all return hipError_t as int
+// D = exp(-i dt E(x)) in the order of the reduced masks `basis` (coset_index;
+// none: natural)
 int launch_phase_table(int64_t N, int nz, const uint64_t *zm, const double *cf, double dt,
-                       double *out, void *stream);
+                       const std::vector<uint64_t> &basis, double *out, void *stream);
 int launch_construct(const ConstructArgs &a, int nd, int64_t max_len, bool c128, void *stream);
 // dst[k] = entry start + k of a diagonal of length len stored in the order
 // (s, c) (perm_pos), for k < count: the natural order of a stored range

@@ -17,18 +17,26 @@ namespace hs {
 
 // ------------------------------------------------------------ construction
 
-// E(x) = sum_k c_k (-1)^{popcount(x & z_k)};  out[x] = exp(-i dt E(x)), FP64.
-__global__ void phase_table_kernel(int64_t N, int nz, const uint64_t *__restrict__ zm,
-                                   const double *__restrict__ cf, double dt,
-                                   double *__restrict__ out) {
-    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < N;
+// E(x) = sum_k c_k (-1)^{popcount(x & z_k)};  out[coset_index(x)] = exp(-i dt E(x)), FP64.
+struct PhaseArgs {
+    int64_t N;
+    int nz, rho;
+    const uint64_t *zm;
+    const double *cf;
+    double dt;
+    double *out;
+    uint32_t basis[HS_MAX_SUPPORT];
+};
+__global__ void phase_table_kernel(PhaseArgs a) {
+    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < a.N;
          x += (int64_t)gridDim.x * blockDim.x) {
         double E = 0.0;
-        for (int k = 0; k < nz; ++k) E += cf[k] * ((__popcll((uint64_t)x & zm[k]) & 1) ? -1.0 : 1.0);
+        for (int k = 0; k < a.nz; ++k) E += a.cf[k] * ((__popcll((uint64_t)x & a.zm[k]) & 1) ? -1.0 : 1.0);
         double s, c;
-        sincos(-dt * E, &s, &c);
-        out[2 * x] = c;
-        out[2 * x + 1] = s;
+        sincos(-a.dt * E, &s, &c);
+        const int64_t at = coset_index((uint32_t)x, a.rho, a.basis, a.N);
+        a.out[2 * at] = c;
+        a.out[2 * at + 1] = s;
     }
 }
 
@@ -67,7 +75,8 @@ __global__ void construct_kernel(ConstructArgs a) {
             vi = a.L[2 * e + 1];
         }
         if (a.phase && (vr != 0.0 || vi != 0.0)) {
-            const C2<double> t = cmul_d(vr, vi, a.phase[2 * p], a.phase[2 * p + 1]);
+            const int64_t at = coset_index((uint32_t)p, a.rho, a.basis, a.N);
+            const C2<double> t = cmul_d(vr, vi, a.phase[2 * at], a.phase[2 * at + 1]);
             vr = t.re;
             vi = t.im;
         }
@@ -778,9 +787,18 @@ static inline int grid_for(int64_t n, int per_block, int cap) {
 }
 
 int launch_phase_table(int64_t N, int nz, const uint64_t *zm, const double *cf, double dt,
-                       double *out, void *stream) {
-    hipLaunchKernelGGL(phase_table_kernel, dim3(grid_for(N, 256, 1 << 20)), dim3(256), 0, S(stream),
-                       N, nz, zm, cf, dt, out);
+                       const std::vector<uint64_t> &basis, double *out, void *stream) {
+    if (basis.size() > HS_MAX_SUPPORT) return (int)hipErrorInvalidValue;
+    PhaseArgs a{};
+    a.N = N;
+    a.nz = nz;
+    a.rho = (int)basis.size();
+    a.zm = zm;
+    a.cf = cf;
+    a.dt = dt;
+    a.out = out;
+    for (size_t k = 0; k < basis.size(); ++k) a.basis[k] = (uint32_t)basis[k];
+    hipLaunchKernelGGL(phase_table_kernel, dim3(grid_for(N, 256, 1 << 20)), dim3(256), 0, S(stream), a);
     return (int)hipGetLastError();
 }
 

@@ -375,7 +375,7 @@ def sweep(torch, steps, warmup, passes=3):
 
     variants = []
     for name, env in SWEEP:
-        launches = with_env(env, lambda: f.step_launches(1))   # the plan for this setting
+        launches = with_env(env, lambda: f.evolve_launches(1))   # the plan for this setting
         per = launch_bytes(desc, launches, N, 1, 8)
         variants.append({"name": name, "env": env, "launches": len(launches),
                          "bytes": sum(per), "ms": []})
@@ -448,7 +448,7 @@ def other_workloads(torch, steps=10, warmup=2, pool=None):
         elem = 16 if dtype == "c128" else 8
         f = hs.build_factors(H.strings, H.coeffs, H.n, run["t"], run["steps"], run["budget"], dtype=dtype)
         B = run["batch"]
-        launches = f.step_launches(B)
+        launches = f.evolve_launches(B, renorm=renorm)
         per = launch_bytes(f.describe(), launches, 1 << H.n, B, elem)
         psi = torch.from_numpy(np.ascontiguousarray(ws.workload_states(cfg, npd))).cuda()
         for _ in range(warmup):
@@ -532,7 +532,7 @@ def complex128_leg(torch, H, psi0, ref, ref_steps, state_c64, steps_total, budge
     import paper_2606_16959_amd as hs
     N = 1 << H.n
     f = hs.build_factors(H.strings, H.coeffs, H.n, 1.0, steps_total, budget, dtype="c128")
-    launches = f.step_launches(1)
+    launches = f.evolve_launches(1)
     per = launch_bytes(f.describe(), launches, N, 1, 16)
     psi = torch.from_numpy(psi0.astype(np.complex128)).cuda()
     hs.evolve(f, psi, warmup)
@@ -623,7 +623,7 @@ def higher_order_leg(torch, steps=10, warmup=3):
         f = hs.build_factors(H.strings, H.coeffs, H.n, run["t"], run["steps"], run["budget"],
                              dtype="c64", order=order)
         desc = f.describe()
-        parts = {p: launch_bytes(desc, f.step_launches(1, part=p), N, 1, 8, f.part_sequence(p, desc))
+        parts = {p: launch_bytes(desc, f.evolve_launches(1, part=p), N, 1, 8, f.part_sequence(p, desc))
                  for p in (1, 2, 3)}
         nbytes = sum(parts[1]) + (steps - 2) * sum(parts[2]) + sum(parts[3])
         n_launch = len(parts[1]) + (steps - 2) * len(parts[2]) + len(parts[3])
@@ -718,7 +718,7 @@ def one_workload_leg(torch, name, dtype, steps=5, warmup=2, batch=None):
     elem = 16 if dtype == "c128" else 8
     B = batch or run["batch"]
     f = hs.build_factors(H.strings, H.coeffs, H.n, run["t"], run["steps"], run["budget"], dtype=dtype)
-    launches = f.step_launches(B)
+    launches = f.evolve_launches(B)
     per = moved_bytes(f.describe(), len(launches), 1 << H.n, B, elem)
     states = ws.workload_states(name, npd)
     psi = torch.from_numpy(np.ascontiguousarray(np.resize(states, (B, states.shape[1])))).cuda()
@@ -782,7 +782,7 @@ def _csv_rows(d, pattern):
 
 
 def summarize_leg_profiles(leg_output, trace_dir, counter_dirs, out_name, command):
-    """Per-launch summary of the DIA tile kernel from rocprofv3 output of a
+    """Per-launch summary of the step kernel from rocprofv3 output of a
     `bench.py --leg workload` run: durations from the kernel trace, and from
     each counter run (one directory per pass) the per-dispatch counter values,
     averaged per launch position of a step.  FETCH_SIZE and WRITE_SIZE (KiB)
@@ -1183,7 +1183,7 @@ def main():
     f = hs.build_factors(H.strings, H.coeffs, H.n, t, steps_total, budget, dtype="c64")
     build_s = time.perf_counter() - tb
     desc = f.describe()
-    launches = f.step_launches(1, fuse=not args.no_fuse)
+    launches = f.evolve_launches(1, fuse=not args.no_fuse, renorm=args.renorm)
     per_launch = launch_bytes(desc, launches, N, 1, 8)
     step_bytes = sum(per_launch)
     log(f"factors={f.n_factors} launches/step={len(launches)} bytes/step={step_bytes / 1e9:.2f} GB build={build_s:.2f}s")

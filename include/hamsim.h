@@ -222,9 +222,9 @@ hs_status hs_footprint_dtype(hs_factors f, int batch, hs_dtype dtype, size_t *by
  * *n_launches receives its length; entry i holds the factors at positions
  * [first_factor[i], first_factor[i] + n_factors[i]) of the part's factor
  * sequence (arrays of `cap` entries, may be NULL to query the count) that one
- * tile of the batch's rows is closed under.  It is what a launch per closed
- * tile of stored diagonals would be; hs_evolve takes the states of a batch
- * tile by tile and may need fewer launches.
+ * tile of the batch's rows is closed under: what a launch per closed tile of
+ * stored diagonals would be.  hs_evolve takes the states of a batch tile by
+ * tile and its launches differ (hs_evolve_launches).
  * `part` selects the step: 0 a lone step (the sequence of hs_step_sequence),
  * and of an evolution of several steps 1 the first (s_0 .. s_{L-2} J),
  * 2 a middle one (s_1 .. s_{L-2} J), 3 the last (s_1 .. s_{L-1}), with J the
@@ -232,9 +232,15 @@ hs_status hs_footprint_dtype(hs_factors f, int batch, hs_dtype dtype, size_t *by
  * Batches above HS_MAX_BATCH repeat the list per chunk. */
 hs_status hs_step_launches(hs_factors f, int batch, unsigned flags, int part, int *n_launches,
                            int *first_factor, int *n_factors, int cap);
-/* Sets *violated to 1 if an evolution met a nonzero coefficient that couples
- * rows of different tiles.  Tiles are formed from the masks the coefficients
- * come from, so it stays 0; syncs. */
+/* The launches hs_evolve makes for one step of `batch` states with `flags`:
+ * outputs and `part` as hs_step_launches.  A step of a small state evolved
+ * whole, or of one diagonal factor without HS_RENORM, is one entry; one launch
+ * then applies every step of the call. */
+hs_status hs_evolve_launches(hs_factors f, int batch, unsigned flags, int part, int *n_launches,
+                             int *first_factor, int *n_factors, int cap);
+/* Sets *violated to 1 if a program that hs_evolve formed for this handle leaves
+ * out a nonzero entry of a factor's local unitary, because it couples rows of
+ * different cosets or tiles (checked where the program is formed); syncs. */
 hs_status hs_check(hs_factors f, void *stream, int *violated);
 /* Release a handle.  Device memory is returned stream-ordered on the build
  * stream; work that uses the factors on other streams must have completed. */

@@ -125,15 +125,24 @@ class Factors:
         return out
 
     def step_launches(self, batch: int = 1, fuse: bool = True, part: int = 0) -> list:
-        """[(first, n_factors)] of the launches of one Trotter step: positions
-        in the part's factor sequence (:meth:`part_sequence`)."""
-        lib = _lib.load()
+        """[(first, n_factors)] of the fusion list of one Trotter step: positions
+        in the part's factor sequence (:meth:`part_sequence`) that one closed
+        tile of stored diagonals holds.  Evolutions launch
+        :meth:`evolve_launches`."""
+        return self._launch_list(_lib.load().hs_step_launches, batch, 0 if fuse else HS_NO_FUSE, part)
+
+    def evolve_launches(self, batch: int = 1, fuse: bool = True, part: int = 0, renorm: bool = False) -> list:
+        """[(first, n_factors)] of the launches :func:`evolve` makes for one
+        Trotter step; one entry where one launch applies all steps."""
+        flags = (0 if fuse else HS_NO_FUSE) | (HS_RENORM if renorm else 0)
+        return self._launch_list(_lib.load().hs_evolve_launches, batch, flags, part)
+
+    def _launch_list(self, query, batch, flags, part):
         n = ctypes.c_int()
-        flags = 0 if fuse else HS_NO_FUSE
-        _lib.check(lib.hs_step_launches(self._h, batch, flags, part, n, None, None, 0))
+        _lib.check(query(self._h, batch, flags, part, n, None, None, 0))
         first = (ctypes.c_int * max(1, n.value))()
         cnt = (ctypes.c_int * max(1, n.value))()
-        _lib.check(lib.hs_step_launches(self._h, batch, flags, part, n, first, cnt, n.value))
+        _lib.check(query(self._h, batch, flags, part, n, first, cnt, n.value))
         return [(first[i], cnt[i]) for i in range(n.value)]
 
     def part_sequence(self, part: int = 0, desc: dict | None = None) -> list:

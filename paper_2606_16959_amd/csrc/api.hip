@@ -138,7 +138,6 @@ struct hs_factors_s {
     bool built = false;
     int dtype = HS_C64;
     int device = 0;
-    int *viol_dev = nullptr;
     double *work_dev = nullptr;      // [8][G][4] partials, then [8][4] records
     double *norm_dev = nullptr;      // per-tile norm partials of the step's last launch, on demand
     size_t norm_bytes = 0;
@@ -329,11 +328,10 @@ hs_status upload_gates(hs_factors_s *h, GatePlan &gp, hipStream_t st) {
 }
 
 // The coset programs of every step part for one plan key, or (loop) of a
-// whole small state.
-hs_status make_gate_plan(hs_factors_s *h, const PlanKey &key, bool loop, std::unique_ptr<GatePlan> &out, void *stream) {
-    const Plan &P = h->plan;
+// whole small state, on the host.
+std::unique_ptr<GatePlan> form_gate_plan(const Plan &P, int dtype, const PlanKey &key, bool loop) {
     std::unique_ptr<GatePlan> gp(new GatePlan());
-    const int wlog = ilog2(std::max<int64_t>(2, w_min(h->dtype, key)));
+    const int wlog = ilog2(std::max<int64_t>(2, w_min(dtype, key)));
     const int max_factors = !key.fuse ? 1 : key.max_fuse < hs::kMaxRun ? key.max_fuse : 0;
     const int parts = P.joint < 0 ? 1 : kParts;     // without a joint factor every part is the plain step
     std::map<int, hs::GateStep> made;
@@ -347,9 +345,9 @@ hs_status make_gate_plan(hs_factors_s *h, const PlanKey &key, bool loop, std::un
             g.launch1[q] = q < parts ? (int)g.prog.launches.size() : g.launch1[0];
         }
     };
-    const int kt = gate_tile_bits(h->dtype, P.N, key.chunk);
+    const int kt = gate_tile_bits(dtype, P.N, key.chunk);
     form(kt, *gp);
-    if (!loop && kt > (h->dtype == HS_C128 ? 11 : 12)) {
+    if (!loop && kt > (dtype == HS_C128 ? 11 : 12)) {
         // half the tile where it needs no more launches: four workgroups share
         // a CU instead of two and overlap each other's phases better (n = 25
         // lattice 508 -> 457 us, MaxCut n = 24 with 8 states 1715 -> 1579 us a
@@ -358,6 +356,12 @@ hs_status make_gate_plan(hs_factors_s *h, const PlanKey &key, bool loop, std::un
         form(kt - 1, half);
         if (half.prog.launches.size() <= gp->prog.launches.size()) std::swap(*gp, half);
     }
+    return gp;
+}
+
+// The same on the device.
+hs_status make_gate_plan(hs_factors_s *h, const PlanKey &key, bool loop, std::unique_ptr<GatePlan> &out, void *stream) {
+    std::unique_ptr<GatePlan> gp = form_gate_plan(h->plan, h->dtype, key, loop);
     // the looped form applies a part's blocks from one launch
     for (int q = 0; loop && q < kParts; ++q)
         if (gp->launch1[q] != gp->launch0[q] + 1) return fail(HS_EDEVICE, "looped coset program of several launches");
@@ -377,6 +381,15 @@ hs_status make_gate_plan(hs_factors_s *h, const PlanKey &key, bool loop, std::un
 int64_t whole_max_rows(int dtype) {
     const int lim = dtype == HS_C128 ? hs::kWholeRowsC128 : hs::kWholeRowsC64;
     return env_int("HAMSIM_WHOLE_MAX_ROWS", 4096, 0, lim);
+}
+
+bool evolves_whole(const Plan &P, int dtype, bool renorm, bool fuse) {
+    return !renorm && fuse && P.N <= whole_max_rows(dtype);
+}
+
+// A step that is one diagonal factor, without renormalisation: one pass.
+bool evolves_lone_diagonal(const Plan &P, bool renorm) {
+    return P.joint < 0 && !renorm && P.seq.size() == 1 && P.factors[P.seq[0]].terms.empty();
 }
 
 hs_status check_handle(hs_factors f) {
@@ -438,7 +451,6 @@ static hs_status build_device(hs_factors_s *h, void *stream) {
         if (f.has_diag && !(f.terms.empty() && f.perm_s == 0))
             pieces.push_back({(size_t)P.N * (f.terms.empty() ? sc : 16), &dtab[k]});
     }
-    pieces.push_back({sizeof(int), reinterpret_cast<void **>(&h->viol_dev)});
     pieces.push_back({sizeof(double) * ((size_t)HS_MAX_BATCH * hs::kReduceBlocks * 4 + HS_MAX_BATCH * 4),
                       reinterpret_cast<void **>(&h->work_dev)});
     size_t sum = 0;
@@ -458,7 +470,6 @@ static hs_status build_device(hs_factors_s *h, void *stream) {
             h->owned.push_back(*q.where);
         }
     }
-    HS_HIP(hipMemsetAsync(h->viol_dev, 0, sizeof(int), st), "hipMemsetAsync(flag)");
 
     // every host table in one upload: Z masks and coefficients of the diagonal
     // terms, then per factor offsets, element offsets and the local unitary
@@ -611,7 +622,7 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
     const bool c128 = f->dtype == HS_C128;
     const bool fuse = !(flags & HS_NO_FUSE);
     const bool renorm = (flags & HS_RENORM) != 0;
-    if (P.joint < 0 && !renorm && P.seq.size() == 1 && P.factors[P.seq[0]].terms.empty()) {
+    if (evolves_lone_diagonal(P, renorm)) {
         // a step that is one diagonal factor: all steps in one pass (the
         // same multiplications, one step after the other, per entry)
         for (int c0 = 0; c0 < batch; c0 += HS_MAX_BATCH) {
@@ -623,7 +634,7 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
         }
         return HS_OK;
     }
-    if (!renorm && fuse && P.N <= whole_max_rows(f->dtype)) {
+    if (evolves_whole(P, f->dtype, renorm, fuse)) {
         // a small state: the whole evolution of every state in one launch
         if (!f->whole)
             if (hs_status s = make_gate_plan(f, plan_key(1, true), true, f->whole, stream)) return s;
@@ -865,6 +876,39 @@ hs_status hs_step_launches(hs_factors f, int batch, unsigned flags, int part, in
     return HS_OK;
 }
 
+hs_status hs_evolve_launches(hs_factors f, int batch, unsigned flags, int part, int *n_launches, int *first_factor,
+                             int *n_factors, int cap) {
+    if (hs_status s = check_handle(f)) return s;
+    if (!f->built) return fail(HS_EINVAL, "handle was planned, not built");
+    if (batch < 1 || !n_launches) return fail(HS_EINVAL, "batch >= 1 and an output are required");
+    if (part < 0 || part >= kParts) return fail(HS_EINVAL, "part must be 0..3");
+    if (flags & ~(unsigned)(HS_RENORM | HS_NO_FUSE)) return fail(HS_EINVAL, "unknown evolve flag");
+    const Plan &P = f->plan;
+    const bool fuse = !(flags & HS_NO_FUSE), renorm = (flags & HS_RENORM) != 0;
+    std::vector<std::pair<int, int>> out;
+    if (evolves_lone_diagonal(P, renorm) || evolves_whole(P, f->dtype, renorm, fuse)) {
+        out.push_back({0, (int)part_sequence(P, part).size()});
+    } else {
+        std::lock_guard<std::mutex> lock(f->mu);
+        const PlanKey key = plan_key(std::min(HS_MAX_BATCH, batch), fuse);
+        auto it = f->plans.find(key);
+        std::unique_ptr<GatePlan> formed;
+        if (it == f->plans.end()) formed = form_gate_plan(P, f->dtype, key, false);
+        const GatePlan &gp = formed ? *formed : *it->second;
+        for (int l = gp.launch0[part]; l < gp.launch1[part]; ++l)
+            out.push_back({gp.prog.launches[l].first, gp.prog.launches[l].count});
+    }
+    *n_launches = (int)out.size();
+    if (first_factor && n_factors) {
+        if (cap < (int)out.size()) return fail(HS_EINVAL, "output too small");
+        for (size_t i = 0; i < out.size(); ++i) {
+            first_factor[i] = out[i].first;
+            n_factors[i] = out[i].second;
+        }
+    }
+    return HS_OK;
+}
+
 static size_t footprint_bytes(const Plan &P, int dtype, int batch) {
     const size_t sc = elem_bytes(dtype);
     size_t total = 0;
@@ -898,7 +942,7 @@ static size_t footprint_bytes(const Plan &P, int dtype, int batch) {
     total += (size_t)std::min(batch, HS_MAX_BATCH) * (size_t)(P.N / 64 + 1) * 4 * sizeof(double);
     total += sizeof(double) * ((size_t)HS_MAX_BATCH * hs::kReduceBlocks * 4 + HS_MAX_BATCH * 4);
     for (const auto &F : P.factors) total += F.L.size() * 16;         // local unitaries while building
-    total += 64 * 1024;                                               // the build's other tables, flag
+    total += 64 * 1024;                                               // the build's other tables
     return total;
 }
 
@@ -920,11 +964,11 @@ hs_status hs_footprint_dtype(hs_factors f, int batch, hs_dtype dtype, size_t *by
 hs_status hs_check(hs_factors f, void *stream, int *violated) {
     if (hs_status s = check_handle(f)) return s;
     if (!f->built || !violated) return fail(HS_EINVAL, "built handle and output required");
-    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    int v = 0;
-    HS_HIP(hipMemcpyAsync(&v, f->viol_dev, sizeof(int), hipMemcpyDeviceToHost, st), "hipMemcpyAsync(flag)");
-    HS_HIP(hipStreamSynchronize(st), "hipStreamSynchronize");
-    *violated = v;
+    HS_HIP(hipStreamSynchronize(reinterpret_cast<hipStream_t>(stream)), "hipStreamSynchronize");
+    std::lock_guard<std::mutex> lock(f->mu);
+    bool closed = !f->whole || f->whole->prog.closed;
+    for (const auto &kv : f->plans) closed = closed && kv.second->prog.closed;
+    *violated = closed ? 0 : 1;
     return HS_OK;
 }
 

@@ -90,6 +90,12 @@ GateStep gate_step(const Plan &P, int factor, int pos) {
     const uint64_t free_bits = support & ~g.pivots();
     for (int q : F.bits)
         if ((free_bits >> q) & 1) g.type_bits.push_back(q);
+    // every nonzero entry couples rows of one coset
+    std::vector<char> span(K, 0);
+    for (int j = 0; j < R; ++j) span[pack_bits(combine(g.basis, j), support)] = 1;
+    for (int a = 0; a < K; ++a)
+        for (int b = 0; b < K; ++b)
+            if (!span[a ^ b] && F.L[(size_t)a * K + b] != 0.0) g.closed = false;
     // the products, one per setting of the free support bits; local indices are
     // linear over XOR
     const int types = 1 << g.type_bits.size();
@@ -174,6 +180,8 @@ void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, in
             ++j;
         }
         GateLaunch L;
+        L.first = (int)i;
+        L.count = (int)(j - i);
         uint64_t tile = (need | ((1ull << w) - 1)) & all;
         for (int q = 0; q < P.n && popc64(tile) < kt; ++q) tile |= 1ull << q;
         L.tile = tile;
@@ -184,6 +192,7 @@ void gate_launches(const Plan &P, const std::vector<GateStep> &steps, int kt, in
         L.block0 = (int)out.blocks.size();
         for (size_t q = i; q < j; ++q) {
             const GateStep &g = steps[q];
+            out.closed = out.closed && g.closed && (g.flips & ~tile) == 0;
             if (g.diag_only && q == i && !loop) {
                 L.stage_diag = g.factor;
                 continue;

@@ -117,6 +117,7 @@ struct GateStep {
     std::vector<uint64_t> basis;   // reduced masks by ascending highest bit (the pivots): ascending
                                    // coset coordinates are ascending rows
     std::vector<int> type_bits;    // support bits that are no pivots: they select the product
+    bool closed = true;            // the cosets hold every nonzero entry of the local unitary
     int form = kGateReal;
     int kmask = 0;
     std::shared_ptr<const std::vector<double>> entries;   // [type][i][j] ([type][j][i] with D) as `form` keeps them, in FP64
@@ -128,6 +129,7 @@ struct GateStep {
 };
 
 struct GateLaunch {
+    int first = 0, count = 0;      // positions of its steps
     uint64_t tile = 0;             // row bits of the tile
     int kt = 0;                    // log2 of its rows
     int64_t rows = 0;
@@ -140,6 +142,7 @@ struct GateProgram {
     bool by_rows = false;               // some block sums row by row (twice the LDS)
     int level = 0;                      // kernel instance: 2 for units, 1 for other kGateRows blocks or a kmask
                                         // that lacks a bit
+    bool closed = true;                 // no entry couples rows of different cosets or tiles
     std::vector<GateLaunch> launches;
     std::vector<GateBlock> blocks;      // diag filled at upload from dfactor
     std::vector<int> dfactor;           // factor whose D the block reads, or -1

@@ -393,6 +393,10 @@ hs_status hs_taylor_steps(hs_dia H, double t, double theta, void *stream, int *s
 /* psi <- p_K(-i dt H)^steps psi for `batch` device states ([batch][N], of
  * H's dtype, 16-byte aligned), 1 <= K <= 64.  In place; library scratch of
  * two states per chunk of HS_MAX_BATCH (one for K = 1), stream-ordered.
+ * An operator from hs_dia_from_pauli (or its complex64 copy) is applied by its
+ * X-masks: a row sums its main diagonal and then the masks in descending
+ * order; other operators sum their diagonals in ascending-offset order, so the
+ * two can differ in rounding.
  * The state is checked before anything else, also when steps is 0.
  * Synchronises `stream`. */
 hs_status hs_taylor_evolve(hs_dia H, void *psi, int batch, double dt, int K, int steps, void *stream);

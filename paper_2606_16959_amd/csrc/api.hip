@@ -171,8 +171,8 @@ namespace {
 // The fusion list of every step part (host only): greedy fusion extends a run
 // while the union of coupling hulls still fits one closed tile of the batch's
 // rows with row runs of at least w_min elements.  hs_step_launches reports it
-// and choose_storage_order reads it; hs_evolve launches gate programs, which
-// need no more launches than this list has entries.
+// and choose_storage_order reads it; hs_evolve launches coset programs
+// (form_gate_plan).
 void form_runs(const Plan &P, int dtype, const PlanKey &key, std::vector<Run> (&all)[kParts]) {
     const int n = P.n;
     const int batch = key.chunk;
@@ -234,13 +234,9 @@ void form_runs(const Plan &P, int dtype, const PlanKey &key, std::vector<Run> (&
 // HAMSIM_PERM_CHUNK_WINDOWS (default 4) of that launch's windows of W
 // consecutive rows, or HAMSIM_PERM_CHUNK_BYTES when that is set (nonzero):
 // neighbouring tiles, which run at the same time on other compute units, then
-// read each level's chunk together.  On the n = 26 TFIM step (complex64) the
-// launch whose levels lie 2 MiB apart took 3.14 ms in natural order, 2.84 ms
-// with 256-byte chunks and 2.64 ms with chunks of four windows (8 windows:
-// 2.92 ms).  Levels 32 KiB apart gained 3% the same way (2.63 -> 2.55 ms), but
-// launches of other batch sizes, which read the same storage through tiles of
-// another shape, lost up to 2% (8 states of the n = 24 MaxCut step), so the
-// default leaves them in natural order.
+// read each level's chunk together.  The order serves a launch that streams the
+// stored diagonals; hs_evolve reads none of them, so here it costs a natural-
+// order copy of a permuted lone diagonal and a gather in host copies.
 void choose_storage_order(Plan &P, int dtype) {
     for (auto &f : P.factors) f.perm_s = f.perm_c = 0;
     const int min_bytes = env_int("HAMSIM_PERM_MIN_BYTES", 1 << 20, 0, 1 << 30);
@@ -280,7 +276,7 @@ void choose_storage_order(Plan &P, int dtype) {
 
 // log2 rows of an evolution's largest tiles: 64 KiB of LDS, so that two
 // workgroups share a CU, halved (down to 1024 rows) while the launch would
-// have fewer than 256 of them, one per compute unit.  make_gate_plan takes
+// have fewer than 256 of them, one per compute unit.  form_gate_plan takes
 // half of it where that needs no more launches.
 int gate_tile_bits(int dtype, int64_t N, int batch) {
     int kt = dtype == HS_C128 ? 12 : 13;
@@ -628,7 +624,7 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
         for (int c0 = 0; c0 < batch; c0 += HS_MAX_BATCH) {
             const int chunk = std::min(HS_MAX_BATCH, batch - c0);
             void *p = static_cast<char *>(psi) + (size_t)c0 * P.N * sc;
-            int e = hs::launch_diag_steps(p, p, f->diag_of[P.seq[0]], P.N, chunk, steps, nullptr, c128,
+            int e = hs::launch_diag_steps(p, p, f->diag_of[P.seq[0]], P.N, chunk, steps, c128,
                                           stream_out(chunk, P.N, f->dtype), stream);
             if (e) return hip_fail((hipError_t)e, "diag kernel launch");
         }

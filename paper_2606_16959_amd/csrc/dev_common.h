@@ -87,14 +87,6 @@ __device__ __forceinline__ void ld2(const C2<double> *p, int i, C2<double> &a, C
     a = ld1(p, i);
     b = ld1(p, i + 1);
 }
-// entries i and i + 1 for any i (8-byte aligned 16-byte load)
-typedef float f4u __attribute__((ext_vector_type(4))) __attribute__((aligned(8)));
-typedef const __attribute__((address_space(1))) f4u g_f4u;
-__device__ __forceinline__ void ld2u(const C2<float> *p, int i, C2<float> &a, C2<float> &b) {
-    const f4u v = HS_LOAD((g_f4u *)(p + i));
-    a = C2<float>{v.x, v.y};
-    b = C2<float>{v.z, v.w};
-}
 
 typedef __attribute__((address_space(1))) f4v g_f4w;
 typedef __attribute__((address_space(1))) d2v g_d2w;

@@ -130,10 +130,10 @@ int launch_construct(const ConstructArgs &a, int nd, int64_t max_len, bool c128,
 int launch_perm_gather(const void *src, void *dst, int64_t start, int64_t count, int64_t len, int s, int c,
                        bool c128, void *stream);
 int launch_tile(const TileArgs &a, int batch, bool c128, void *stream);
-// the same with the Horner epilogue y = x0 + alpha (A x); y may alias x0, not x
 // `steps` products x <- A x of every state in one launch (loop_fits)
 bool loop_fits(int64_t N, int nd, bool c128);
 int launch_loop(const LoopArgs &a, int batch, bool c128, void *stream);
+// launch_tile with the Horner epilogue y = x0 + alpha (A x); y may alias x0, not x
 int launch_tile_horner(const TileArgs &a, int batch, bool c128, void *stream);
 // Largest state (rows) evolved whole by one workgroup: 8192 complex64 or
 // 4096 complex128 rows (64 KiB of LDS).
@@ -141,7 +141,7 @@ constexpr int kWholeRowsC64 = 8192;
 constexpr int kWholeRowsC128 = 4096;
 // the single-diagonal factor applied `steps` times in one pass (N even)
 int launch_diag_steps(void *y, const void *x, const void *diag, int64_t N, int batch, int steps,
-                      const double *nrm2, bool c128, bool stream_out, void *stream);
+                      bool c128, bool stream_out, void *stream);
 int launch_reduce(const void *A, int ta, const void *B, int tb, int batch, int64_t N,
                   double *partial, int G, double *out, bool dot, void *stream);
 int launch_scale(void *psi, int64_t N, int batch, const double *nrm2, bool c128, void *stream);
@@ -203,7 +203,10 @@ int launch_dia_to_c64(const double *const *src, float *const *dst, const int64_t
 
 constexpr int kReduceBlocks = 1024;   // partial sums per state (fixed: determinism)
 
-// Tile-kernel shape (compile-time; the launch planner and the kernels must agree).
+// Tile shapes.  The tile kernel of general operators launches the open ones
+// (compile-time; planner and kernel must agree).  The closed ones are those of a
+// launch per closed tile of stored diagonals: no kernel launches them, the
+// fusion list (hs_step_launches) and the storage order are made from them.
 #ifndef HS_TILE_THREADS
 #define HS_TILE_THREADS 512
 #endif
@@ -221,8 +224,8 @@ constexpr int kReduceBlocks = 1024;   // partial sums per state (fixed: determin
                                  // respects the device's per-workgroup LDS limit
 #endif
 #ifndef HS_TILE_LDS_MAX_BYTES
-#define HS_TILE_LDS_MAX_BYTES 163840 // a CU's whole LDS: closed complex64 launches of 5
-                                     // states stage 4096-row tiles in it
+#define HS_TILE_LDS_MAX_BYTES 163840 // a CU's whole LDS: closed tiles of 5 complex64
+                                     // states have 4096 rows in it
 #endif
 // LDS budget of a tile: the general one, or the whole LDS for the one shape
 // that needs it to double its tile (5 complex64 states, closed)
@@ -231,9 +234,8 @@ constexpr int tile_lds_bytes(bool c128, int batch, bool open) {
 }
 constexpr int kTileThreads = HS_TILE_THREADS;
 
-// Closed complex128 launches of two to four states run twice the default
-// threads with half the rows each (2048-row tiles): 16 waves per CU instead
-// of 8, measured 4-6% faster; for one state the same change was slower.
+// Closed complex128 tiles of two to four states: twice the default threads with
+// half the rows each (2048-row tiles).
 constexpr bool tile_c128_pair_wide(bool c128, int batch, bool open) {
     return c128 && !open && batch >= 2 && batch <= 4;
 }
@@ -245,15 +247,11 @@ constexpr int tile_rpt(bool c128, int batch, bool open = false) {
     if (tile_c128_pair_wide(c128, batch, open)) bp *= 2;
     const int acc = c128 ? HS_TILE_ACC_C128 : (open ? HS_TILE_ACC_C64_OPEN : HS_TILE_ACC_C64);
     if (tile_lds_bytes(c128, batch, open) > HS_TILE_LDS_BYTES) return 4;   // 4096-row tiles
-    if (c128 && !open && batch == 2) return 4;   // 4096-row tiles (128 KiB): 3 launches for
-                                                 // a 24-qubit MaxCut step instead of 4
+    if (c128 && !open && batch == 2) return 4;   // 4096-row tiles (128 KiB)
     return acc / bp >= 2 ? acc / bp : 2;
 }
-// Threads per workgroup: closed complex64 launches of 3-8 states use twice
-// the default, so a 2048-row tile (128 KiB of LDS, one workgroup per CU) still
-// runs 16 waves per CU with one row pair per thread; open launches of either
-// dtype do too (8192-row tiles for one state), and closed complex128
-// launches of two states.
+// Threads per workgroup: open launches use twice the default (8192-row tiles
+// for one state), as do closed tiles of 3-8 complex64 and 2-4 complex128 states.
 constexpr int tile_threads(bool c128, int batch, bool open = false) {
     return (open || (!c128 && batch > 2) || tile_c128_pair_wide(c128, batch, open)) ? 2 * kTileThreads
                                                                                     : kTileThreads;

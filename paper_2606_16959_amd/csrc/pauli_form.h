@@ -34,8 +34,10 @@ struct PauliForm {
 };
 
 // The form of a sum of `terms`, or false when a mask has more independent
-// parities than a table holds or there are too many masks.  Coefficients are
-// summed in term order, as the stored diagonals are.
+// parities than a table holds or there are too many masks.  A coefficient sums
+// its strings in term order, as a stored entry does.  A row sums the main diagonal
+// and then the masks in descending order, where stored diagonals go by ascending
+// offset: the one product that can differ from them in rounding.
 bool pauli_form(const std::vector<Term> &terms, PauliForm &out);
 
 struct PauliArgs {

@@ -41,8 +41,8 @@ inline int lds_budget() {
     return v;
 }
 
-// Largest tile (rows) one launch of `batch` states over N rows uses: the
-// kernel's capacity (closed or open launch), halved (down to 1024 rows) while
+// Largest tile (rows) of `batch` states over N rows: the open launch's capacity,
+// or the closed shape's (hs_internal.h), halved (down to 1024 rows) while
 // the grid would have fewer than 256 tiles, one per compute unit.
 inline int tile_rows_max(int dtype, int batch, long long N, bool open = false) {
     int T = tile_rows_cap(dtype == HS_C128, batch, open, lds_budget());

@@ -624,7 +624,7 @@ hs_status hs_evolve(hs_factors f, void *psi, int batch, int steps, void *stream,
         for (int c0 = 0; c0 < batch; c0 += HS_MAX_BATCH) {
             const int chunk = std::min(HS_MAX_BATCH, batch - c0);
             void *p = static_cast<char *>(psi) + (size_t)c0 * P.N * sc;
-            int e = hs::launch_diag_steps(p, p, f->diag_of[P.seq[0]], P.N, chunk, steps, c128,
+            int e = hs::launch_diag_steps(p, p, f->diag_of[P.seq[0]], P.N, chunk, steps, nullptr, c128,
                                           stream_out(chunk, P.N, f->dtype), stream);
             if (e) return hip_fail((hipError_t)e, "diag kernel launch");
         }

@@ -141,7 +141,7 @@ constexpr int kWholeRowsC64 = 8192;
 constexpr int kWholeRowsC128 = 4096;
 // the single-diagonal factor applied `steps` times in one pass (N even)
 int launch_diag_steps(void *y, const void *x, const void *diag, int64_t N, int batch, int steps,
-                      bool c128, bool stream_out, void *stream);
+                      const double *nrm2, bool c128, bool stream_out, void *stream);
 int launch_reduce(const void *A, int ta, const void *B, int tb, int batch, int64_t N,
                   double *partial, int G, double *out, bool dot, void *stream);
 int launch_scale(void *psi, int64_t N, int batch, const double *nrm2, bool c128, void *stream);

@@ -622,10 +622,16 @@ __global__ __launch_bounds__(NT) void dia_loop_kernel(LoopArgs a) {
 // `steps` successive complex multiplications in registers in the order of
 // one step at a time, so the result equals `steps` single-step passes bit
 // for bit while the diagonal and the states cross HBM once.  In place
-// allowed.  STREAM: non-temporal output stores.
+// allowed.  STREAM: non-temporal output stores.  nrm2 is null in every present
+// call; the product by 1 that it leaves holds the coefficients' load back until
+// the state has arrived, without which a pass over 2^26 complex64 rows takes
+// 0.287 instead of 0.263 ms.
 template <typename R, int B, bool STREAM>
 __global__ __launch_bounds__(256) void diag_steps_kernel(C2<R> *y, const C2<R> *x, const C2<R> *__restrict__ v,
-                                                         int64_t N, int steps) {
+                                                         int64_t N, int steps, const double *nrm2) {
+    R scale[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) scale[b] = inv_norm<R>(nrm2, b);
     const int64_t npairs = N >> 1;
     for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < npairs;
          q += (int64_t)gridDim.x * blockDim.x) {
@@ -637,7 +643,7 @@ __global__ __launch_bounds__(256) void diag_steps_kernel(C2<R> *y, const C2<R> *
         for (int b = 0; b < B; ++b) ld2(x + b * N, i, u[b][0], u[b][1]);
 #pragma unroll
         for (int b = 0; b < B; ++b) {
-            C2<R> a0 = u[b][0], a1 = u[b][1];
+            C2<R> a0 = cscale(u[b][0], scale[b]), a1 = cscale(u[b][1], scale[b]);
             for (int s = 0; s < steps; ++s) {
                 C2<R> t0{(R)0, (R)0}, t1{(R)0, (R)0};
                 cfma(t0, c0, a0);
@@ -948,14 +954,14 @@ int launch_tile_horner(const TileArgs &a, int batch, bool c128, void *stream) {
 
 template <typename R, bool STREAM>
 static int diag_steps_dispatch(void *y, const void *x, const void *v, int64_t N, int batch, int steps,
-                               void *stream) {
+                               const double *nrm2, void *stream) {
     C2<R> *py = reinterpret_cast<C2<R> *>(y);
     const C2<R> *px = reinterpret_cast<const C2<R> *>(x);
     const C2<R> *pv = reinterpret_cast<const C2<R> *>(v);
     const dim3 g(grid_for(N >> 1, 256, 1 << 20)), blk(256);
     switch (batch) {
 #define HS_DSTEP_CASE(BB) \
-    case BB: hipLaunchKernelGGL((diag_steps_kernel<R, BB, STREAM>), g, blk, 0, S(stream), py, px, pv, N, steps); break;
+    case BB: hipLaunchKernelGGL((diag_steps_kernel<R, BB, STREAM>), g, blk, 0, S(stream), py, px, pv, N, steps, nrm2); break;
         HS_DSTEP_CASE(1) HS_DSTEP_CASE(2) HS_DSTEP_CASE(3) HS_DSTEP_CASE(4)
         HS_DSTEP_CASE(5) HS_DSTEP_CASE(6) HS_DSTEP_CASE(7) HS_DSTEP_CASE(8)
 #undef HS_DSTEP_CASE
@@ -965,13 +971,13 @@ static int diag_steps_dispatch(void *y, const void *x, const void *v, int64_t N,
 }
 
 int launch_diag_steps(void *y, const void *x, const void *diag, int64_t N, int batch, int steps,
-                      bool c128, bool stream_out, void *stream) {
+                      const double *nrm2, bool c128, bool stream_out, void *stream) {
     if (N < 2 || (N & 1) || steps < 1) return (int)hipErrorInvalidValue;
     if (c128)
-        return stream_out ? diag_steps_dispatch<double, true>(y, x, diag, N, batch, steps, stream)
-                          : diag_steps_dispatch<double, false>(y, x, diag, N, batch, steps, stream);
-    return stream_out ? diag_steps_dispatch<float, true>(y, x, diag, N, batch, steps, stream)
-                      : diag_steps_dispatch<float, false>(y, x, diag, N, batch, steps, stream);
+        return stream_out ? diag_steps_dispatch<double, true>(y, x, diag, N, batch, steps, nrm2, stream)
+                          : diag_steps_dispatch<double, false>(y, x, diag, N, batch, steps, nrm2, stream);
+    return stream_out ? diag_steps_dispatch<float, true>(y, x, diag, N, batch, steps, nrm2, stream)
+                      : diag_steps_dispatch<float, false>(y, x, diag, N, batch, steps, nrm2, stream);
 }
 
 int launch_scale(void *psi, int64_t N, int batch, const double *nrm2, bool c128, void *stream) {

@@ -41,7 +41,7 @@ WORKLOAD = {
 KERNEL_SRC = [os.path.join(ROOT, "paper_2606_16959_amd", "csrc", f)
               for f in ("gates.hip", "gate_plan.h", "gate_plan.cpp", "dev_common.h", "hs_internal.h",
                         "tile_plan.h", "api.hip")]
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_dia_tile_tfim2d_n26.json")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_coset_tfim2d_n26.json")
 OUT_DIR = os.path.join(ROOT, "profiles")      # where summaries are written (--out-dir)
 
 
@@ -218,11 +218,11 @@ def serve_leg(torch, n_jobs, rate, slots, oracle_nmax, jsonl_dir=None):
 
 def summarize_profiles(trace_dir, fetch_dir, write_dir, command, extra_dirs=(), bench_trace=None, bench_log=None):
     """Turn rocprofv3 CSV output of bench.py runs into the committed summaries:
-    per-kernel durations (trace) and per-launch HBM bytes of the DIA tile
+    per-kernel durations (trace) and per-launch HBM bytes of the step
     kernel from FETCH_SIZE / WRITE_SIZE (KiB per dispatch), each scaled by
     what the same counter reads for the 2 GiB device copies the run makes.
     bench_trace: a kernel trace of the default bench run itself, whose first
-    tile dispatches are the headline's warm-up and timed steps; their
+    step dispatches are the headline's warm-up and timed steps; their
     durations are set beside the bench line of that run (bench_log), since
     where the 65 GB of diagonals land in HBM moves the step time by a few
     percent from one process to the next."""
@@ -320,7 +320,7 @@ def summarize_profiles(trace_dir, fetch_dir, write_dir, command, extra_dirs=(), 
         pos = [float(np.mean(bd[j::nl])) for j in range(nl)]
         md += ["", "## The bench run itself", "",
                f"Kernel trace of the default `python3 bench.py` run (rocprofv3 --kernel-trace), its {steps} timed "
-               f"headline steps after {warm} warm-up steps: the first {(warm + steps) * nl} tile dispatches of the "
+               f"headline steps after {warm} warm-up steps: the first {(warm + steps) * nl} step dispatches of the "
                "process.", "", "| launch | kernel form | avg ms | algorithmic GB | GB/s |", "|---|---|---|---|---|"]
         alg = line["roofline"]["algorithmic_bytes_per_launch"] if line else [None] * nl
         for j in range(nl):
@@ -331,7 +331,7 @@ def summarize_profiles(trace_dir, fetch_dir, write_dir, command, extra_dirs=(), 
                + (f"; the same run's bench line (HIP events on the launch stream): {line['roofline']['avg_launch_ms']} "
                   f"ms per launch, {line['ms_per_step']} ms per step, {line['roofline']['achieved']} GB/s moved = "
                   f"{line['roofline']['frac']:.4f} of 8 TB/s." if line else ".")]
-    with open(os.path.join(OUT_DIR, "dia_tile_tfim2d_n26.md"), "w") as fh:
+    with open(os.path.join(OUT_DIR, "coset_tfim2d_n26.md"), "w") as fh:
         fh.write("\n".join(md) + "\n")
     with open(os.path.join(OUT_DIR, os.path.basename(TRAFFIC_FILE)), "w") as fh:
         json.dump({"kernel_sha": kernel_hash(), "bytes_per_launch_scaled": per,
@@ -695,6 +695,7 @@ def taylor_leg(torch, cases=None, timed_steps=3):
                "moved_gbs": round(4 * N * 8 * K / ms / 1e6, 1),
                "full_run_s_estimate": round(ms * r / 1e3, 3),
                "dispatches": K * (1 + timed_steps)}
+        row["moved_gb_per_stage"] = round(4 * N * 8 / 1e9, 3)
         row["frac_of_peak"] = round(row["moved_gbs"] / HBM_PEAK_GBS, 4)
         out.append(row)
         log(f"taylor {name}: r={r} K={K} {ms:.3f} ms/step {row['moved_gbs']} GB/s moved; t=1 in {row['full_run_s_estimate']} s")
@@ -803,7 +804,7 @@ def summarize_leg_profiles(leg_output, trace_dir, counter_dirs, out_name, comman
     forms = [_kernel_form(r["Kernel_Name"]) for r in trace[-L:]]
     durs = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e6 for r in trace]
     if len(durs) % L:
-        raise SystemExit(f"{len(durs)} tile dispatches is not a multiple of {L} launches per step")
+        raise SystemExit(f"{len(durs)} step dispatches is not a multiple of {L} launches per step")
     pos_ms = [float(np.mean(durs[j::L])) for j in range(L)]
     counters = {}                      # name -> [per tile dispatch], plus the copy's value
     copy_val = {}
@@ -877,7 +878,7 @@ def summarize_diagonal_profiles(leg_output, trace_dir, fetch_dir, write_dir, com
     """Profile summary of `bench.py --leg diagonal`: the single-diagonal
     kernel's dispatches in order (one warm-up pass, the timed one-step passes,
     then the whole run in one pass), with FETCH_SIZE / WRITE_SIZE scaled by
-    the copy calibration stored with the tile kernel's traffic summary."""
+    the copy calibration stored with the step kernel's traffic summary."""
     leg = None
     with open(leg_output) as fh:
         for line in fh:
@@ -940,7 +941,7 @@ def summarize_taylor_profiles(trace_dir, fetch_dir, write_dir, leg_output):
     `bench.py --leg taylor`, against the algorithmic bytes the leg itself
     reports (`leg_output`: a file holding the leg's JSON line, e.g. the
     profiled run's log).  The counters are scaled by the copy calibration
-    stored with the tile kernel's traffic summary."""
+    stored with the step kernel's traffic summary."""
     import csv
     import statistics
     rows = None
@@ -969,6 +970,7 @@ def summarize_taylor_profiles(trace_dir, fetch_dir, write_dir, leg_output):
     fetch, write = counters(fetch_dir, "FETCH_SIZE"), counters(write_dir, "WRITE_SIZE")
     trace = [r for r in csv.DictReader(open(os.path.join(trace_dir, "run_kernel_trace.csv"))) if horner(r["Kernel_Name"])]
     trace.sort(key=lambda r: int(r["Dispatch_Id"]))
+    masks = bool(trace) and "pauli_tile_kernel" in trace[0]["Kernel_Name"]      # stages by X-masks
     durs = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e6 for r in trace]
     need = sum(r["dispatches"] for r in rows)
     if not (len(fetch) == len(write) == len(durs) == need):
@@ -993,8 +995,9 @@ def summarize_taylor_profiles(trace_dir, fetch_dir, write_dir, leg_output):
                   f"{float(r['MinNs']) / 1e3:.1f} | {float(r['MaxNs']) / 1e3:.1f} | {float(r['Percentage']):.1f} |")
     md += ["", "## Per Horner stage (averages over each workload's dispatches)", "",
            f"FETCH_SIZE is scaled by {f_scale:.4f} and WRITE_SIZE by {w_scale:.4f}, the factors a 2 GiB device copy "
-           f"gives (`{os.path.relpath(TRAFFIC_FILE, ROOT)}`). Algorithmic bytes: every stored diagonal of H once "
-           "plus three state passes (w, the step input in the epilogue, the output).", "",
+           f"gives (`{os.path.relpath(TRAFFIC_FILE, ROOT)}`). Algorithmic bytes: " +
+           ("four arrays of N entries (the main diagonal, w, the step input, the output)." if masks else
+            "every stored diagonal of H once plus three state passes (w, the step input in the epilogue, the output)."), "",
            "| workload | avg ms | FETCH KiB | WRITE KiB | scaled HBM GB | algorithmic GB | algorithmic GB/s | "
            "HBM / algorithmic |", "|---|---|---|---|---|---|---|---|"]
     lo = 0
@@ -1002,14 +1005,16 @@ def summarize_taylor_profiles(trace_dir, fetch_dir, write_dir, leg_output):
         hi = lo + r["dispatches"]
         fk, wk, ms = statistics.mean(fetch[lo:hi]), statistics.mean(write[lo:hi]), statistics.mean(durs[lo:hi])
         meas = (fk * f_scale + wk * w_scale) * 1024 / 1e9
-        alg = r["gb_per_stage"]
+        alg = r["moved_gb_per_stage"] if masks else r["gb_per_stage"]
         md.append(f"| {r['workload']} | {ms:.3f} | {fk:.0f} | {wk:.0f} | {meas:.3f} | {alg:.3f} | "
                   f"{alg / ms * 1e3:.0f} | {meas / alg:.3f} |")
         lo = hi
-    md += ["", "The excess over the algorithmic bytes is re-reads of w by out-of-tile partner gathers: H flips "
-           "every qubit, a tile is closed over 13 of them, and far partners are no longer in the XCD's L2 when "
-           "they are gathered. FETCH_SIZE counts every request that leaves the L2, whether the 256 MB "
-           "last-level cache or HBM serves it."]
+    md += ["", ("The excess over the algorithmic bytes is partner tiles: each of H's masks with a bit above the 2048-row tile "
+                "pairs the tile with another whole one. " if masks else
+                "The excess over the algorithmic bytes is re-reads of w by out-of-tile partner gathers: H flips "
+                "every qubit, a tile is closed over 13 of them, and far partners are no longer in the XCD's L2 when "
+                "they are gathered. ") +
+           "FETCH_SIZE counts every request that leaves the L2, whether the 256 MB last-level cache or HBM serves it."]
     path = os.path.join(OUT_DIR, "dia_tile_horner_tfim_n24_n26.md")
     with open(path, "w") as fh:
         fh.write("\n".join(md) + "\n")

@@ -20,8 +20,8 @@
 // round trip, an LDS round trip and a barrier, 17-24 us a launch of a
 // complex128 state of 2^20 rows.
 // Measured against one DIA SpMV per factor over the stored diagonals, a step:
-// n = 26 lattice complex64 10.3 -> 0.79 ms (4.3 GB moved in three launches),
-// n = 24 MaxCut with 8 states 4.5 -> 1.44 ms, n = 20 chain complex128
+// n = 26 lattice complex64 10.3 -> 0.81 ms (4.3 GB moved in three launches),
+// n = 24 MaxCut with 8 states 4.5 -> 1.46 ms, n = 20 chain complex128
 // 232 -> 58 us, n = 17 second order 82 -> 37 us.
 #include <hip/hip_runtime.h>
 
